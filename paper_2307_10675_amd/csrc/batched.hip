@@ -63,8 +63,8 @@ struct Lds {
   double* Km;      // [k*k] (pq|qp)
   double* hd;      // [k] h'_pp
   double* G;       // [16*16] subspace matrix
-  double* Qp;      // [16*16] eigenvectors of the previous subspace matrix
-  double* Lam;     // [16] its eigenvalues
+  double* Qp;      // [16*16] eigenvectors of the subspace matrix at a restart
+  double* yp;      // [16] its lowest eigenvector (the Ritz vector in the basis)
   int* pidx;       // [kPsMax] packed entries of the P-space block (three-vector solver)
   double* plam;    // [kPsMax + 2] eigenvalues of that block, minus E0; [kPsMax]: the
                    // largest diagonal entry of the block (with pidx[P - 1] it bounds
@@ -75,7 +75,6 @@ struct Lds {
   double* tv;      // [n_sym] working vector, packed scaled
   double* Gs;      // [16*16]
   double* Qv;      // [16*16]
-  double* y;       // [16]
   double* cf;      // [16] projection coefficients
   double* ev;      // [16] sorted eigenvalues
   int* perm;       // [16]
@@ -112,7 +111,7 @@ __host__ __device__ inline int64_t persistent_bytes(int k, int n_str, int n_link
          a16(8 * ns);
 }
 __host__ __device__ inline int64_t transient_bytes(int n_str) {
-  return a16(8 * tri(n_str)) + 8 * (256 + 256 + 16 + 16 + 16) + 4 * 16 + 8 * 32 + 4 * 16 + 16 + 8 * 16 * 24;
+  return a16(8 * tri(n_str)) + 8 * (256 + 256 + 16 + 16) + 4 * 16 + 8 * 32 + 4 * 16 + 16 + 8 * 16 * 24;
 }
 // E slice of one wave, transposed: E[a][o] for one column and the
 // off-diagonal pairs o, 16-string tiles of the longest column by an odd row
@@ -171,7 +170,7 @@ __device__ inline Lds carve(char* base, const IncDev& d, int lds_bytes) {
   p += 8 * 256;
   L.Qp = (double*)p;
   p += 8 * 256;
-  L.Lam = (double*)p;
+  L.yp = (double*)p;
   p += 8 * 16;
   L.plam = (double*)p;
   p += 8 * (kPsMax + 2);
@@ -190,8 +189,6 @@ __device__ inline Lds carve(char* base, const IncDev& d, int lds_bytes) {
   p += 8 * 256;
   L.Qv = (double*)p;
   p += 8 * 256;
-  L.y = (double*)p;
-  p += 8 * 16;
   L.cf = (double*)p;
   p += 8 * 16;
   L.ev = (double*)p;
@@ -738,41 +735,25 @@ __device__ inline void argmin_block(const double* __restrict__ HD, int64_t ns, c
   __syncthreads();
 }
 
-// Subspace eigenproblem of the (m+1)-dimensional matrix G, warm started:
-// with the previous block's eigenpairs (Lam, Qp), G is first rotated to
-// [[diag(Lam), Qp^T g], [., g_mm]] (g = the new column), and Jacobi only
-// has to resolve that arrowhead.  Leaves Lam/Qp for the next call, the
-// sorted eigenvalues in ev/perm and the lowest pair in scal[20] / y.
-__device__ inline void subspace_solve(const Lds& L, int m) {
+// Subspace eigenproblem of the (m+1)-dimensional matrix G: the lowest pair in
+// scal[20] / yp, from lowest_pair where it applies (p: the largest component
+// of the previous subspace's vector, theta its value, yp the vector; after a
+// restart the first unit vector); at a restart, which needs the kept Ritz
+// vectors too, and where it does not apply, from a full Jacobi decomposition
+// (eigenvectors in Qp, sorted eigenvalues in ev / perm).  iscal[1] is the next
+// call's p.
+__device__ inline void subspace_solve(const Lds& L, int m, int p, double theta, bool restart) {
   const int tid = threadIdx.x, n = m + 1;
-  if (tid < 256) {
-    const int i = tid >> 4, j = tid & 15;
-    double gs = 0.0, q = 0.0;
-    if (i < n && j < n) {
-      if (i < m && j < m) {
-        gs = (i == j) ? L.Lam[i] : 0.0;
-        q = L.Qp[i * 16 + j];
-      } else if (i == m && j == m) {
-        gs = L.G[m * 16 + m];
-        q = 1.0;
-      } else {
-        const int r = (i == m) ? j : i;  // entry r of Qp^T g
-        double s = 0.0;
-        for (int l = 0; l < m; ++l) s += L.Qp[l * 16 + r] * L.G[l * 16 + m];
-        gs = s;
-        q = 0.0;
-      }
+  if (tid < 64) {
+    int pn = restart ? -1 : lowest_pair(L.G, n, p, theta, L.yp, &L.scal[20], L.yp);
+    if (pn < 0) {
+      for (int i = tid; i < 256; i += 64) L.Gs[i] = L.G[i];
+      jacobi_lowest(L.Gs, L.Qp, n, &L.scal[20], L.yp, L.ev, L.perm);
+      pn = 0;
+      for (int j = 1; j < n; ++j)
+        if (fabs(L.yp[j]) > fabs(L.yp[pn])) pn = j;
     }
-    L.Gs[tid] = gs;
-    L.Qv[tid] = q;
-  }
-  __syncthreads();
-  if (tid < 64) jacobi_warm(L.Gs, L.Qv, n, &L.scal[20], L.y, L.ev, L.perm);
-  __syncthreads();
-  if (tid < 256) {
-    const int i = tid >> 4;
-    L.Qp[tid] = L.Qv[tid];
-    if ((tid & 15) == 0 && i < n) L.Lam[i] = L.Gs[i * 16 + i];
+    if (tid == 0) L.iscal[1] = pn;
   }
   __syncthreads();
 }
@@ -1529,15 +1510,14 @@ __device__ __forceinline__ void solve_dav(const SolveArgs& A, int pos, char* lds
   const int ew32 = tuned_waves(et_waves_for<float, K>(d, L), A.tune.e_waves[K][1]);
   int phase = (A.precision == IFCI_MIXED) ? 32 : 64;
   int m = 0, iters = 0, status = IFCI_INC_NOT_CONVERGED;
+  int p_large = 0;  // largest component of the Ritz vector in the basis (the kept vectors: the first)
   double theta = 0.0, resid = 1e300;
   const int64_t o = (int64_t)id - A.first;
   const bool evict = A.evict && A.evict[o] != 0;
   const int keep = mmax / 2 < kKeep ? mmax / 2 : kKeep;
   bool staged = false;
   bool w_built = false;
-  // per-wave partial overlaps [kMaxSpace][2][8]: the eigenvector scratch of
-  // subspace_solve, free once it returns
-  double* wpart = L.Qv;
+  double* wpart = L.Qv;  // per-wave partial overlaps [kMaxSpace][2][8]
 
   while (true) {
     // ---- sigma of v_m -> S_m, and G[m][m]
@@ -1569,17 +1549,18 @@ __device__ __forceinline__ void solve_dav(const SolveArgs& A, int pos, char* lds
       for (int u = tix; u < P * P / 4; u += kBatchThreads) ((float4*)Us)[u] = ((const float4*)Ug)[u];
     __syncthreads();
     IFCI_MARK(kPhSigma);
-    subspace_solve(L, m);
-    theta = L.scal[20];
-    IFCI_MARK(kPhSubspace);
     const bool restart = (m + 1 == mmax);
+    subspace_solve(L, m, p_large, theta, restart);
+    theta = L.scal[20];
+    p_large = restart ? 0 : L.iscal[1];
+    IFCI_MARK(kPhSubspace);
     // ---- pass A: x = V y, Ax = S y, r, t
     double rx[NE], rax[NE], rt[NE];
 #pragma unroll
     for (int e = 0; e < NE; ++e) rx[e] = rax[e] = 0.0;
 #pragma unroll 4
     for (int j = 0; j <= m; ++j) {
-      const double yj = L.y[j];
+      const double yj = L.yp[j];
       const double* vj = base + j * sti;
       const double* sj = base + mst + j * sti;
 #pragma unroll
@@ -1682,6 +1663,7 @@ __device__ __forceinline__ void solve_dav(const SolveArgs& A, int pos, char* lds
       }
       for (int i = tid; i < 256; i += blockDim.x) L.G[i] = 0.0;
       m = 0;
+      p_large = 0;
       __syncthreads();
       continue;
     }
@@ -1744,15 +1726,10 @@ __device__ __forceinline__ void solve_dav(const SolveArgs& A, int pos, char* lds
     }
     __syncthreads();
     if (restart) {
-      for (int i = tid; i < 256; i += blockDim.x) {
-        L.G[i] = 0.0;
-        L.Qp[i] = ((i >> 4) == (i & 15)) ? 1.0 : 0.0;
-      }
+      for (int i = tid; i < 256; i += blockDim.x)
+        L.G[i] = ((i >> 4) == (i & 15) && (i & 15) < keep) ? L.ev[i & 15] : 0.0;
+      if (tid < kMaxSpace) L.yp[tid] = tid == 0 ? 1.0 : 0.0;
       __syncthreads();
-      if (tid < keep) {
-        L.G[tid * 16 + tid] = L.ev[tid];
-        L.Lam[tid] = L.ev[tid];
-      }
     }
     // ---- pass C: t -= sum_j c_j B_j; if its norm dropped below half,
     // the overlaps with t' and a second subtraction

@@ -16,18 +16,25 @@
 
 namespace ifci {
 
+constexpr int kNVmax = kMaxSpace + 3;
+
 // Solver state of one increment (device memory, one block of 4096 doubles).
 struct DavState {
   double G[256];   // Rayleigh matrix V^T H V (stride 16)
-  double Gs[256];  // its copy, diagonalised in place
-  double Q[256];   // eigenvectors of Gs
+  double Q[256];   // its eigenvectors (written at a restart)
   double y[16];    // lowest Ritz vector in the subspace basis
   double cf[16];   // V^T t (first orthogonalisation pass)
   double c2[16];   // V^T t (second pass)
   double ev[16];   // Ritz values, increasing
   double theta, E0, resid, tt0, tt, dx, inv, ecore;
   int m, phase, iters, status, restart, action, mb, reorth;
-  int guess, keep, alive, pad[5];
+  int guess, keep, alive, plarge, pad[4];  // plarge: largest component of y (next subspace solve)
+  int perm[16];
+};
+
+// LDS of small_G
+struct SmallG {
+  double g[kNVmax], G[256], Q[256], y[16], ev[16], theta;
   int perm[16];
 };
 
@@ -35,7 +42,7 @@ struct DavState {
 enum { kActContinue = 0, kActDone = 1, kActSwitch = 2, kActMaxIter = 3, kActEvicted = 4 };
 
 constexpr int kPartBlocks = 1024;
-constexpr int kNV = kMaxSpace + 3;
+constexpr int kNV = kNVmax;
 
 // Partial sums of nv values of this block into part_row[0..nv).  Ends with a
 // barrier, so `red` may be reused right away.
@@ -184,6 +191,7 @@ __device__ inline void op_switch(DavState* S, double* Vb, const double* X, int64
     if (threadIdx.x == 0) {
       S->phase = 64;
       S->m = 0;
+      S->plarge = 0;
     }
   }
 }
@@ -250,24 +258,43 @@ __device__ inline void op_normalize(const DavState* __restrict__ S, double* Vb, 
 }
 
 // ---------------------------------------------------------------- small steps
-// One wavefront (64 threads) per increment.  `sh` is kNV doubles of LDS.
+// One wavefront (64 threads) per increment; the scratch arguments are LDS.
 
 // New column of the Rayleigh matrix from the partials of op_dots, then its
-// lowest eigenpair (cyclic Jacobi); counts the iteration and decides whether
-// the next orthogonalisation is preceded by a thick restart.
-__device__ inline void small_G(DavState* S, const double* part, int nblk, int mmax, double* g) {
-  const int m = S->m;
-  reduce_parts(part, nblk, m + 1, g);
-  if (threadIdx.x <= (unsigned)m) {
-    S->G[threadIdx.x * 16 + m] = g[threadIdx.x];
-    S->G[m * 16 + threadIdx.x] = g[threadIdx.x];
+// lowest eigenpair (lowest_pair; a full Jacobi decomposition at a restart or
+// where that does not apply); counts the iteration and decides whether the
+// next orthogonalisation is preceded by a thick restart.
+__device__ inline void small_G(DavState* S, const double* part, int nblk, int mmax, SmallG* sh) {
+  const int m = S->m, n = m + 1, lane = threadIdx.x;
+  const bool restart = n == mmax;
+  for (int i = lane; i < 256; i += 64) sh->G[i] = S->G[i];
+  if (lane < kMaxSpace) sh->y[lane] = S->y[lane];
+  reduce_parts(part, nblk, n, sh->g);
+  if (lane <= m) {
+    const double v = sh->g[lane];
+    sh->G[lane * 16 + m] = v;
+    sh->G[m * 16 + lane] = v;
+    S->G[lane * 16 + m] = v;
+    S->G[m * 16 + lane] = v;
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < 256; i += 64) S->Gs[i] = S->G[i];
-  __syncthreads();
-  jacobi_lowest(S->Gs, S->Q, m + 1, &S->theta, S->y, S->ev, S->perm);
-  if (threadIdx.x == 0) {
-    S->restart = (m + 1 == mmax);
+  int pn = restart ? -1 : lowest_pair(sh->G, n, S->plarge, S->theta, sh->y, &sh->theta, sh->y);
+  if (pn < 0) {
+    jacobi_lowest(sh->G, sh->Q, n, &sh->theta, sh->y, sh->ev, sh->perm);
+    for (int i = lane; i < 256; i += 64) S->Q[i] = sh->Q[i];
+    if (lane < n) {
+      S->ev[lane] = sh->ev[lane];
+      S->perm[lane] = sh->perm[lane];
+    }
+    pn = 0;
+    for (int j = 1; j < n; ++j)
+      if (fabs(sh->y[j]) > fabs(sh->y[pn])) pn = j;
+  }
+  if (lane < n) S->y[lane] = sh->y[lane];
+  if (lane == 0) {
+    S->theta = sh->theta;
+    S->plarge = pn;
+    S->restart = restart;
     S->keep = mmax / 2 < kKeep ? mmax / 2 : kKeep;
     S->iters += 1;
   }
@@ -320,6 +347,8 @@ __device__ inline void small_R(DavState* S) {
   for (int i = 0; i < 256; ++i) S->G[i] = 0.0;
   for (int kk = 0; kk < keep; ++kk) S->G[kk * 16 + kk] = S->ev[kk];
   S->mb = keep - 1;
+  S->plarge = 0;
+  for (int j = 0; j < 16; ++j) S->y[j] = j == 0 ? 1.0 : 0.0;
 }
 
 __device__ inline void small_B(DavState* S, const double* part, int nblk, double* v) {

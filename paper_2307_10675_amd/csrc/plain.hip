@@ -221,6 +221,7 @@ __global__ void init_state_kernel(DavState* S, const double* part, int nblk, dou
     S->action = 0;
     S->ecore = ecore;
     S->keep = 0;
+    S->plarge = 0;
     S->theta = 0.0;
     S->resid = 1e300;
   }
@@ -237,8 +238,8 @@ __global__ void __launch_bounds__(256) dots_kernel(const double* __restrict__ Vb
 }
 
 __global__ void __launch_bounds__(64) small_G_kernel(DavState* S, const double* part, int nblk, int mmax) {
-  __shared__ double g[kNV];
-  small_G(S, part, nblk, mmax, g);
+  __shared__ SmallG sh;
+  small_G(S, part, nblk, mmax, &sh);
 }
 
 __global__ void __launch_bounds__(256) passA_kernel(const DavState* __restrict__ S, double* Vb, double* Sb,

@@ -112,6 +112,7 @@ __global__ void __launch_bounds__(64) wb_init_kernel(WideItem* const* it, int n,
       S->action = kActContinue;
       S->ecore = w->B[int_block(w->d.k).misc];
       S->keep = 0;
+      S->plarge = 0;
       S->theta = 0.0;
       S->resid = 1e300;
       S->alive = 1;
@@ -345,9 +346,9 @@ __global__ void __launch_bounds__(kVecThreads) wb_dots_kernel(WideItem* const* i
 }
 
 __global__ void __launch_bounds__(64) wb_small_G_kernel(WideItem* const* it, const int* ctl, int cap) {
-  __shared__ double g[kNV];
+  __shared__ SmallG sh;
   WB_SMALL_LOOP(kAll)
-  small_G(S, w->part, nb, w->mmax, g);
+  small_G(S, w->part, nb, w->mmax, &sh);
   __syncthreads();
   }
 }
