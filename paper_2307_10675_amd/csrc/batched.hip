@@ -20,10 +20,11 @@
 // product over the B operands already formed for the MFMA (one FMA per
 // operand), which at 8 orbitals saves the third 16-row tile (28 off-diagonal
 // pairs of 36).
-// Each wavefront owns one beta column b at a time: it computes E for the
-// whole column in its private LDS slice (stored transposed, E[a][P]) and
-// gathers S[:, b] from it, so no workgroup barrier sits inside the column
-// loop.  The MFMA B operand is built without dependent loads: the alpha
+// Each wavefront owns one beta column b at a time, so no workgroup barrier
+// sits inside the column loop.  In FP32 it computes E for the whole column in
+// its private LDS slice (stored transposed, E[a][P]) and gathers S[:, b] from
+// it; in FP64 it adds each E straight into its private copy of S[:, b]
+// (sigma_scatter).  The MFMA B operand is built without dependent loads: the alpha
 // part reads a per-wave copy of column b (and its negation) at offsets held
 // in registers for the whole sigma, the beta part reads C at a per-column
 // row offset plus a compile-time tile offset.  The packed sigma slot of
@@ -69,9 +70,12 @@ struct Lds {
   double* plam;    // [kPsMax + 2] eigenvalues of that block, minus E0; [kPsMax]: the
                    // largest diagonal entry of the block (with pidx[P - 1] it bounds
                    // the block in (H_II, I) order)
-  double* cp;      // CI vector, full (n+1) x (n+1) of T with a zero last row and column
+  double* cp;      // FP32: CI vector, full (n+1) x (n+1) with a zero last row and column;
+                   // FP64: per wave, the column copy and the column accumulator
   double* sp;      // [n_sym] sigma accumulator, packed scaled
-  // transient (overlaid by the E slices during sigma)
+  double* c64;     // FP64: CI vector, full (n+1) x (n+1) with a zero last row (past the transient
+                   // part; written when a vector is staged, free once its sigma is done)
+  // transient (overlaid by the E slices during an FP32 sigma)
   double* tv;      // [n_sym] working vector, packed scaled
   double* Gs;      // [16*16]
   double* Qv;      // [16*16]
@@ -87,33 +91,35 @@ struct Lds {
 
 __host__ __device__ inline int64_t a16(int64_t x) { return (x + 15) & ~int64_t(15); }
 
-// CI vector in LDS: FP64 packed with a zero tail of n+1 entries, or FP32
-// full (n+1) x (n+1) with a zero last row and column.
-__host__ __device__ inline int64_t cp_bytes(int n_str) {
-  const int64_t a = 8 * (tri(n_str) + n_str + 1), b = 4 * (int64_t)(n_str + 1) * (n_str + 1);
+// FP64 sigma, per wave: a column of C, its negation and 16 zeros (read where
+// a string has no link), then the column accumulator with a negated twin and
+// 16 dump entries (added to where there is no link), laid out alike.
+__host__ __device__ constexpr int col64_entries(int k) { return 2 * (max_strings(k) + 1) + 16; }
+// CI vector in LDS: FP32 full (n+1) x (n+1) with a zero last row and column;
+// in an FP64 sigma the same bytes hold the waves' column pairs.
+__host__ __device__ inline int64_t cp_bytes(int k, int n_str) {
+  const int64_t a = 8LL * 8 * 2 * col64_entries(k), b = 4 * (int64_t)(n_str + 1) * (n_str + 1);
   return a16(a > b ? a : b);
 }
+__host__ __device__ inline int64_t c64_bytes(int n_str) { return a16(8 * (int64_t)(n_str + 1) * (n_str + 1)); }
 // pair count padded to the MFMA k-step
 __host__ __device__ inline int npair_pad(int k) { return (k * (k + 1) / 2 + 3) / 4 * 4; }
 // int16 table of (n+1) x npair_pad entries
 __host__ __device__ inline int64_t ptab_bytes(int k, int n_str) {
   return a16(2 * (int64_t)(n_str + 1) * npair_pad(k));
 }
-// column copies: eight waves of floats, or of doubles when that stays small
-__host__ __device__ inline int64_t colb_bytes(int n_str) {
-  const int64_t e = 2 * (int64_t)(n_str + 1);
-  return a16(n_str <= 64 ? 8 * 8 * e : 8 * 4 * e);
-}
+// FP32 column copies of eight waves
+__host__ __device__ inline int64_t colb_bytes(int n_str) { return a16(8 * 4 * 2 * (int64_t)(n_str + 1)); }
 __host__ __device__ inline int64_t persistent_bytes(int k, int n_str, int n_link) {
   const int64_t ns = tri(n_str);
   return colb_bytes(n_str) + ptab_bytes(k, n_str) + a16(4 * (int64_t)n_str * n_link) + a16(4 * n_str) +
-         a16(8 * n_str) + a16(8 * (2 * k * k + k)) + 8 * (256 + 256 + 16) + 12 * kPsMax + 16 + cp_bytes(n_str) +
+         a16(8 * n_str) + a16(8 * (2 * k * k + k)) + 8 * (256 + 256 + 16) + 12 * kPsMax + 16 + cp_bytes(k, n_str) +
          a16(8 * ns);
 }
 __host__ __device__ inline int64_t transient_bytes(int n_str) {
   return a16(8 * tri(n_str)) + 8 * (256 + 256 + 16 + 16) + 4 * 16 + 8 * 32 + 4 * 16 + 16 + 8 * 16 * 24;
 }
-// E slice of one wave, transposed: E[a][o] for one column and the
+// FP32 E slice of one wave, transposed: E[a][o] for one column and the
 // off-diagonal pairs o, 16-string tiles of the longest column by an odd row
 // stride of at least 17 (n_off | 1), and a spare tail for the padding rows of
 // the last MFMA tile.  With a stride of at least 16 the padding rows
@@ -131,8 +137,8 @@ __host__ __device__ constexpr int wt_stride(int k) { return slice_rows(k) | 16; 
 // of V it is summed from, of T, at the start of the sigma scratch (ahead of
 // the E slices).
 // FP32 A fragments of the off-diagonal rows of V in lane order,
-// [MT][KS][64] floats (FP64 reads its fragments from V for each sigma: the
-// FP64 copy would cost an E slice at 8 orbitals).
+// [MT][KS][64] floats (FP64 reads its fragments from V for each sigma: its
+// copy does not fit beside the full FP64 vector at 8 orbitals).
 __host__ __device__ inline int64_t afr_bytes(int k, int elem) {
   const int mt = (k * (k - 1) / 2 + 15) / 16;
   return elem == 4 ? a16((int64_t)(mt > 0 ? mt : 1) * (npair_pad(k) / 4) * 64 * elem) : 0;
@@ -177,7 +183,7 @@ __device__ inline Lds carve(char* base, const IncDev& d, int lds_bytes) {
   L.pidx = (int*)p;
   p += 4 * kPsMax;
   L.cp = (double*)p;
-  p += cp_bytes(n);
+  p += cp_bytes(k, n);
   L.sp = (double*)p;
   p += a16(8 * d.n_sym);
   // transient
@@ -201,6 +207,7 @@ __device__ inline Lds carve(char* base, const IncDev& d, int lds_bytes) {
   p += 4 * 16;
   p = (char*)(((uintptr_t)p + 15) & ~(uintptr_t)15);
   L.red = (double*)p;
+  L.c64 = (double*)(L.et + a16(transient_bytes(n)));
   return L;
 }
 
@@ -215,102 +222,279 @@ __device__ __forceinline__ int pk32(int x, int y) {
   return x <= y ? ((y * (y + 1)) >> 1) + x : ((x * (x + 1)) >> 1) + y;
 }
 
-// ---------------------------------------------------------------------------
-// Sigma of the CI vector in L.cp (unscaled; FP32 full (n+1) x (n+1) with a
-// zero last row and column, FP64 packed with a zero tail), accumulated into
-// L.sp (packed, scaled, must be zero).
-// V holds the pair contraction matrix; shift is subtracted from its
-// (diagonal pair, diagonal pair) block, which subtracts shift * N / N^2 * N
-// = shift from the operator.
+// Pair at position q of the contraction order used by both sigmas: the
+// off-diagonal pairs (p > r, at p (p - 1) / 2 + r) first, so that position
+// and MFMA row agree, then the diagonal ones; the packed index Q = p (p + 1) /
+// 2 + r of V.
+__host__ __device__ inline int pair_at(int k, int q) {
+  const int no = k * (k - 1) / 2;
+  if (q >= no) return (q - no) * (q - no + 3) / 2;
+  int p = 1;
+  while (p * (p + 1) / 2 <= q) ++p;
+  return q + p;
+}
+
+// Diagonal-pair weights w[q][a] = sum over the orbitals p of string a of
+// V[pp][pair q] (shifted in the diagonal block), summed in a fixed order from
+// the rows u[p][q]; zero for padding pairs and strings a >= n.  They sit at
+// the end of the scratch region, which neither the E slices nor the solver's
+// transient data reach, so a caller that keeps V, the shift and T builds them
+// once and reuses them for later sigmas.  FP32 stores its A fragments V[pair
+// o = 16 m + lane % 16][pair 4 s + lane / 16] in lane order beside them.
+// Ends with a barrier.
 template <typename T, int K>
-__device__ __forceinline__ void sigma_sector(const IncDev& d, const Lds& L, const double* __restrict__ V,
-                                             double shift, int et_waves, bool build_w) {
+__device__ __forceinline__ T fragment(const double* __restrict__ V, int m, int s, int ln) {
+  constexpr int NP = K * (K + 1) / 2, NO = K * (K - 1) / 2;
+  const int o = 16 * m + (ln & 15), q = 4 * s + (ln >> 4);
+  return (T)(o < NO && q < NP ? V[pair_at(K, o) * NP + pair_at(K, q)] : 0.0);
+}
+template <typename T, int K>
+__device__ __forceinline__ void build_weights(const IncDev& d, const Lds& L, const double* __restrict__ V,
+                                              double shift) {
+  constexpr int NP = K * (K + 1) / 2, NO = K * (K - 1) / 2, MT = (NO + 15) / 16, KS = (NP + 3) / 4;
+  constexpr int NPp = 4 * KS, WS = wt_stride(K);
+  const double nel = 2.0 * d.na;
+  const double sh = nel > 0.0 ? shift / (nel * nel) : 0.0;
+  T* const wt = (T*)(L.et + wt_offset(L, K, (int)sizeof(T)));
+  T* const ut = (T*)((char*)wt + a16((int64_t)NPp * WS * (int64_t)sizeof(T)));
+  T* const afl = (T*)((char*)ut + a16((int64_t)K * NPp * (int64_t)sizeof(T)));
+  if (sizeof(T) == 4)
+    for (int i = threadIdx.x; i < (MT > 0 ? MT : 1) * KS * 64; i += blockDim.x) {
+      const int ms = i >> 6, m = ms / KS;
+      afl[i] = fragment<T, K>(V, m, ms - m * KS, i & 63);
+    }
+  for (int i = threadIdx.x; i < K * NPp; i += blockDim.x) {
+    const int p = i / NPp, q = i - p * NPp;
+    double v = 0.0;
+    if (q < NP) {
+      v = V[(p * (p + 3) / 2) * NP + pair_at(K, q)];
+      if (q >= NO) v -= sh;
+    }
+    ut[i] = (T)v;
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < NPp * WS; i += blockDim.x) {
+    const int q = i / WS, a = i - q * WS;
+    T v = (T)0;
+    if (a < d.n_str && q < NP) {
+      uint32_t occ = (uint32_t)L.strs[a];
+      while (occ) {
+        const int p = __builtin_ctz(occ);
+        occ &= occ - 1u;
+        v += ut[p * NPp + q];
+      }
+    }
+    wt[i] = v;
+  }
+  __syncthreads();
+}
+
+// ---------------------------------------------------------------------------
+// FP64 sigma of the CI vector in L.c64 (unscaled, full, with a zero last row),
+// accumulated into L.sp (packed, scaled, must be zero).  V and shift as in
+// sigma_sector below, of which this is the FP64 form: the same columns and
+// operands, but the E of a column is never stored.  Accumulator register r
+// of row tile m holds pair 4 (4 m + r) + lane / 16 of string 16 t + lane % 16,
+// whose table entry is the one that the lane read D through at k-step 4 m +
+// r, and E_P is symmetric, so the lane adds the register straight into the
+// wave's copy of S[:, b] at that entry (ds_add_f64), which has the same layout
+// as its copy of column b (sign twins included).  An E slice per wave (18.6
+// KB) left room for four of the eight waves at 8 orbitals, one per SIMD; the
+// column pair takes 2.5 KB, all eight run, and the link decoding of the gather
+// goes.  LDS adds are 8 to 27 cycles a wave and instruction (measured;
+// ds_add_f32 takes 192, which is why FP32 keeps its slices): 35 of them beside
+// 90 MFMAs of 64 cycles a column.  8o8e sigma in a full launch 306k -> 205k
+// cycles (100k of MFMA per SIMD).
+template <int K>
+__device__ __forceinline__ void sigma_scatter(const IncDev& d, const Lds& L, const double* __restrict__ V, int waves) {
+  constexpr int NP = K * (K + 1) / 2, NO = K * (K - 1) / 2, MT = (NO + 15) / 16, MTA = MT > 0 ? MT : 1;
+  constexpr int KS = (NP + 3) / 4, NPp = 4 * KS, WS = wt_stride(K), NTM = slice_rows(K) / 16;
+  constexpr int CE = col64_entries(K);
+  typedef Mfma<double> M;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (wave >= waves) return;
+  const int n = d.n_str, ld = n + 1, kq = lane >> 4, col = lane & 15;
+  const double* const c64 = L.c64;
+  const double* const wl = (const double*)(L.et + wt_offset(L, K, 8)) + kq * WS + col;
+  const int16_t* pt = (const int16_t*)L.ptab;  // [a][q]: J | neg << 15, J = n: none
+  double* const colb = L.cp + wave * (2 * CE);
+  double* const scol = colb + CE;
+  double afr[MTA][KS];
+#pragma unroll
+  for (int m = 0; m < MTA; ++m)
+#pragma unroll
+    for (int s = 0; s < KS; ++s) afr[m][s] = fragment<double, K>(V, m, s, lane);
+  // entry of (string 16 t + col, position 4 s + kq) in the column copy and the
+  // accumulator, as an LDS byte offset, two a register: J, ld + J (negated),
+  // or where there is no link one of 16 entries (zeros of the copy, dump of
+  // the accumulator) chosen by col, which spreads the adds that go nowhere
+  constexpr int NA = NTM * KS;
+  uint32_t ia[(NA + 1) / 2];
+  const uint32_t colb_off = (uint32_t)((const char*)colb - L.root);
+#pragma unroll
+  for (int i = 0; i < (NA + 1) / 2; ++i) ia[i] = 0;
+#pragma unroll
+  for (int t = 0; t < NTM; ++t)
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const int a = min(16 * t + col, n);
+      const int e = (int)(uint16_t)pt[a * NPp + 4 * s + kq];
+      const int J = e & 0x7FFF;
+      const int j = J >= n ? 2 * ld + col : J + (e >> 15) * ld;
+      const int i = t * KS + s;
+      ia[i >> 1] |= (colb_off + 8u * (uint32_t)j) << (16 * (i & 1));
+    }
+  for (int j = lane; j < 2 * ld + 16; j += 64) {
+    scol[j] = 0.0;
+    if (j >= 2 * ld) colb[j] = 0.0;
+  }
+  const uint32_t c64_off = (uint32_t)((const char*)c64 - L.root);
+  double sg[KS];
+  uint32_t r2[KS];  // byte offset of C[J2][col]
+  auto column_setup = [&](int bb) {
+    for (int j = lane; j < ld; j += 64) {
+      const double v = j < n ? c64[bb * ld + j] : 0.0;  // C is symmetric: row b
+      colb[j] = v;
+      colb[ld + j] = -v;
+    }
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const int e = (int)(uint16_t)pt[bb * NPp + 4 * s + kq];
+      sg[s] = (e & 0x8000) ? -1.0 : 1.0;
+      r2[s] = c64_off + 8u * (uint32_t)((e & 0x7FFF) * ld + col);
+    }
+  };
+  if (wave < n) column_setup(wave);
+  for (int b = wave; b < n; b += waves) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int i = 0; i < (NA + 1) / 2; ++i) asm volatile("" : "+v"(ia[i]));  // keep the offsets packed
+    double dext0 = 0.0, dext1 = 0.0;  // diagonal-pair part of strings lane and 64 + lane
+    auto tiles = [&](auto tt, auto cnt) {
+      constexpr int t = decltype(tt)::value, C = decltype(cnt)::value;
+      M::acc acc[C][MTA];
+#pragma unroll
+      for (int c = 0; c < C; ++c)
+#pragma unroll
+        for (int m = 0; m < MTA; ++m) acc[c][m] = M::zero();
+      auto off = [&](int tc, int s) -> uint32_t {
+        const int i = tc * KS + s;
+        return (ia[i >> 1] >> (16 * (i & 1))) & 0xFFFFu;
+      };
+      auto alpha = [&](int tc, int s) -> double { return *(const double*)(L.root + off(tc, s)); };
+      auto beta = [&](int tc, int s) -> double { return *(const double*)(L.root + r2[s] + 128 * tc); };
+      double va[C], vb[C], wv[C], dsum[C];
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        va[c] = alpha(t + c, 0);
+        vb[c] = beta(t + c, 0);
+        wv[c] = wl[16 * (t + c)];
+        dsum[c] = 0.0;
+      }
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        double bo[C];
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+          bo[c] = fma_t(sg[s], vb[c], va[c]);
+          dsum[c] = fma_t(wv[c], bo[c], dsum[c]);
+        }
+        if (s + 1 < KS) {  // loads of step s + 1 ahead of the MFMAs of step s
+#pragma unroll
+          for (int c = 0; c < C; ++c) {
+            va[c] = alpha(t + c, s + 1);
+            vb[c] = beta(t + c, s + 1);
+            wv[c] = wl[4 * (s + 1) * WS + 16 * (t + c)];
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+          for (int c = 0; c < C; ++c) acc[c][m] = M::mma(afr[m][s], bo[c], acc[c][m]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        const double v = rows_sum(dsum[c]);  // string 16 (t + c) + col, in every row of lanes
+        if (t + c < 4) {
+          if (kq == t + c) dext0 = v;
+        } else {
+          dext1 = v;
+        }
+      }
+      // (unpack the offsets again: kept from the loads above they would spill)
+#pragma unroll
+      for (int i = t * KS / 2; i < ((t + C) * KS + 1) / 2; ++i) asm volatile("" : "+v"(ia[i]));
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (16 * m + 4 * r < NO) {
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+              lds_add((double*)(L.root + off(t + c, 4 * m + r)) + CE, acc[c][m][r]);
+          }
+    };
+    static_for<0, (NTM + 1) / 2>([&](auto hp) {
+      constexpr int t = 2 * decltype(hp)::value;
+      const int nt_count = (n + 15) / 16;
+      if (t + 1 < nt_count && t + 1 < NTM)
+        tiles(std::integral_constant<int, t>{}, std::integral_constant<int, t + 1 < NTM ? 2 : 1>{});
+      else if (t < nt_count)
+        tiles(std::integral_constant<int, t>{}, std::integral_constant<int, 1>{});
+    });
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    if (b + waves < n) column_setup(b + waves);
+    auto finish = [&](int a, double dext) {
+      const double v = scol[a] - scol[ld + a] + dext;
+      scol[a] = 0.0;
+      scol[ld + a] = 0.0;
+      lds_add(&L.sp[pk32(a, b)], (a == b ? 2.0 : kSqrt2) * v);
+    };
+    if (lane < n) finish(lane, dext0);
+    if (max_strings(K) > 64 && lane < n - 64) finish(64 + lane, dext1);
+  }
+}
+
+// FP32 sigma of the CI vector in L.cp (unscaled, full (n+1) x (n+1) with a
+// zero last row and column), accumulated into L.sp (packed, scaled, must be
+// zero).
+// V holds the pair contraction matrix; its shift, subtracted from the
+// (diagonal pair, diagonal pair) block (shift * N / N^2 * N = shift taken from
+// the operator), enters through the diagonal-pair weights only.
+template <int K>
+__device__ __forceinline__ void sigma_sector(const IncDev& d, const Lds& L, int et_waves) {
+  typedef float T;
   constexpr int NP = K * (K + 1) / 2;
   constexpr int NO = K * (K - 1) / 2;       // off-diagonal pairs: the MFMA rows
   constexpr int MT = (NO + 15) / 16;        // 0 at one orbital
   constexpr int MTA = MT > 0 ? MT : 1;      // array extent
   constexpr int KS = (NP + 3) / 4;
   typedef Mfma<T> M;
-  // bit P set for the diagonal pairs P = i (i + 3) / 2 (the pair (i, i))
-  constexpr uint64_t kDiagPairs = [] {
-    uint64_t m = 0;
-    for (int i = 0; i < K; ++i) m |= 1ull << (i * (i + 3) / 2);
-    return m;
-  }();
-  static_assert(NP <= 64, "pair mask holds 64 pairs");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n = d.n_str, nlink = d.n_link - d.na;  // off-diagonal links per string
   const int lstride = d.n_link;                     // row stride of the link table
   const T* cp = (const T*)L.cp;
-  const double nel = 2.0 * d.na;
-  const double sh = nel > 0.0 ? shift / (nel * nel) : 0.0;
   constexpr int NPp = 4 * KS;
   constexpr int WS = wt_stride(K);
-
-  // Diagonal-pair weights w[Q][a] = sum over the orbitals p of string a of
-  // V[pp][Q] (shifted in the diagonal block), summed in a fixed order from
-  // the rows u[p][Q]; zero for padding pairs and strings a >= n.  They sit
-  // at the end of the scratch region, which neither the E slices nor the
-  // solver's transient data reach, so a caller that keeps V, the shift and
-  // T builds them once (build_w) and reuses them for later sigmas.
-  T* const wt = (T*)(L.et + wt_offset(L, K, (int)sizeof(T)));
-  T* const ut = (T*)((char*)wt + a16((int64_t)NPp * WS * (int64_t)sizeof(T)));
-  // A fragments: V[P(16 m + lane % 16)][4 s + lane / 16] for the off-diagonal
-  // pair P(o) = o + p of row o (p the larger orbital of the pair); FP32
-  // stores them in lane order beside the weights, built with them
-  constexpr bool kAfrLds = sizeof(T) == 4;
-  T* const afl = (T*)((char*)ut + a16((int64_t)K * NPp * (int64_t)sizeof(T)));
-  auto afr_value = [&](int m, int sq, int ln) -> T {
-    const int o = 16 * m + (ln & 15), Q = 4 * sq + (ln >> 4);
-    double v = 0.0;
-    if (m < MT && o < NO && Q < NP) {
-      int p = 1;
-      while (p * (p + 1) / 2 <= o) ++p;
-      v = V[(o + p) * NP + Q];
-    }
-    return (T)v;
-  };
-  if (build_w) {
-  for (int i = threadIdx.x; kAfrLds && i < MTA * KS * 64; i += blockDim.x) {
-    const int ms = i >> 6, m = ms / KS;
-    afl[i] = afr_value(m, ms - m * KS, i & 63);
-  }
-  for (int i = threadIdx.x; i < K * NPp; i += blockDim.x) {
-    const int p = i / NPp, Q = i - p * NPp;
-    double v = 0.0;
-    if (Q < NP) {
-      v = V[(p * (p + 3) / 2) * NP + Q];
-      if ((kDiagPairs >> Q) & 1) v -= sh;
-    }
-    ut[i] = (T)v;
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < NPp * WS; i += blockDim.x) {
-    const int Q = i / WS, a = i - Q * WS;
-    T v = (T)0;
-    if (a < n && Q < NP) {
-      uint32_t occ = (uint32_t)L.strs[a];
-      while (occ) {
-        const int p = __builtin_ctz(occ);
-        occ &= occ - 1u;
-        v += ut[p * NPp + Q];
-      }
-    }
-    wt[i] = v;
-  }
-  __syncthreads();
-  }
+  const T* const wt = (const T*)(L.et + wt_offset(L, K, (int)sizeof(T)));
+  const T* const ut = (const T*)((const char*)wt + a16((int64_t)NPp * WS * (int64_t)sizeof(T)));
+  const T* const afl = (const T*)((const char*)ut + a16((int64_t)K * NPp * (int64_t)sizeof(T)));
 
   if (wave >= et_waves) return;
   T afr[MTA][KS];
 #pragma unroll
   for (int m = 0; m < MTA; ++m)
 #pragma unroll
-    for (int s = 0; s < KS; ++s) afr[m][s] = kAfrLds ? afl[(m * KS + s) * 64 + lane] : afr_value(m, s, lane);
+    for (int s = 0; s < KS; ++s) afr[m][s] = afl[(m * KS + s) * 64 + lane];
   constexpr int NTM = slice_rows(K) / 16;  // 16-string tiles of the longest column
   constexpr int NS = slice_stride(K);      // E slice row stride (odd, >= 17)
   static_assert(NS >= 16 && 16 * MT - NS <= NS, "padding rows must stay within the next row's first tiles");
-  constexpr bool kFull = sizeof(T) == 4;   // FP32: full layout, FP64: packed
   const int nt_count = (n + 15) / 16;
   const int kq = lane >> 4, col = lane & 15;
   const int ld = n + 1;
@@ -329,7 +513,7 @@ __device__ __forceinline__ void sigma_sector(const IncDev& d, const Lds& L, cons
   // offsets a register.  A missing link, a padding pair and a string a >= n
   // address colb[n] = 0.  The beta part reads C[a][J2] = C[J2][a] with the
   // sign of (b, Q) applied in a fused multiply-add; J2 = n (no link) reads
-  // the zero row (FP32) or the zero tail (FP64).  No load depends on another.
+  // the zero row.  No load depends on another.
   constexpr int NA = NTM * KS;
   uint32_t ia[(NA + 1) / 2];
 #pragma unroll
@@ -351,14 +535,12 @@ __device__ __forceinline__ void sigma_sector(const IncDev& d, const Lds& L, cons
   // reads the slice's zero entry.  Pass 0: string a = lane, all its links.
   // Pass 1 (more than 64 strings, 8 orbitals): strings 64 + lane / 8, three
   // links per lane, summed over the 8 lanes of a string in a fixed tree.
-  // FP32 keeps the codes in registers for every column; FP64 has no
-  // registers to spare and decodes them per column.
+  // The codes stay in registers for every column.
   constexpr int LM = (K / 2) * ((K + 1) / 2);  // max of na (K - na): off-diagonal links
   constexpr int LP = LM > 0 ? (LM + 1) / 2 : 1;
   constexpr bool kTwoPass = max_strings(K) > 64;
   static_assert(!kTwoPass || (LM <= 24 && max_strings(K) <= 64 + 8), "pass 1 covers 8 strings of 24 links");
   constexpr int ZI = slice_rows(K) * NS + 16;  // zero entry of the slice
-  constexpr bool kLinkRegs = kFull;
   auto code_of = [&](int a, int l) -> uint32_t {
     if (a < n && l < nlink) {
       const int code = L.links[a * lstride + l];
@@ -376,8 +558,8 @@ __device__ __forceinline__ void sigma_sector(const IncDev& d, const Lds& L, cons
       lk1[1] = code_of(a1, l1 + 2);
     }
   };
-  uint32_t lk0_keep[LP], lk1_keep[2];
-  if (kLinkRegs) link_codes(lk0_keep, lk1_keep);
+  uint32_t lk0[LP], lk1[2];
+  link_codes(lk0, lk1);
   if (lane == 0) et[ZI] = (T)0;
 
   // MFMA output row of (lane, r) within a 16-row tile, and the lane's store
@@ -388,21 +570,19 @@ __device__ __forceinline__ void sigma_sector(const IncDev& d, const Lds& L, cons
   // per column: the wave's copy of column b and its negation (row n / the
   // tail is zero), and the beta part (one entry per k-step of this lane).
   // The next column's are prepared while the current one is gathered.
-  int j2[KS];
   T sg[KS];
-  uint32_t r2[KS];  // FP32: byte offset of C[J2][col]
+  uint32_t r2[KS];  // byte offset of C[J2][col]
   auto column_setup = [&](int bb) {
     for (int j = lane; j < ld; j += 64) {
-      const T v = kFull ? cp[j * ld + bb] : cp[pk32(j, bb)];
+      const T v = cp[j * ld + bb];
       colb[j] = v;
       colb[ld + j] = -v;
     }
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       const int e = (int)(uint16_t)pt[bb * NPp + 4 * s + kq];
-      j2[s] = e & 0x7FFF;
       sg[s] = (e & 0x8000) ? (T)-1 : (T)1;
-      r2[s] = cp_off + (uint32_t)((j2[s] * ld + col) * (int)sizeof(T));
+      r2[s] = cp_off + (uint32_t)(((e & 0x7FFF) * ld + col) * (int)sizeof(T));
     }
   };
   if (wave < n) column_setup(wave);
@@ -417,16 +597,10 @@ __device__ __forceinline__ void sigma_sector(const IncDev& d, const Lds& L, cons
     // them once before the loop into twice as many registers and spills.
 #pragma unroll
     for (int i = 0; i < (NA + 1) / 2; ++i) asm volatile("" : "+v"(ia[i]));
-    if (kLinkRegs) {
 #pragma unroll
-      for (int i = 0; i < LP; ++i) asm volatile("" : "+v"(lk0_keep[i]));
-    }
+    for (int i = 0; i < LP; ++i) asm volatile("" : "+v"(lk0[i]));
 
-    auto beta = [&](int t, int s) -> T {
-      if (kFull) return *(const T*)(L.root + r2[s] + 16 * t * sizeof(T));
-      const int a = min(16 * t + col, n);  // a = n: the zero tail
-      return cp[pk32(a, j2[s])];
-    };
+    auto beta = [&](int t, int s) -> T { return *(const T*)(L.root + r2[s] + 16 * t * sizeof(T)); };
     // E[:, (a, b)] for C consecutive 16-string tiles from tile t on (C
     // independent MFMA chains per row tile), stored transposed into the
     // wave's slice.  Rows a >= n of the slice are padding.  The last MFMA
@@ -504,10 +678,10 @@ __device__ __forceinline__ void sigma_sector(const IncDev& d, const Lds& L, cons
         if (mm == 0) asm volatile("" ::: "memory");
       }
     };
-    // FP32 columns of full length run all their tiles in one pass (one
+    // columns of full length run all their tiles in one pass (one
     // accumulator drain per column, MT x NTM independent MFMAs per k-step);
     // otherwise pairs of tiles
-    if (kFull && nt_count == NTM) {
+    if (nt_count == NTM) {
       tiles(std::integral_constant<int, 0>{}, std::integral_constant<int, NTM>{});
     } else {
       static_for<0, (NTM + 1) / 2>([&](auto hp) {
@@ -524,10 +698,6 @@ __device__ __forceinline__ void sigma_sector(const IncDev& d, const Lds& L, cons
     // the next column's copy and beta part (colb and r2 are free again)
     if (b + et_waves < n) column_setup(b + et_waves);
     // S[a][b] = sum over the links (a -> J, pair Q) of sign E[(J, b)][Q]
-    uint32_t lk0_col[LP], lk1_col[2];
-    if (!kLinkRegs) link_codes(lk0_col, lk1_col);
-    const uint32_t(&lk0)[LP] = kLinkRegs ? lk0_keep : lk0_col;
-    const uint32_t(&lk1)[2] = kLinkRegs ? lk1_keep : lk1_col;
     {
       T v[2 * LP];
 #pragma unroll
@@ -566,8 +736,8 @@ __device__ inline void load_tables(const IncDev& d, const Lds& L, const int32_t*
   const int npp = npair_pad(d.k);
   int16_t* pt = (int16_t*)L.ptab;
   for (int i = threadIdx.x; i < (n + 1) * npp; i += blockDim.x) {
-    const int a = i / npp, Q = i - a * npp;
-    const int e = (a < n && Q < np) ? tables[d.pair_off + a * np + Q] : -1;
+    const int a = i / npp, q = i - a * npp;  // contraction order (pair_at)
+    const int e = (a < n && q < np) ? tables[d.pair_off + a * np + pair_at(d.k, q)] : -1;
     const int J = e < 0 ? n : (e >> 1), neg = e < 0 ? 0 : (e & 1);
     pt[i] = (int16_t)(J | (neg << 15));
   }
@@ -591,53 +761,41 @@ __device__ inline void load_tables(const IncDev& d, const Lds& L, const int32_t*
   }
 }
 
-// Expand the packed scaled vector tv into the unscaled cp of type T (FP32
-// full with a zero last row and column, FP64 packed with a zero tail) and
-// clear sp.
+// Expand the packed scaled vector tv into the unscaled vector of type T (full,
+// FP32 in cp with a zero last row and column, FP64 in c64 with a zero last
+// row) and clear sp.
 template <typename T>
 __device__ inline void prepare_sigma(const IncDev& d, const Lds& L) {
-  T* cp = (T*)L.cp;
+  T* cp = sizeof(T) == 4 ? (T*)L.cp : (T*)L.c64;
   const int n = d.n_str, ld = n + 1;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  if (sizeof(T) == 4) {
-    for (int a = wave; a < ld; a += nw)
-      for (int b = lane; b < ld; b += 64) {
-        double v = 0.0;
-        if (a < n && b < n) {
-          v = L.tv[pk32(a, b)];
-          if (a != b) v *= kRSqrt2;
-        }
-        cp[a * ld + b] = (T)v;
+  for (int a = wave; a < ld; a += nw)
+    for (int b = lane; b < ld; b += 64) {
+      double v = 0.0;
+      if (a < n && b < n) {
+        v = L.tv[pk32(a, b)];
+        if (a != b) v *= kRSqrt2;
       }
-  } else {
-    for (int b = wave; b < n; b += nw)
-      for (int a = lane; a <= b; a += 64) {
-        const int i = ((b * (b + 1)) >> 1) + a;
-        const double v = L.tv[i];
-        cp[i] = (T)(a == b ? v : v * kRSqrt2);
-      }
-    for (int i = threadIdx.x; i <= n; i += blockDim.x) cp[d.n_sym + i] = (T)0;  // zero tail
-  }
+      cp[a * ld + b] = (T)v;
+    }
   for (int64_t i = threadIdx.x; i < d.n_sym; i += blockDim.x) L.sp[i] = 0.0;
   __syncthreads();
 }
 
-// Entry i = (a, b) of the packed scaled vector, value v, into cp in the
-// layout of T, and the sigma accumulator slot cleared: the per-entry part of
-// prepare_sigma, for callers that produce the vector entry by entry.
+// Entry i = (a, b) of the packed scaled vector, value v, into the layout of
+// T, and the sigma accumulator slot cleared: the per-entry part of
+// prepare_sigma, for callers that produce the vector entry by entry.  FP64
+// also rewrites the zero row (its place is scratch between sigmas).
 template <typename T>
 __device__ __forceinline__ void stage_entry(const IncDev& d, const Lds& L, int i, double v) {
   int a, b;
   unpack32(i, &a, &b);
-  T* cp = (T*)L.cp;
+  T* cp = sizeof(T) == 4 ? (T*)L.cp : (T*)L.c64;
   const T c = (T)(a == b ? v : v * kRSqrt2);
-  if (sizeof(T) == 4) {
-    const int ld = d.n_str + 1;
-    cp[a * ld + b] = c;
-    cp[b * ld + a] = c;
-  } else {
-    cp[i] = c;
-  }
+  const int ld = d.n_str + 1;
+  cp[a * ld + b] = c;
+  cp[b * ld + a] = c;
+  if (sizeof(T) == 8 && a == b) cp[d.n_str * ld + a] = (T)0;
   L.sp[i] = 0.0;
 }
 
@@ -647,17 +805,20 @@ template <typename T, int K>
 __device__ inline void sigma_phase(const IncDev& d, const Lds& L, const double* V, double shift,
                                    int et_waves, bool staged = false, bool build_w = true, bool sync = true) {
   if (!staged) prepare_sigma<T>(d, L);
-  sigma_sector<T, K>(d, L, V, shift, et_waves, build_w);
+  if (build_w) build_weights<T, K>(d, L, V, shift);
+  if constexpr (sizeof(T) == 4)
+    sigma_sector<K>(d, L, et_waves);
+  else
+    sigma_scatter<K>(d, L, V, et_waves);
   if (sync) __syncthreads();
 }
 
+// Waves that contract: all in FP64, as many as hold an E slice in FP32.
 template <typename T, int K>
 __device__ inline int et_waves_for(const IncDev& d, const Lds& L) {
-  const int64_t slice = et_slice_bytes(K, d.n_str, (int)sizeof(T));
-  int w = (int)(wt_offset(L, K, (int)sizeof(T)) / slice);
-  const int wc = (int)(colb_bytes(d.n_str) / (2 * (int64_t)(d.n_str + 1) * (int64_t)sizeof(T)));
-  w = w < wc ? w : wc;
   const int nw = blockDim.x >> 6;
+  if (sizeof(T) == 8) return nw;
+  const int w = (int)(wt_offset(L, K, 4) / et_slice_bytes(K, d.n_str, 4));
   return w > nw ? nw : w;
 }
 
@@ -849,7 +1010,7 @@ __device__ inline int64_t ps_scratch_offset(const IncDev& d) { return a16(transi
 // rotations (2 P floats) and planes (P ints) in 1 KB, h' [K][K] and a copy
 // of the pair matrix V [np][np] and k [K][K] of the increment (FP64) for
 // the Slater-Condon elements.
-__device__ inline int64_t ps_scratch_bytes(int P, int K) {
+__host__ __device__ inline int64_t ps_scratch_bytes(int P, int K) {
   const int64_t np = K * (K + 1) / 2;
   return 8LL * P * P + 1024 + 8LL * (2 * K * K + np * np) + 64;
 }
@@ -1910,16 +2071,23 @@ __global__ void __launch_bounds__(kBatchThreads) sigma_one_kernel(const IncDev* 
   }
 }
 
-// LDS the batched solver needs for an increment: the persistent part plus
-// the larger of the transient part and one FP64 E slice.
-int64_t batched_lds_bytes(int k, int n_str, int n_link) {
-  const int64_t tr = transient_bytes(n_str), sl = et_slice_bytes(k, n_str, 8);
-  return persistent_bytes(k, n_str, n_link) + (tr > sl ? tr : sl) + wt_bytes(k, 8) + 16;
+// LDS the batched solver needs for an increment: the persistent part, then
+// the transient part with the full FP64 vector after it or one FP32 E slice,
+// whichever is larger, and the diagonal-pair weights.
+static int64_t scratch_bytes(int k, int n_str, int slices) {
+  const int64_t v = a16(transient_bytes(n_str)) + c64_bytes(n_str), e = slices * et_slice_bytes(k, n_str, 4);
+  const int64_t w8 = wt_bytes(k, 8), w4 = wt_bytes(k, 4);
+  return (v > e ? v : e) + (w8 > w4 ? w8 : w4) + 16;
 }
-// LDS that gives every wave of the workgroup its FP64 E slice.
+int64_t batched_lds_bytes(int k, int n_str, int n_link) {
+  return persistent_bytes(k, n_str, n_link) + scratch_bytes(k, n_str, 1);
+}
+// LDS that gives every wave of the workgroup its FP32 E slice, or the set-up
+// of a P-space block its scratch.
 int64_t batched_lds_want(int k, int n_str, int n_link) {
-  const int64_t tr = transient_bytes(n_str), sl = (kBatchThreads / 64) * et_slice_bytes(k, n_str, 8);
-  return persistent_bytes(k, n_str, n_link) + (tr > sl ? tr : sl) + wt_bytes(k, 8) + 16;
+  const int64_t ps = a16(transient_bytes(n_str)) + ps_scratch_bytes(kPsMax, k);
+  const int64_t sc = scratch_bytes(k, n_str, kBatchThreads / 64);
+  return persistent_bytes(k, n_str, n_link) + (sc > ps ? sc : ps);
 }
 
 hipError_t launch_batched(const SolveArgs& A, int lds_bytes, hipStream_t st) {

@@ -67,6 +67,19 @@ __device__ __forceinline__ double dpp_f64(double v) {
   return __hiloint2double(hi, lo);
 }
 
+// Sum over the four rows of 16 lanes (lanes equal mod 16), in each of them.
+__device__ __forceinline__ double rows_sum(double v) {
+#pragma clang fp contract(off)
+  {
+    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+    v = __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+  }
+  const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+
 // Sum over the wavefront, the total in every lane.  Inside a row of 16 lanes
 // by DPP (neighbour, pair, half-row and row mirrors), across rows by the
 // gfx950 lane-row swaps: both operands of each add are the same in every
@@ -82,17 +95,7 @@ __device__ __forceinline__ double wave_sum(double v) {
   v += dpp_f64<0x4E>(v);   // quad_perm [2, 3, 0, 1]
   v += dpp_f64<0x141>(v);  // row_half_mirror: the other quad of the half row
   v += dpp_f64<0x140>(v);  // row_mirror: the other half row
-  {
-    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
-    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
-    v = __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
-  }
-  {
-    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
-    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
-    v = __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
-  }
-  return v;
+  return rows_sum(v);
 }
 
 // Sum NV values over the workgroup; every thread gets the totals in out[].
