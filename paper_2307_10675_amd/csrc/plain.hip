@@ -18,7 +18,8 @@ namespace ifci {
 
 __global__ void __launch_bounds__(256) sym_combine_kernel(IncDev d, const double* __restrict__ Sm,
                                                           double* __restrict__ sig) {
-  sym_combine_body(d, Sm, sig, blockIdx.x, gridDim.x);
+  __shared__ double tl[32][33];
+  sym_combine_body(d.n_str, Sm, blockIdx.x, gridDim.x, tl, [&](int64_t i, double v) { sig[i] = v; });
 }
 
 bool sigma_column_supported(const IncDev& d) {
@@ -222,6 +223,8 @@ __global__ void init_state_kernel(DavState* S, const double* part, int nblk, dou
     S->ecore = ecore;
     S->keep = 0;
     S->plarge = 0;
+    S->fresh = 1;
+    S->count = 0;
     S->theta = 0.0;
     S->resid = 1e300;
   }
@@ -237,9 +240,10 @@ __global__ void __launch_bounds__(256) dots_kernel(const double* __restrict__ Vb
   op_dots(Vb, st, m, s, ns, part + blockIdx.x * kNV, blockIdx.x, gridDim.x, red);
 }
 
-__global__ void __launch_bounds__(64) small_G_kernel(DavState* S, const double* part, int nblk, int mmax) {
+__global__ void __launch_bounds__(256) small_G_kernel(DavState* S, const double* part, int nblk, int mmax) {
   __shared__ SmallG sh;
-  small_G(S, part, nblk, mmax, &sh);
+  __shared__ double red[4 * kNV];
+  small_G(S, part, nblk, mmax, &sh, red);
 }
 
 __global__ void __launch_bounds__(256) passA_kernel(const DavState* __restrict__ S, double* Vb, double* Sb,
@@ -251,57 +255,37 @@ __global__ void __launch_bounds__(256) passA_kernel(const DavState* __restrict__
   op_passA(S, Vb, Sb, st, HD, X, T, ns, part + blockIdx.x * kNV, blockIdx.x, gridDim.x, red, y);
 }
 
-__global__ void __launch_bounds__(64) small_A_kernel(DavState* S, const double* part, int nblk, double tol32,
-                                                     double tol64, int max_iter, int evict) {
-  __shared__ double v[kNV];
-  small_A(S, part, nblk, tol32, tol64, max_iter, evict, v);
+__global__ void __launch_bounds__(256) small_A_kernel(DavState* S, const double* part, int nblk, double tol32,
+                                                      double tol64, int max_iter, int evict) {
+  __shared__ double v[kNV], red[4 * kNV];
+  small_A(S, part, nblk, tol32, tol64, max_iter, evict, v, red);
 }
 
-__global__ void __launch_bounds__(256) restart_kernel(const DavState* __restrict__ S, double* Vb, double* Sb,
-                                                      int64_t st, int64_t ns) {
-  __shared__ double q[kMaxSpace * kKeep];
-  op_restart(S, Vb, Sb, st, ns, blockIdx.x, gridDim.x, q);
+__global__ void __launch_bounds__(256) switch_kernel(double* Vb, const double* X, int64_t ns) {
+  op_switch(Vb, X, ns, blockIdx.x, gridDim.x);
 }
 
-__global__ void small_R_kernel(DavState* S) { small_R(S); }
+__global__ void __launch_bounds__(256) small_switch_kernel(DavState* S) { small_switch(S); }
 
-__global__ void __launch_bounds__(256) switch_kernel(DavState* S, double* Vb, const double* X, int64_t ns) {
-  op_switch(S, Vb, X, ns, blockIdx.x, gridDim.x);
-}
-
-__global__ void __launch_bounds__(256) passB_kernel(const DavState* __restrict__ S, const double* __restrict__ Vb,
-                                                    int64_t st, double* __restrict__ T, int64_t ns, double* part) {
+__global__ void __launch_bounds__(256) passB_kernel(const DavState* __restrict__ S, double* Vb, double* Sb, int64_t st,
+                                                    double* __restrict__ T, int64_t ns, double* part) {
   __shared__ double red[4 * kNV];
-  __shared__ double cf[16];
-  op_passB(S, Vb, st, T, ns, part + blockIdx.x * kNV, blockIdx.x, gridDim.x, red, cf);
+  __shared__ double c[16 + kMaxSpace * kKeep];
+  op_passB(S, Vb, Sb, st, T, ns, part + blockIdx.x * kNV, blockIdx.x, gridDim.x, red, c);
 }
 
-__global__ void __launch_bounds__(64) small_B_kernel(DavState* S, const double* part, int nblk) {
-  __shared__ double v[kNV];
-  small_B(S, part, nblk, v);
+__global__ void __launch_bounds__(256) small_B_kernel(DavState* S, const double* part, int nblk) {
+  __shared__ double v[kNV], red[4 * kNV];
+  small_B(S, part, nblk, v, red);
 }
 
-__global__ void __launch_bounds__(256) passC_kernel(const DavState* __restrict__ S, const double* __restrict__ Vb,
-                                                    int64_t st, double* __restrict__ T, int64_t ns, double* part) {
-  __shared__ double red[4 * kNV];
-  __shared__ double c2[16];
-  if (!S->reorth) return;
-  op_passC(S, Vb, st, T, ns, part + blockIdx.x * kNV, blockIdx.x, gridDim.x, red, c2);
-}
-
-__global__ void __launch_bounds__(64) small_C_kernel(DavState* S, const double* part, int nblk) {
-  if (!S->reorth) return;
-  __shared__ double v[kNV];
-  small_C(S, part, nblk, v);
-}
-
-__global__ void __launch_bounds__(256) normalize_kernel(DavState* S, double* Vb, int64_t st,
-                                                        const double* __restrict__ T, int64_t ns) {
-  op_normalize(S, Vb, st, T, ns, blockIdx.x, gridDim.x);
-}
-
-__global__ void set_m_kernel(DavState* S) {
-  if (threadIdx.x == 0) S->m = S->mb + 1;
+__global__ void __launch_bounds__(256) advance_kernel(const DavState* S, double* Vb, int64_t st,
+                                                      const double* __restrict__ T, int64_t ns) {
+  const int m = S->m;
+  const bool reorth = S->reorth != 0;
+  const double inv = S->inv;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < ns; i += (int64_t)gridDim.x * blockDim.x)
+    Vb[(int64_t)m * st + i] = advance_value(Vb, st, T, i, m, reorth, inv, S->c2);
 }
 
 __global__ void finish_kernel(const DavState* S, double e_const, double* e_out, int32_t* status_out,
@@ -356,31 +340,23 @@ hipError_t run_plain(const PlainArgs& A, double* e_out, int32_t* status_out, int
                           phase == 32 ? IFCI_MIXED : IFCI_FP64, 1, shift, st);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(dots_kernel, dim3(nb), dim3(256), 0, st, Vb, sd, m, Sb + m * sd, ns, A.part);
-    hipLaunchKernelGGL(small_G_kernel, dim3(1), dim3(64), 0, st, S, A.part, (int)nb, mmax);
+    hipLaunchKernelGGL(small_G_kernel, dim3(1), dim3(256), 0, st, S, A.part, (int)nb, mmax);
     hipLaunchKernelGGL(passA_kernel, dim3(nb), dim3(256), 0, st, S, Vb, Sb, sd, HD, X, T, ns, A.part);
-    hipLaunchKernelGGL(small_A_kernel, dim3(1), dim3(64), 0, st, S, A.part, (int)nb, A.r_tol_inner, A.r_tol,
+    hipLaunchKernelGGL(small_A_kernel, dim3(1), dim3(256), 0, st, S, A.part, (int)nb, A.r_tol_inner, A.r_tol,
                        A.max_iter, A.evict ? 1 : 0);
     if ((e = hipMemcpyAsync(&hs, S, sizeof(DavState), hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
     if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
-    if (hs.action == 1 || hs.action == 3 || hs.action == 4) break;
-    if (hs.action == 2) {
-      hipLaunchKernelGGL(switch_kernel, dim3(nb), dim3(256), 0, st, S, Vb, X, ns);
+    if (hs.action == kActDone || hs.action == kActMaxIter || hs.action == kActEvicted) break;
+    if (hs.action == kActSwitch) {
+      hipLaunchKernelGGL(switch_kernel, dim3(nb), dim3(256), 0, st, Vb, X, ns);
+      hipLaunchKernelGGL(small_switch_kernel, dim3(1), dim3(256), 0, st, S);
       m = 0;
       phase = 64;
       continue;
     }
-    if (hs.restart) {
-      hipLaunchKernelGGL(restart_kernel, dim3(nb), dim3(256), 0, st, S, Vb, Sb, sd, ns);
-      hipLaunchKernelGGL(small_R_kernel, dim3(1), dim3(64), 0, st, S);
-      if ((e = hipMemcpyAsync(&hs, S, sizeof(DavState), hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
-      if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(passB_kernel, dim3(nb), dim3(256), 0, st, S, Vb, sd, T, ns, A.part);
-    hipLaunchKernelGGL(small_B_kernel, dim3(1), dim3(64), 0, st, S, A.part, (int)nb);
-    hipLaunchKernelGGL(passC_kernel, dim3(nb), dim3(256), 0, st, S, Vb, sd, T, ns, A.part);
-    hipLaunchKernelGGL(small_C_kernel, dim3(1), dim3(64), 0, st, S, A.part, (int)nb);
-    hipLaunchKernelGGL(normalize_kernel, dim3(nb), dim3(256), 0, st, S, Vb, sd, T, ns);
-    hipLaunchKernelGGL(set_m_kernel, dim3(1), dim3(64), 0, st, S);
+    hipLaunchKernelGGL(passB_kernel, dim3(nb), dim3(256), 0, st, S, Vb, Sb, sd, T, ns, A.part);
+    hipLaunchKernelGGL(small_B_kernel, dim3(1), dim3(256), 0, st, S, A.part, (int)nb);
+    hipLaunchKernelGGL(advance_kernel, dim3(nb), dim3(256), 0, st, S, Vb, sd, T, ns);
     m = hs.mb + 1;
   }
   hipLaunchKernelGGL(finish_kernel, dim3(1), dim3(64), 0, st, S, A.e_const, e_out, status_out, iters_out,

@@ -134,11 +134,10 @@ __global__ void __launch_bounds__(kWideThreads) gather_full_kernel(IncDev d, con
   sig[j] = (double)s;
 }
 
-// Symmetric gather into a packed scaled vector: sigma = S + S^T.
+// Symmetric gather: entry i of the packed scaled sigma = S + S^T.
 template <typename T>
-__device__ __forceinline__ void gather_sym_body(const IncDev& d, const int32_t* __restrict__ links,
-                                                const T* __restrict__ E, double* __restrict__ sig, int64_t i) {
-  if (i >= d.n_sym) return;
+__device__ __forceinline__ double gather_sym_value(const IncDev& d, const int32_t* __restrict__ links,
+                                                   const T* __restrict__ E, int64_t i) {
   int a, b;
   unpack(i, &a, &b);
   const int n = d.n_str, nl = d.n_link;
@@ -150,24 +149,22 @@ __device__ __forceinline__ void gather_sym_body(const IncDev& d, const int32_t* 
     const T v = E[(int64_t)Q * nd + (int64_t)b * n + J];
     s1 += (code & 1) ? -v : v;
   }
-  if (a == b) {
-    sig[i] = 2.0 * (double)s1;
-    return;
-  }
+  if (a == b) return 2.0 * (double)s1;
   for (int l = 0; l < nl; ++l) {
     const int code = links[b * nl + l];
     const int Q = code >> 17, J = (code >> 1) & 0xFFFF;
     const T v = E[(int64_t)Q * nd + (int64_t)a * n + J];
     s2 += (code & 1) ? -v : v;
   }
-  sig[i] = kSqrt2 * ((double)s1 + (double)s2);
+  return kSqrt2 * ((double)s1 + (double)s2);
 }
 
 template <typename T>
 __global__ void __launch_bounds__(kWideThreads) gather_sym_kernel(IncDev d, const int32_t* __restrict__ links,
                                                                   const T* __restrict__ E,
                                                                   double* __restrict__ sig) {
-  gather_sym_body<T>(d, links, E, sig, (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < d.n_sym) sig[i] = gather_sym_value<T>(d, links, E, i);
 }
 
 // ------------------------------------------------- fused column sigma (k 10..14)
@@ -209,51 +206,51 @@ struct ColShape {
   static constexpr int64_t lds = vf_bytes + ((col_bytes + 15) / 16) * 16 + s_bytes + brow_bytes;
 };
 
-// Packed scaled symmetric c -> full unscaled C [(n + 1) x n] of T (row n and
-// a tail of 16 entries zero), in 32 x 32 tiles, grid-strided over the tiles
-// blk, blk + nblk, ...  (256 threads).  Entry (r, cc) is c[tri(cc) + r] above
-// the diagonal and c[tri(r) + cc] on and below it; tiles wholly above the
-// diagonal are read along r into LDS and written along cc, so both the reads
-// of c and the writes of C are coalesced.
-template <typename T>
-__device__ __forceinline__ void expand_sym_body(int n, const double* __restrict__ c, T* __restrict__ cf, int blk,
-                                                int nblk) {
-  __shared__ double tl[32][33];
-  const int tc = (n + 31) / 32;
-  const int64_t nt = (int64_t)((n + 32) / 32) * tc;  // (n + 1) rows
+// Tiles of 32 x 32 entries of the upper triangle (ta <= tb).
+__device__ __forceinline__ int64_t sym_tiles(int n) {
+  const int64_t t = (n + 31) / 32;
+  return t * (t + 1) / 2;
+}
+
+// Packed scaled symmetric vector -> full unscaled C [(n + 1) x n] of T (row n
+// and a tail of 16 entries zero), over the tiles blk, blk + nblk, ... of the
+// upper triangle (256 threads).  value(i) is packed entry i, asked for once
+// per entry, in runs of 32; a tile is written along its rows and, through
+// LDS, along its columns, so the writes are coalesced too.
+template <typename T, typename F>
+__device__ __forceinline__ void expand_sym_body(int n, T* __restrict__ cf, int blk, int nblk, F&& value) {
+  __shared__ T tl[32][33];
+  const int64_t nt = sym_tiles(n);
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  if (blk == 0 && threadIdx.x < 16) cf[(int64_t)(n + 1) * n + threadIdx.x] = (T)0;
+  if (blk == 0)
+    for (int j = threadIdx.x; j < n + 16; j += blockDim.x) cf[(int64_t)n * n + j] = (T)0;
   for (int64_t t = blk; t < nt; t += nblk) {
-    const int r0 = (int)(t / tc) * 32, c0 = (int)(t % tc) * 32;
-    if (r0 + 32 <= c0) {
-      for (int k = ty; k < 32; k += 8) {
-        const int cc = c0 + k;
-        tl[k][tx] = cc < n ? c[tri(cc) + r0 + tx] : 0.0;
-      }
-      __syncthreads();
-      for (int k = ty; k < 32; k += 8) {
-        const int cc = c0 + tx;
-        if (cc < n) cf[(int64_t)(r0 + k) * n + cc] = (T)(tl[tx][k] * kRSqrt2);
-      }
-      __syncthreads();
-    } else {
-      for (int k = ty; k < 32; k += 8) {
-        const int r = r0 + k, cc = c0 + tx;
-        if (r > n || cc >= n) continue;
-        double v = 0.0;
-        if (r < n) {
-          v = c[packed(r, cc)];
-          if (r != cc) v *= kRSqrt2;
-        }
-        cf[(int64_t)r * n + cc] = (T)v;
+    int ta, tb;
+    unpack(t, &ta, &tb);
+    const int a0 = 32 * ta, b0 = 32 * tb;
+#pragma unroll
+    for (int k = 0; k < 32; k += 8) {
+      const int a = a0 + tx, b = b0 + ty + k;
+      if (a <= b && b < n) {
+        const double v = value(tri(b) + a);
+        const T c = (T)(a == b ? v : v * kRSqrt2);
+        cf[(int64_t)b * n + a] = c;
+        tl[ty + k][tx] = c;
       }
     }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 32; k += 8) {
+      const int a = a0 + ty + k, b = b0 + tx;
+      if (a < b && b < n) cf[(int64_t)a * n + b] = tl[tx][ty + k];
+    }
+    __syncthreads();
   }
 }
 
 template <typename T>
 __global__ void __launch_bounds__(256) expand_sym_kernel(IncDev d, const double* __restrict__ c, T* __restrict__ cf) {
-  expand_sym_body<T>(d.n_str, c, cf, blockIdx.x, gridDim.x);
+  expand_sym_body<T>(d.n_str, cf, blockIdx.x, gridDim.x, [&](int64_t i) { return c[i]; });
 }
 
 // A fragments of V for the column kernel, in its LDS image, with the
@@ -594,40 +591,35 @@ __global__ void __launch_bounds__(split_threads<T>()) sigma_column_split_kernel(
   column_split_body<T, K>(ptab, ptabT, cf, vfg, Sm, blockIdx.x, lds);
 }
 
-// sigma (packed scaled) = S + S^T from Sm[b][a] = S[a][b], in 32 x 32 tiles
-// (ta <= tb) of the upper triangle, grid-strided over the tiles blk, blk +
-// nblk, ...  (256 threads).  Sm[a][b] is read along b into LDS; Sm[b][a] and
-// sigma[tri(b) + a] along a.
-__device__ __forceinline__ int64_t sym_combine_tiles(int n) {
-  const int64_t t = (n + 31) / 32;
-  return t * (t + 1) / 2;
-}
-__device__ __forceinline__ void sym_combine_body(const IncDev& d, const double* __restrict__ Sm,
-                                                 double* __restrict__ sig, int64_t blk, int64_t nblk) {
-  __shared__ double tl[32][33];
-  const int n = d.n_str;
-  const int64_t nt = sym_combine_tiles(n);
+// sigma (packed scaled) = S + S^T from Sm[b][a] = S[a][b], over the tiles blk,
+// blk + nblk, ... of the upper triangle (256 threads): Sm[a][b] is read along
+// b into LDS (tl), Sm[b][a] along a, and out(i, value) takes packed entry i.
+template <typename F>
+__device__ __forceinline__ void sym_combine_body(int n, const double* __restrict__ Sm, int64_t blk, int64_t nblk,
+                                                 double (*tl)[33], F&& out) {
+  const int64_t nt = sym_tiles(n);
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
   for (int64_t t = blk; t < nt; t += nblk) {
     int ta, tb;
     unpack(t, &ta, &tb);
     const int a0 = 32 * ta, b0 = 32 * tb;
-    for (int k = ty; k < 32; k += 8) {
-      const int a = a0 + k, b = b0 + tx;
-      tl[k][tx] = (a < n && b < n) ? Sm[(int64_t)a * n + b] : 0.0;
+#pragma unroll
+    for (int k = 0; k < 32; k += 8) {
+      const int a = a0 + ty + k, b = b0 + tx;
+      tl[ty + k][tx] = (a < n && b < n) ? Sm[(int64_t)a * n + b] : 0.0;
     }
     __syncthreads();
-    for (int k = ty; k < 32; k += 8) {
-      const int a = a0 + tx, b = b0 + k;
+#pragma unroll 2
+    for (int k = 0; k < 32; k += 8) {
+      const int a = a0 + tx, b = b0 + ty + k;
       if (a <= b && b < n) {
         const double y = Sm[(int64_t)b * n + a];
-        sig[tri(b) + a] = a == b ? 2.0 * y : kSqrt2 * (y + tl[tx][k]);
+        out(tri(b) + a, a == b ? 2.0 * y : kSqrt2 * (y + tl[tx][ty + k]));
       }
     }
     __syncthreads();
   }
 }
-
 
 // ---------------------------------------------------------------- H diagonal
 // F(a) = sum_{p in a} h'_pp + 1/2 sum_{p, q in a} (J_pq - K_pq): the energy of

@@ -36,8 +36,12 @@ constexpr int kVecGrid = 1024;    // persistent grid of the vector steps
 constexpr int kSmallGrid = 512;   // persistent grid of the one-wave steps
 constexpr int kCompactThreads = 1024;
 
+// Blocks of a vector pass over one increment: four entries a thread, so that
+// the end of a block (partial sums to memory, then the count of finished
+// blocks: two round trips) is paid a quarter as often; by the length alone,
+// so that an increment's sums do not depend on its batch.
 __host__ __device__ inline int vec_blocks(int64_t ns) {
-  const int64_t b = (ns + kVecThreads - 1) / kVecThreads;
+  const int64_t b = (ns + 4 * kVecThreads - 1) / (4 * kVecThreads);
   return (int)(b < 1 ? 1 : (b > kPartBlocks ? kPartBlocks : b));
 }
 
@@ -113,6 +117,8 @@ __global__ void __launch_bounds__(64) wb_init_kernel(WideItem* const* it, int n,
       S->ecore = w->B[int_block(w->d.k).misc];
       S->keep = 0;
       S->plarge = 0;
+      S->fresh = 1;
+      S->count = 0;
       S->theta = 0.0;
       S->resid = 1e300;
       S->alive = 1;
@@ -189,20 +195,47 @@ __global__ void __launch_bounds__(kCompactThreads) wb_compact_kernel(WideItem* c
 }
 
 // ------------------------------------------------------------------ sigma
+// The new basis vector V[m] where the last iteration left its correction
+// (advance_value), and full C of it in the contraction precision.
 template <typename T>
 __global__ void __launch_bounds__(kVecThreads) wb_expand_kernel(WideItem* const* it, const int* ctl, int cap,
                                                                 int which) {
   const int nl = live_count(ctl, which);
   const int* lst = live_list(ctl, cap, which);
-  const int per = kVecGrid;  // blocks per increment, grid-strided inside over 32 x 32 tiles
-  const int n = it[0]->d.n_str;
-  const int64_t nb = (int64_t)((n + 32) / 32) * ((n + 31) / 32);
-  const int units = nb < per ? (int)nb : per;
+  const int64_t nb = sym_tiles(it[0]->d.n_str);
+  const int units = nb < kVecGrid ? (int)nb : kVecGrid;
   for (int u = blockIdx.x; u < nl * units; u += gridDim.x) {
     const WideItem* w = it[lst[u / units]];
     const DavState* S = st(w);
-    expand_sym_body<T>(w->d.n_str, w->Vb + (int64_t)S->m * w->d.stride, (T*)(w->sc + col_scratch(w->d).cf),
-                       u % units, units);
+    const int m = S->m;
+    const bool fresh = S->fresh != 0, reorth = S->reorth != 0;
+    const double inv = S->inv;
+    const int64_t sd = w->d.stride;
+    double* const Vb = w->Vb;
+    expand_sym_body<T>(w->d.n_str, (T*)(w->sc + col_scratch(w->d).cf), u % units, units, [&](int64_t i) {
+      if (fresh) return Vb[(int64_t)m * sd + i];
+      const double v = advance_value(Vb, sd, w->T, i, m, reorth, inv, S->c2);
+      Vb[(int64_t)m * sd + i] = v;
+      return v;
+    });
+  }
+}
+
+// The new basis vector alone (general product, which reads it packed).
+__global__ void __launch_bounds__(kVecThreads) wb_advance_kernel(WideItem* const* it, const int* ctl, int cap) {
+  const int nl = live_count(ctl, 0);
+  const int* lst = live_list(ctl, cap, 0);
+  const int nb = vec_blocks(it[0]->d.n_sym);
+  for (int u = blockIdx.x; u < nl * nb; u += gridDim.x) {
+    const WideItem* w = it[lst[u / nb]];
+    const DavState* S = st(w);
+    if (S->fresh) continue;
+    const int m = S->m;
+    const bool reorth = S->reorth != 0;
+    const double inv = S->inv;
+    const int64_t sd = w->d.stride, ns = w->d.n_sym;
+    for (int64_t i = (int64_t)(u % nb) * kVecThreads + threadIdx.x; i < ns; i += (int64_t)nb * kVecThreads)
+      w->Vb[(int64_t)m * sd + i] = advance_value(w->Vb, sd, w->T, i, m, reorth, inv, S->c2);
   }
 }
 
@@ -259,14 +292,16 @@ __global__ void __launch_bounds__(split_threads<T>()) wb_column_split_kernel(Wid
 }
 
 __global__ void __launch_bounds__(kVecThreads) wb_combine_kernel(WideItem* const* it, const int* ctl, int cap) {
+  __shared__ double tl[32][33];
   const int nl = live_count(ctl, 0);
   const int* lst = live_list(ctl, cap, 0);
-  const int64_t nt = sym_combine_tiles(it[0]->d.n_str);
+  const int64_t nt = sym_tiles(it[0]->d.n_str);
   const int per = nt < kVecGrid ? (int)nt : kVecGrid;  // blocks per increment, grid-strided inside
   for (int64_t u = blockIdx.x; u < (int64_t)nl * per; u += gridDim.x) {
     const WideItem* w = it[lst[u / per]];
-    const DavState* S = st(w);
-    sym_combine_body(w->d, w->sc + col_scratch(w->d).sm, w->Sb + (int64_t)S->m * w->d.stride, u % per, per);
+    double* const sg = w->Sb + (int64_t)st(w)->m * w->d.stride;
+    sym_combine_body(w->d.n_str, w->sc + col_scratch(w->d).sm, u % per, per, tl,
+                     [&](int64_t i, double v) { sg[i] = v; });
   }
 }
 
@@ -293,28 +328,22 @@ __global__ void __launch_bounds__(kWideThreads) wb_gather_kernel(WideItem* const
   const int64_t per = (it[0]->d.n_sym + kWideThreads - 1) / kWideThreads;
   for (int64_t u = blockIdx.x; u < (int64_t)nl * per; u += gridDim.x) {
     const WideItem* w = it[lst[u / per]];
-    const DavState* S = st(w);
-    gather_sym_body<T>(w->d, w->tabs + w->d.link_off, (const T*)w->sc, w->Sb + (int64_t)S->m * w->d.stride,
-                       (u % per) * kWideThreads + threadIdx.x);
+    const int64_t i = (u % per) * kWideThreads + threadIdx.x;
+    if (i < w->d.n_sym)
+      w->Sb[(int64_t)st(w)->m * w->d.stride + i] =
+          gather_sym_value<T>(w->d, w->tabs + w->d.link_off, (const T*)w->sc, i);
   }
 }
 
-// ------------------------------------------------------------------ vector and small steps
-// Each takes the live increments, optionally only those whose state passes
-// `want` (evaluated once per unit from the state, the same for every thread).
-enum Want { kAll = 0, kCont, kContRestart, kContReorth, kSwitching };
-
-__device__ __forceinline__ bool wanted(const DavState* S, int want) {
-  switch (want) {
-    case kCont: return S->action == kActContinue;
-    case kContRestart: return S->action == kActContinue && S->restart;
-    case kContReorth: return S->action == kActContinue && S->reorth;
-    case kSwitching: return S->action == kActSwitch;
-    default: return true;
-  }
-}
-
-#define WB_VEC_LOOP(want)                                                  \
+// ------------------------------------------------------------------ vector steps
+// Each takes the live increments; the last block of an increment's pass goes
+// on to the small step that follows it, so an iteration is four launches
+// beside sigma's own (a launch costs 4 to 5 us, which with one launch per
+// small step was most of an iteration of a small batch).  The overlaps of
+// sigma stay a pass of their own: formed where sigma is written (32 x 32 tiles,
+// a few blocks per increment) they had too few loads in flight: 64 x 10o10e
+// 80 us a launch against 12 + 31 us.
+#define WB_VEC_LOOP                                                        \
   const int nl = live_count(ctl, 0);                                       \
   const int* lst = live_list(ctl, cap, 0);                                 \
   const int nb = vec_blocks(it[0]->d.n_sym);                               \
@@ -322,112 +351,43 @@ __device__ __forceinline__ bool wanted(const DavState* S, int want) {
     WideItem* w = it[lst[u / nb]];                                         \
     DavState* S = st(w);                                                   \
     const int blk = u % nb;                                                \
-    if (!wanted(S, want)) continue;                                        \
-    const int64_t sd = w->d.stride, ns = w->d.n_sym;                       \
-    (void)sd;                                                              \
-    (void)ns;
-
-#define WB_SMALL_LOOP(want)                                                \
-  const int nl = live_count(ctl, 0);                                       \
-  const int* lst = live_list(ctl, cap, 0);                                 \
-  const int nb = vec_blocks(it[0]->d.n_sym);                               \
-  (void)nb;                                                                \
-  for (int u = blockIdx.x; u < nl; u += gridDim.x) {                       \
-    WideItem* w = it[lst[u]];                                              \
-    DavState* S = st(w);                                                   \
-    if (!wanted(S, want)) continue;
+    const int64_t sd = w->d.stride, ns = w->d.n_sym;
 
 __global__ void __launch_bounds__(kVecThreads) wb_dots_kernel(WideItem* const* it, const int* ctl, int cap) {
   __shared__ double red[4 * kNV];
-  WB_VEC_LOOP(kAll)
-  const int m = S->m;
-  op_dots(w->Vb, sd, m, w->Sb + (int64_t)m * sd, ns, w->part + blk * kNV, blk, nb, red);
+  __shared__ SmallG g;
+  WB_VEC_LOOP
+    const int m = S->m;
+    op_dots(w->Vb, sd, m, w->Sb + (int64_t)m * sd, ns, w->part + blk * kNV, blk, nb, red);
+    if (last_block(&S->count, nb)) small_G(S, w->part, nb, w->mmax, &g, red);
+    __syncthreads();
   }
 }
 
-__global__ void __launch_bounds__(64) wb_small_G_kernel(WideItem* const* it, const int* ctl, int cap) {
-  __shared__ SmallG sh;
-  WB_SMALL_LOOP(kAll)
-  small_G(S, w->part, nb, w->mmax, &sh);
-  __syncthreads();
+__global__ void __launch_bounds__(kVecThreads) wb_passA_kernel(WideItem* const* it, const int* ctl, int cap,
+                                                               double tol32, double tol64, int max_iter) {
+  __shared__ double red[4 * kNV], v[kNV], y[16];
+  WB_VEC_LOOP
+    op_passA(S, w->Vb, w->Sb, sd, w->HD, w->X, w->T, ns, w->part + blk * kNV, blk, nb, red, y);
+    if (last_block(&S->count, nb))
+      small_A(S, w->part, nb, tol32, tol64, max_iter, w->evict ? (int)(*w->evict != 0) : 0, v, red);
+    __syncthreads();
   }
 }
 
-__global__ void __launch_bounds__(kVecThreads) wb_passA_kernel(WideItem* const* it, const int* ctl, int cap) {
-  __shared__ double red[4 * kNV];
-  __shared__ double y[16];
-  WB_VEC_LOOP(kAll)
-  op_passA(S, w->Vb, w->Sb, sd, w->HD, w->X, w->T, ns, w->part + blk * kNV, blk, nb, red, y);
-  }
-}
-
-__global__ void __launch_bounds__(64) wb_small_A_kernel(WideItem* const* it, const int* ctl, int cap, double tol32,
-                                                        double tol64, int max_iter) {
-  __shared__ double v[kNV];
-  WB_SMALL_LOOP(kAll)
-  small_A(S, w->part, nb, tol32, tol64, max_iter, w->evict ? (int)(*w->evict != 0) : 0, v);
-  __syncthreads();
-  }
-}
-
-__global__ void __launch_bounds__(kVecThreads) wb_switch_kernel(WideItem* const* it, const int* ctl, int cap) {
-  WB_VEC_LOOP(kSwitching)
-  op_switch(S, w->Vb, w->X, ns, blk, nb);
-  }
-}
-
-__global__ void __launch_bounds__(kVecThreads) wb_restart_kernel(WideItem* const* it, const int* ctl, int cap) {
-  __shared__ double q[kMaxSpace * kKeep];
-  WB_VEC_LOOP(kContRestart)
-  op_restart(S, w->Vb, w->Sb, sd, ns, blk, nb, q);
-  }
-}
-
-__global__ void __launch_bounds__(64) wb_small_R_kernel(WideItem* const* it, const int* ctl, int cap) {
-  WB_SMALL_LOOP(kContRestart)
-  small_R(S);
-  __syncthreads();
-  }
-}
-
-__global__ void __launch_bounds__(kVecThreads) wb_passB_kernel(WideItem* const* it, const int* ctl, int cap) {
-  __shared__ double red[4 * kNV];
-  __shared__ double cf[16];
-  WB_VEC_LOOP(kCont)
-  op_passB(S, w->Vb, sd, w->T, ns, w->part + blk * kNV, blk, nb, red, cf);
-  }
-}
-
-__global__ void __launch_bounds__(64) wb_small_B_kernel(WideItem* const* it, const int* ctl, int cap) {
-  __shared__ double v[kNV];
-  WB_SMALL_LOOP(kCont)
-  small_B(S, w->part, nb, v);
-  __syncthreads();
-  }
-}
-
-__global__ void __launch_bounds__(kVecThreads) wb_passC_kernel(WideItem* const* it, const int* ctl, int cap) {
-  __shared__ double red[4 * kNV];
-  __shared__ double c2[16];
-  WB_VEC_LOOP(kContReorth)
-  op_passC(S, w->Vb, sd, w->T, ns, w->part + blk * kNV, blk, nb, red, c2);
-  }
-}
-
-__global__ void __launch_bounds__(64) wb_small_C_kernel(WideItem* const* it, const int* ctl, int cap) {
-  __shared__ double v[kNV];
-  WB_SMALL_LOOP(kContReorth)
-  small_C(S, w->part, nb, v);
-  __syncthreads();
-  }
-}
-
-// V[mb + 1] <- t / ||t||; the first block also advances m (normalize reads
-// only mb, so no block of the same launch reads m)
-__global__ void __launch_bounds__(kVecThreads) wb_normalize_kernel(WideItem* const* it, const int* ctl, int cap) {
-  WB_VEC_LOOP(kCont)
-  op_normalize(S, w->Vb, sd, w->T, ns, blk, nb);
-  if (blk == 0 && threadIdx.x == 0) S->m = S->mb + 1;
+// First orthogonalisation, thick restart included; or, for an increment that
+// moves to its FP64 stage, the start of that stage.
+__global__ void __launch_bounds__(kVecThreads, 2) wb_passB_kernel(WideItem* const* it, const int* ctl, int cap) {
+  __shared__ double red[4 * kNV], v[kNV], c[16 + kMaxSpace * kKeep];
+  WB_VEC_LOOP
+    if (S->action == kActSwitch) {
+      op_switch(w->Vb, w->X, ns, blk, nb);
+      if (last_block(&S->count, nb)) small_switch(S);
+    } else if (S->action == kActContinue) {
+      op_passB(S, w->Vb, w->Sb, sd, w->T, ns, w->part + blk * kNV, blk, nb, red, c);
+      if (last_block(&S->count, nb)) small_B(S, w->part, nb, v, red);
+    }
+    __syncthreads();
   }
 }
 
@@ -554,6 +514,7 @@ hipError_t wide_iteration(const WideRun& R, hipStream_t s) {
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(wb_combine_kernel, dim3(kVecGrid), dim3(kVecThreads), 0, s, R.items, R.ctl, n);
   } else {
+    hipLaunchKernelGGL(wb_advance_kernel, dim3(kVecGrid), dim3(kVecThreads), 0, s, R.items, R.ctl, n);
     if (R.precision == IFCI_MIXED) {
       hipLaunchKernelGGL((wb_contract_kernel<float>), dim3(kVecGrid), dim3(kWideThreads), 0, s, R.items, R.ctl, n, 1);
       hipLaunchKernelGGL((wb_gather_kernel<float>), dim3(kVecGrid), dim3(kWideThreads), 0, s, R.items, R.ctl, n, 1);
@@ -561,19 +522,10 @@ hipError_t wide_iteration(const WideRun& R, hipStream_t s) {
     hipLaunchKernelGGL((wb_contract_kernel<double>), dim3(kVecGrid), dim3(kWideThreads), 0, s, R.items, R.ctl, n, 2);
     hipLaunchKernelGGL((wb_gather_kernel<double>), dim3(kVecGrid), dim3(kWideThreads), 0, s, R.items, R.ctl, n, 2);
   }
-  const dim3 gv(kVecGrid), bv(kVecThreads), gs(grid_for(n, kSmallGrid)), bs(64);
-  hipLaunchKernelGGL(wb_dots_kernel, gv, bv, 0, s, R.items, R.ctl, n);
-  hipLaunchKernelGGL(wb_small_G_kernel, gs, bs, 0, s, R.items, R.ctl, n);
-  hipLaunchKernelGGL(wb_passA_kernel, gv, bv, 0, s, R.items, R.ctl, n);
-  hipLaunchKernelGGL(wb_small_A_kernel, gs, bs, 0, s, R.items, R.ctl, n, R.r_tol_inner, R.r_tol, R.max_iter);
-  if (R.precision == IFCI_MIXED) hipLaunchKernelGGL(wb_switch_kernel, gv, bv, 0, s, R.items, R.ctl, n);
-  hipLaunchKernelGGL(wb_restart_kernel, gv, bv, 0, s, R.items, R.ctl, n);
-  hipLaunchKernelGGL(wb_small_R_kernel, gs, bs, 0, s, R.items, R.ctl, n);
-  hipLaunchKernelGGL(wb_passB_kernel, gv, bv, 0, s, R.items, R.ctl, n);
-  hipLaunchKernelGGL(wb_small_B_kernel, gs, bs, 0, s, R.items, R.ctl, n);
-  hipLaunchKernelGGL(wb_passC_kernel, gv, bv, 0, s, R.items, R.ctl, n);
-  hipLaunchKernelGGL(wb_small_C_kernel, gs, bs, 0, s, R.items, R.ctl, n);
-  hipLaunchKernelGGL(wb_normalize_kernel, gv, bv, 0, s, R.items, R.ctl, n);
+  hipLaunchKernelGGL(wb_dots_kernel, dim3(kVecGrid), dim3(kVecThreads), 0, s, R.items, R.ctl, n);
+  hipLaunchKernelGGL(wb_passA_kernel, dim3(kVecGrid), dim3(kVecThreads), 0, s, R.items, R.ctl, n, R.r_tol_inner,
+                     R.r_tol, R.max_iter);
+  hipLaunchKernelGGL(wb_passB_kernel, dim3(kVecGrid), dim3(kVecThreads), 0, s, R.items, R.ctl, n);
   hipLaunchKernelGGL(wb_compact_kernel, dim3(1), dim3(kCompactThreads), 0, s, R.items, n, R.ctl, n);
   return hipGetLastError();
 }
