@@ -45,7 +45,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK = {"fp64_mfma": 78.6e12, "fp32_mfma": 157.3e12, "hbm": 8.0e12}
-KERNEL_SOURCES = ["batched.hip", "pspace.hpp", "device_common.hpp", "ifci_internal.h", "launch.hpp"]
+KERNEL_SOURCES = ["batched.hip", "batched_solver.hpp", "pspace.hpp", "device_common.hpp", "ifci_internal.h", "launch.hpp"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "batched_lobpcg_kernel_workload2.traffic.json")
 ORACLE_W2 = os.path.join(ROOT, "tests", "golden", "oracle_w2.json")
 ALL_LEGS = ("mixed", "fp64", "plain", "large", "w3", "w4", "cnb", "sno", "hbci", "cpu")

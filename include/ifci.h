@@ -253,16 +253,16 @@ ifci_status ifci_davidson(ifci_plan_t plan, int64_t first, int64_t count, double
 
 /* Lowest even-spin roots of every increment of n_plans plans (for instance
  * independent FCI problems, each a one-increment plan) in one batched solve:
- * each plan's increments that fit on chip run in one launch of the batched
- * solver, and the others of all plans join the same batched device-wide
- * solve (one per active-space shape).  plans: host [n_plans], distinct, on
+ * the increments of all plans that fit on chip run in one launch of the
+ * batched solver, and the others of all plans join the same batched
+ * device-wide solve (one per active-space shape).  plans: host [n_plans], distinct, on
  * one device, each with workspace and integrals set, all created with the
  * batched solver and identical options.  e_out[j], status_out[j] (and,
  * where given, iters_out[j], resid_out[j]): device arrays of plan j's
  * increment count, as in ifci_davidson; iters_out and resid_out may be NULL.
  * Stream order and return as in ifci_davidson; converged vectors stay in
- * each plan's workspace.  The first plan keeps the solve's control block
- * (device memory it allocates on first use and grows as needed).
+ * each plan's workspace.  The first plan keeps the solve's control block and
+ * work list (device memory it allocates on first use and grows as needed).
  * IFCI_ERR_UNSUPPORTED for a plan with a screening mask (ifci_screen). */
 ifci_status ifci_davidson_group(const ifci_plan_t* plans, int32_t n_plans, double* const* e_out,
                                 int32_t* const* status_out, int32_t* const* iters_out,

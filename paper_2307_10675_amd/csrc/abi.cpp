@@ -100,6 +100,8 @@ void free_device(ifci_plan_s* P) {
   free_one(P->d_keep);
   free_one(P->group_ctl);
   P->group_ctl_bytes = 0;
+  free_one(P->group_jobs);
+  P->group_jobs_bytes = 0;
   release_in_flight(P, true);
   if (P->capture_stream) (void)hipStreamDestroy(P->capture_stream);
   P->capture_stream = nullptr;
@@ -218,6 +220,19 @@ CtlBlock ctl_block(char* base, int n) {
   return c;
 }
 
+// Device buffer `buf` of at least `need` bytes: where it has to grow, its
+// earlier work on `st` is done first.
+ifci_status grow(char** buf, int64_t* bytes, int64_t need, hipStream_t st, const char* where) {
+  if (need <= *bytes) return IFCI_OK;
+  HIP_TRY(hipStreamSynchronize(st), where);
+  if (*buf) (void)hipFree(*buf);
+  *buf = nullptr;
+  *bytes = 0;
+  HIP_TRY(hipMalloc((void**)buf, need), where);
+  *bytes = need;
+  return IFCI_OK;
+}
+
 // The increments of one plan that a batched device-wide solve takes, with
 // where their outputs go.
 struct WideMember {
@@ -323,16 +338,9 @@ ifci_status run_wide(ifci_plan_s* owner, std::vector<WideMember>& members, hipSt
         ifci_plan_s* P = members[0].P;
         cbase = P->ws + P->off_wide_ctl + ((int64_t)P->wide_cap * sizeof(WideItem) + 255) / 256 * 256;
       } else {
-        const int64_t need = ctl_block_bytes(n);
-        if (need > O->group_ctl_bytes) {
-          // grow the owner's control block (its earlier work is done first)
-          HIP_TRY(hipStreamSynchronize(st), "ifci_davidson_group");
-          if (O->group_ctl) (void)hipFree(O->group_ctl);
-          O->group_ctl = nullptr;
-          O->group_ctl_bytes = 0;
-          HIP_TRY(hipMalloc((void**)&O->group_ctl, need), "ifci_davidson_group control block");
-          O->group_ctl_bytes = need;
-        }
+        const ifci_status gs =
+            grow(&O->group_ctl, &O->group_ctl_bytes, ctl_block_bytes(n), st, "ifci_davidson_group control block");
+        if (gs != IFCI_OK) return gs;
         cbase = O->group_ctl;
       }
       const CtlBlock cb = ctl_block(cbase, n);
@@ -392,25 +400,13 @@ ifci_status run_wide(ifci_plan_s* owner, std::vector<WideMember>& members, hipSt
   return IFCI_OK;
 }
 
-// One launch of the on-chip batched solver over the increments `ids`
-// (heaviest first) of plan p.
-ifci_status launch_on_chip(ifci_plan_s* p, const std::vector<int32_t>& ids, int64_t first, double* e_out,
-                           int32_t* status_out, const uint8_t* evict_mask, int32_t* iters_out, double* resid_out,
-                           hipStream_t st) {
-  if (ids.empty()) return IFCI_OK;
-  if (ids != p->order_batch) {
-    // a new work list: wait for any earlier upload from order_batch
-    // before reusing its host memory (a repeated list is already there)
-    HIP_TRY(hipStreamSynchronize(st), "ifci_davidson");
-    p->order_batch = ids;
-    HIP_TRY(hipMemcpyAsync(p->d_order, p->order_batch.data(), ids.size() * sizeof(int32_t), hipMemcpyHostToDevice,
-                           st),
-            "ifci_davidson upload");
-  }
+// Arguments of the on-chip solver for plan p's increments [first, ...).
+SolveArgs solve_args(const ifci_plan_s* p, int64_t first, double* e_out, int32_t* status_out,
+                     const uint8_t* evict_mask, int32_t* iters_out, double* resid_out) {
   SolveArgs A;
   A.inc = p->d_inc;
   A.order = p->d_order;
-  A.count = (int32_t)ids.size();
+  A.count = 0;
   A.precision = p->opt.precision;
   A.max_iter = p->opt.max_iter;
   A.max_space = p->opt.max_space;
@@ -429,7 +425,70 @@ ifci_status launch_on_chip(ifci_plan_s* p, const std::vector<int32_t>& ids, int6
   A.e_const = p->e_const;
   A.phase = p->phase_counters;
   A.tune = p->tune;
+  return A;
+}
+
+// One launch of the on-chip batched solver over the increments `ids`
+// (heaviest first) of plan p.
+ifci_status launch_on_chip(ifci_plan_s* p, const std::vector<int32_t>& ids, int64_t first, double* e_out,
+                           int32_t* status_out, const uint8_t* evict_mask, int32_t* iters_out, double* resid_out,
+                           hipStream_t st) {
+  if (ids.empty()) return IFCI_OK;
+  if (ids != p->order_batch) {
+    // a new work list: wait for any earlier upload from order_batch
+    // before reusing its host memory (a repeated list is already there)
+    HIP_TRY(hipStreamSynchronize(st), "ifci_davidson");
+    p->order_batch = ids;
+    HIP_TRY(hipMemcpyAsync(p->d_order, p->order_batch.data(), ids.size() * sizeof(int32_t), hipMemcpyHostToDevice,
+                           st),
+            "ifci_davidson upload");
+  }
+  SolveArgs A = solve_args(p, first, e_out, status_out, evict_mask, iters_out, resid_out);
+  A.count = (int32_t)ids.size();
   HIP_TRY(launch_batched(A, batch_lds(p, ids), st), "ifci_davidson batched");
+  return IFCI_OK;
+}
+
+// The on-chip increments of every member (all of one solver) in one launch,
+// heaviest first over all plans.
+ifci_status launch_on_chip_group(ifci_plan_s* owner, const std::vector<WideMember>& members, hipStream_t st) {
+  std::vector<SolveArgs> jobs;
+  std::vector<int2> work;
+  int lds = 0;
+  for (const WideMember& m : members) {
+    if (m.ids.empty()) continue;
+    for (int32_t i : m.ids) work.push_back(make_int2((int)jobs.size(), i));
+    jobs.push_back(solve_args(m.P, m.first, m.e_out, m.status_out, m.evict, m.iters_out, m.resid_out));
+    jobs.back().order = nullptr;  // the work list names the increments
+    jobs.back().count = (int32_t)m.ids.size();
+    lds = std::max(lds, batch_lds(m.P, m.ids));
+  }
+  if (work.empty()) return IFCI_OK;
+  std::vector<const WideMember*> of_job;
+  for (const WideMember& m : members)
+    if (!m.ids.empty()) of_job.push_back(&m);
+  std::stable_sort(work.begin(), work.end(), [&](const int2& a, const int2& b) {
+    return of_job[a.x]->P->inc[a.y].n_det > of_job[b.x]->P->inc[b.y].n_det;
+  });
+  release_in_flight(owner, false);
+  const int64_t at_work = ((int64_t)jobs.size() * sizeof(SolveArgs) + 255) / 256 * 256;
+  const int64_t need = at_work + (int64_t)work.size() * sizeof(int2);
+  ifci_status s = grow(&owner->group_jobs, &owner->group_jobs_bytes, need, st, "ifci_davidson_group work list");
+  if (s != IFCI_OK) return s;
+  ifci_plan_s::InFlight fl;  // keeps the host copies until their upload has run
+  const char* h_jobs = push_bytes(fl.host, jobs);
+  const char* h_work = push_bytes(fl.host, work);
+  HIP_TRY(hipMemcpyAsync(owner->group_jobs, h_jobs, jobs.size() * sizeof(SolveArgs), hipMemcpyHostToDevice, st),
+          "ifci_davidson_group upload");
+  HIP_TRY(hipMemcpyAsync(owner->group_jobs + at_work, h_work, work.size() * sizeof(int2), hipMemcpyHostToDevice, st),
+          "ifci_davidson_group upload");
+  HIP_TRY(hipEventCreateWithFlags(&fl.done, hipEventDisableTiming), "event");
+  const hipError_t re = hipEventRecord(fl.done, st);
+  owner->in_flight.push_back(std::move(fl));
+  HIP_TRY(re, "event");
+  HIP_TRY(launch_batched_group((const SolveArgs*)owner->group_jobs, (const int2*)(owner->group_jobs + at_work),
+                               (int)work.size(), owner->opt.max_space, lds, st),
+          "ifci_davidson_group batched");
   return IFCI_OK;
 }
 
@@ -920,16 +979,25 @@ ifci_status ifci_davidson_group(const ifci_plan_t* plans, int32_t n_plans, doubl
   }
   DeviceGuard g(O->device);
   hipStream_t st = (hipStream_t)stream;
-  std::vector<WideMember> mem;
+  std::vector<WideMember> mem, chip;
   for (int32_t j = 0; j < n_plans; ++j) {
     ifci_plan_s* p = plans[j];
     std::vector<int32_t> ids, rest;
     for (int32_t i : p->order_all) (p->batched_ok[i] ? ids : rest).push_back(i);
     int32_t* it = iters_out ? iters_out[j] : nullptr;
     double* rs = resid_out ? resid_out[j] : nullptr;
-    ifci_status s = launch_on_chip(p, ids, 0, e_out[j], status_out[j], nullptr, it, rs, st);
-    if (s != IFCI_OK) return s;
+    if (!ids.empty()) chip.push_back(WideMember{p, ids, 0, e_out[j], status_out[j], it, rs, nullptr});
     if (!rest.empty()) mem.push_back(WideMember{p, rest, 0, e_out[j], status_out[j], it, rs, nullptr});
+  }
+  {
+    ifci_status s = IFCI_OK;
+    if (chip.size() == 1) {
+      const WideMember& m = chip[0];
+      s = launch_on_chip(m.P, m.ids, 0, m.e_out, m.status_out, nullptr, m.iters_out, m.resid_out, st);
+    } else {
+      s = launch_on_chip_group(O, chip, st);
+    }
+    if (s != IFCI_OK) return s;
   }
   if (!mem.empty()) {
     ifci_status s = run_wide(O, mem, st);

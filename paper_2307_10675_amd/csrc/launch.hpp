@@ -20,6 +20,10 @@ hipError_t launch_embed(const IncDev* incs, int n_inc, const int32_t* orbs, cons
 int64_t batched_lds_bytes(int k, int n_str, int n_link);
 int64_t batched_lds_want(int k, int n_str, int n_link);
 hipError_t launch_batched(const SolveArgs& A, int lds_bytes, hipStream_t st);
+// The same for the increments of several plans: work (device) holds pairs
+// (index into jobs, increment of that job), count of them.
+hipError_t launch_batched_group(const SolveArgs* jobs, const int2* work, int count, int max_space, int lds_bytes,
+                                hipStream_t st);
 hipError_t launch_sigma_one(const IncDev* incs, int inc, const double* ints, const int32_t* tables,
                             const double* c, double* sig, int precision, int lds_bytes,
                             hipStream_t st);

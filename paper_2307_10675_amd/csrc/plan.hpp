@@ -58,6 +58,8 @@ struct ifci_plan_s {
   std::vector<InFlight> in_flight;
   char* group_ctl = nullptr;  // control block of solves across several plans (grown on demand)
   int64_t group_ctl_bytes = 0;
+  char* group_jobs = nullptr;  // arguments and work list of on-chip solves across several plans
+  int64_t group_jobs_bytes = 0;
   // device
   ifci::IncDev* d_inc = nullptr;
   int32_t* d_orbs = nullptr;
