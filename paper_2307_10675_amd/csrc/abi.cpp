@@ -261,7 +261,6 @@ ifci_status run_wide(ifci_plan_s* owner, std::vector<WideMember>& members, hipSt
       return IFCI_ERR_STATE;
     }
   }
-  HIP_TRY(wide_prepare(0), "ifci_davidson wide");
   if (!O->capture_stream) HIP_TRY(hipStreamCreateWithFlags(&O->capture_stream, hipStreamNonBlocking), "stream");
   if (!O->pinned) HIP_TRY(hipHostMalloc((void**)&O->pinned, 2 * sizeof(int32_t), hipHostMallocDefault), "pinned");
   for (hipEvent_t& e : O->poll_event)
@@ -277,6 +276,7 @@ ifci_status run_wide(ifci_plan_s* owner, std::vector<WideMember>& members, hipSt
       if (std::find(shapes.begin(), shapes.end(), key) == shapes.end()) shapes.push_back(key);
     }
   for (const std::pair<int, int>& key : shapes) {
+    HIP_TRY(wide_prepare(key.first), "ifci_davidson wide");
     std::vector<std::vector<int32_t>> todo(members.size());
     size_t left = 0;
     for (size_t mi = 0; mi < members.size(); ++mi)
@@ -798,7 +798,7 @@ ifci_status ifci_sigma_sector(ifci_plan_t p, int64_t inc, const double* c, doubl
     return IFCI_ERR_ARG;
   }
   const IncDev& d = p->inc[inc];
-  if (!p->batched_ok[inc] && !sigma_column_supported(d)) {
+  if (!p->batched_ok[inc] && !sigma_sector_shape(d)) {
     set_error("ifci_sigma_sector: no symmetric-sector sigma for this increment shape");
     return IFCI_ERR_UNSUPPORTED;
   }
@@ -910,7 +910,6 @@ ifci_status ifci_davidson(ifci_plan_t p, int64_t first, int64_t count, double* e
           p->slot_events.push_back(se);
         }
       }
-      prepare_sigma_wide();
       HIP_TRY(hipEventRecord(p->fork_event, st), "ifci_davidson");
       for (int w = 0; w < W; ++w) HIP_TRY(hipStreamWaitEvent(p->slot_streams[w], p->fork_event, 0), "ifci_davidson");
       std::atomic<size_t> next(0);

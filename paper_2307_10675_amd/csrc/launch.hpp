@@ -29,13 +29,13 @@ hipError_t launch_sigma_one(const IncDev* incs, int inc, const double* ints, con
                             hipStream_t st);
 
 // Device-wide sigma for any increment.  mode 0: c and sigma full [n_det]
-// vectors, any c (E materialised in the workspace).  mode 1: c and sigma
-// packed scaled symmetric vectors; half-filled increments of 10, 12 or 14
-// orbitals take the fused column kernel (sigma_column_supported), others the
-// materialised E.
+// vectors, any c.  mode 1: c and sigma packed scaled symmetric vectors.
+// Increments of 9 to 14 orbitals (mode 1: and half-filled 16) take the fused
+// column kernel (sigma_column_supported), others the materialised E.  `E` is
+// scratch: npair x n_det values, or sigma_column_ws_doubles(d, 2 in mode 0).
 bool sigma_column_supported(const IncDev& d);
-hipError_t prepare_sigma_wide();  // one-time kernel attributes, thread safe
-int64_t sigma_column_ws_doubles(const IncDev& d);  // workspace of the column path
+bool sigma_sector_shape(const IncDev& d);  // shapes of ifci_sigma_sector above 8 orbitals
+int64_t sigma_column_ws_doubles(const IncDev& d, int parts);  // workspace of the column path
 // The static scratch array (plain.hip): its device address on the current
 // device (looked up once per device), kStaticScratchDoubles doubles.
 constexpr int64_t kStaticScratchDoubles = (int64_t)4 << 20;  // 32 MiB

@@ -4,6 +4,7 @@
 // the unfused per-increment path (one launch per step, the host reading the
 // solver state every iteration) that the batched solvers are compared with.
 // The kernel bodies live in sigma_wide.hpp and davidson_ops.hpp.
+#include <algorithm>
 #include <map>
 #include <mutex>
 #include <set>
@@ -22,40 +23,55 @@ __global__ void __launch_bounds__(256) sym_combine_kernel(IncDev d, const double
   sym_combine_body(d.n_str, Sm, blockIdx.x, gridDim.x, tl, [&](int64_t i, double v) { sig[i] = v; });
 }
 
+// Shapes of the column kernels: 9 to 14 orbitals at any filling (LDS holds
+// the fragments, a column and its accumulator), 16 at half filling.
 bool sigma_column_supported(const IncDev& d) {
+  return (d.k >= 9 && d.k <= 14) || (d.k == 16 && d.na * 2 == d.k);
+}
+// Shapes whose symmetric-sector product is an entry of its own.
+bool sigma_sector_shape(const IncDev& d) {
   return d.na * 2 == d.k && (d.k == 10 || d.k == 12 || d.k == 14 || d.k == 16);
 }
 
 // Workspace doubles of the column path (full C of either precision, S, the
-// fragment image, with 256-byte alignment of each).
-int64_t sigma_column_ws_doubles(const IncDev& d) {
+// fragment image, with 256-byte alignment of each); `parts` matrices and S.
+static int64_t up32(int64_t x) { return (x + 31) / 32 * 32; }
+int64_t sigma_column_ws_doubles(const IncDev& d, int parts) {
   const int64_t n = d.n_str;
-  auto up = [](int64_t x) { return (x + 31) / 32 * 32; };
   const int64_t np = (int64_t)d.k * (d.k + 1) / 2, mt = (np + 15) / 16, ks = (np + 3) / 4;
-  return up((n + 1) * n + 16) + up(n * n) + up(mt * (ks + 1) * 64) + 64;
+  return parts * (up32((n + 1) * n + 16) + up32(n * n)) + up32(mt * (ks + 1) * 64) + 64;
 }
 
+// mode 0: c and sig full vectors, any c; mode 1: packed scaled symmetric ones.
 template <typename T, int K>
 static hipError_t launch_column_k(const IncDev& d, const double* V, const int32_t* ptab, const int16_t* ptabT,
-                                  const double* c, double* sig, double* ws, double shift, hipStream_t st) {
+                                  const double* c, double* sig, double* ws, int mode, double shift, hipStream_t st) {
   typedef ColShape<T, K> SH;
   static_assert(SH::lds <= kMaxLds, "column sigma LDS");
-  const int n = d.n_str;
-  // workspace (256-byte aligned): full C, then S, then the fragment image,
-  // each starting on a 256-byte boundary
-  auto up = [](int64_t x) { return (x + 31) / 32 * 32; };
+  const hipError_t e = allow_max_lds((const void*)sigma_column_kernel<T, K>);
+  if (e != hipSuccess) return e;
+  const int n = d.n_str, parts = mode == 0 ? 2 : 1;
+  // workspace (256-byte aligned): full C (and its transpose), then S, then the
+  // fragment image, each starting on a 256-byte boundary
   T* cf = (T*)ws;
-  const int64_t cf_elems = (int64_t)(n + 1) * n + 16;
-  const int64_t off_s = up((cf_elems * (int64_t)sizeof(T) + 7) / 8);
-  double* Sm = ws + off_s;
-  T* vfg = (T*)(ws + up(off_s + (int64_t)n * n));
+  const int64_t cf_doubles = up32(((int64_t)(n + 1) * n + 16) * (int64_t)sizeof(T) / 8 + 1);
+  const int64_t cf_step = cf_doubles * 8 / (int64_t)sizeof(T);
+  double* Sm = ws + parts * cf_doubles;
+  T* vfg = (T*)(ws + up32(parts * (cf_doubles + (int64_t)n * n)));
   const int nfrag = (int)(SH::vf_bytes / sizeof(T));
   hipLaunchKernelGGL((col_frag_kernel<T, K>), dim3((nfrag + 255) / 256), dim3(256), 0, st, V, shift, 2.0 * d.na,
                      vfg);
-  hipLaunchKernelGGL((expand_sym_kernel<T>), dim3(2048), dim3(256), 0, st, d, c, cf);
-  hipLaunchKernelGGL((sigma_column_kernel<T, K>), dim3(n), dim3(col_threads<T>()), (unsigned)SH::lds, st, d, V, ptab,
-                     ptabT, (const T*)cf, (const T*)vfg, Sm);
-  hipLaunchKernelGGL(sym_combine_kernel, dim3(4096), dim3(256), 0, st, d, Sm, sig);
+  const unsigned tiles = (unsigned)std::min<int64_t>(4096, (int64_t)((n + 31) / 32) * ((n + 31) / 32) + 1);
+  if (mode == 0)
+    hipLaunchKernelGGL((column_both_kernel<T>), dim3(tiles), dim3(256), 0, st, n, c, cf, cf_step);
+  else
+    hipLaunchKernelGGL((expand_sym_kernel<T>), dim3(std::min(2048u, tiles)), dim3(256), 0, st, d, c, cf);
+  hipLaunchKernelGGL((sigma_column_kernel<T, K>), dim3(parts * n), dim3(col_threads<T>()), (unsigned)SH::lds, st, n,
+                     ptab, ptabT, (const T*)cf, cf_step, (const T*)vfg, Sm);
+  if (mode == 0)
+    hipLaunchKernelGGL(column_sum_kernel, dim3(tiles), dim3(256), 0, st, n, Sm, sig);
+  else
+    hipLaunchKernelGGL(sym_combine_kernel, dim3(tiles), dim3(256), 0, st, d, Sm, sig);
   return hipGetLastError();
 }
 
@@ -63,6 +79,8 @@ template <typename T, int K>
 static hipError_t launch_column_split(const IncDev& d, const double* V, const int32_t* ptab, const int16_t* ptabT,
                                       const double* c, double* sig, double* ws, double shift, hipStream_t st) {
   typedef ColSplit<T, K> SH;
+  const hipError_t le = allow_max_lds((const void*)sigma_column_split_kernel<T, K>);
+  if (le != hipSuccess) return le;
   const int n = d.n_str;
   auto up = [](int64_t x) { return (x + 31) / 32 * 32; };
   T* cf = (T*)ws;
@@ -93,35 +111,20 @@ hipError_t allow_max_lds(const void* fn) {
   return e;
 }
 
-// Set-up of the column kernels on the current device (their LDS exceeds the
-// default limit); safe to call from several host threads.
-hipError_t prepare_sigma_wide() {
-  const void* fns[] = {(const void*)sigma_column_kernel<float, 10>, (const void*)sigma_column_kernel<double, 10>,
-                       (const void*)sigma_column_kernel<float, 12>, (const void*)sigma_column_kernel<double, 12>,
-                       (const void*)sigma_column_kernel<float, 14>, (const void*)sigma_column_kernel<double, 14>,
-                       (const void*)sigma_column_split_kernel<float, 16>,
-                       (const void*)sigma_column_split_kernel<double, 16>};
-  for (const void* f : fns) {
-    const hipError_t e = allow_max_lds(f);
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
-}
-
 static hipError_t launch_sigma_column(const IncDev& d, const double* V, const int32_t* ptab, const int16_t* ptabT,
-                                      const double* c, double* sig, double* ws, int precision, double shift,
+                                      const double* c, double* sig, double* ws, int precision, int mode, double shift,
                                       hipStream_t st) {
-  if (prepare_sigma_wide() != hipSuccess) return hipErrorInvalidValue;
   const bool f32 = precision == IFCI_MIXED;
   switch (d.k) {
-    case 10: return f32 ? launch_column_k<float, 10>(d, V, ptab, ptabT, c, sig, ws, shift, st)
-                        : launch_column_k<double, 10>(d, V, ptab, ptabT, c, sig, ws, shift, st);
-    case 12: return f32 ? launch_column_k<float, 12>(d, V, ptab, ptabT, c, sig, ws, shift, st)
-                        : launch_column_k<double, 12>(d, V, ptab, ptabT, c, sig, ws, shift, st);
-    case 14: return f32 ? launch_column_k<float, 14>(d, V, ptab, ptabT, c, sig, ws, shift, st)
-                        : launch_column_k<double, 14>(d, V, ptab, ptabT, c, sig, ws, shift, st);
-    case 16: return f32 ? launch_column_split<float, 16>(d, V, ptab, ptabT, c, sig, ws, shift, st)
-                        : launch_column_split<double, 16>(d, V, ptab, ptabT, c, sig, ws, shift, st);
+#define IFCI_COL(K)                                                                               \
+  case K: return f32 ? launch_column_k<float, K>(d, V, ptab, ptabT, c, sig, ws, mode, shift, st)  \
+                     : launch_column_k<double, K>(d, V, ptab, ptabT, c, sig, ws, mode, shift, st);
+    IFCI_COL(9) IFCI_COL(10) IFCI_COL(11) IFCI_COL(12) IFCI_COL(13) IFCI_COL(14)
+#undef IFCI_COL
+    case 16:
+      if (mode == 0) return hipErrorInvalidValue;
+      return f32 ? launch_column_split<float, 16>(d, V, ptab, ptabT, c, sig, ws, shift, st)
+                 : launch_column_split<double, 16>(d, V, ptab, ptabT, c, sig, ws, shift, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -159,8 +162,10 @@ hipError_t launch_sigma_wide(const IncDev& d, const IncDev*, int, const double* 
   const double* V = ints + d.int_off + int_block(d.k).V;
   const int32_t* ptab = tables + d.pair_off;
   const int32_t* links = tables + d.link_off;
-  if (mode == 1 && sigma_column_supported(d))
-    return launch_sigma_column(d, V, ptab, (const int16_t*)(tables + d.pairT_off), c, sig, E, precision, shift, st);
+  // 16 orbitals have the column form for symmetric vectors only
+  if (sigma_column_supported(d) && (mode == 1 || d.k <= 14))
+    return launch_sigma_column(d, V, ptab, (const int16_t*)(tables + d.pairT_off), c, sig, E, precision, mode, shift,
+                               st);
   const int64_t tiles = (d.n_det + 63) / 64;
   if (tiles > 0x7fffffff) return hipErrorInvalidValue;
   const dim3 g1((unsigned)tiles), blk(kWideThreads);

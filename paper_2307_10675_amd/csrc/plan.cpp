@@ -326,7 +326,7 @@ ifci_status plan_build(ifci_plan_s* P, const ifci_problem* pr, const ifci_option
     for (const ifci::IncDev& d : P->inc) {
       int64_t e = d.npair * d.n_det;
       if (ifci::sigma_column_supported(d))
-        e = d.k > 14 ? ifci::sigma_column_ws_doubles(d) : std::max(e, ifci::sigma_column_ws_doubles(d));
+        e = d.k > 14 ? ifci::sigma_column_ws_doubles(d, 1) : std::max(e, ifci::sigma_column_ws_doubles(d, 2));
       need = std::max(need, e);
     }
     P->E_doubles = align_up(need, 32);

@@ -167,16 +167,21 @@ __global__ void __launch_bounds__(kWideThreads) gather_sym_kernel(IncDev d, cons
   if (i < d.n_sym) sig[i] = gather_sym_value<T>(d, links, E, i);
 }
 
-// ------------------------------------------------- fused column sigma (k 10..14)
-// Symmetric vectors of increments too large for the on-chip solver, one
-// workgroup per beta string b (a column of C).  With the pair table of
+// ------------------------------------------------- fused column sigma (k 9..14)
+// Increments too large for the on-chip solver, one workgroup per beta string b
+// (a column of C).  With the pair table of
 // string J, (J1, s1) = E_Q J (read pair-major, 16 strings a row segment),
 // the column is
 //   D[Q][J] = s1 C[J1][b] + s2 C[J][J2]      ((J2, s2) = E_Q b),
 //   E[P][J] = sum_Q V[P][Q] D[Q][J]           (MFMA, 16-string tiles),
 //   S[E_P J][b] += s E[P][J]                  (scatter, LDS FP64 atomics),
 // the scatter form of the alpha gather (E_P is symmetric, so the pair table
-// is its own inverse).  sigma = S + S^T follows in a separate pass.  The
+// is its own inverse).  For symmetric C, sigma = S + S^T follows in a separate
+// pass.  For any C, S is the alpha part of sigma, and the beta part is the
+// transpose of the alpha part of the transposed vector: the columns of C and
+// of C^T run in one launch, sigma = S(C) + S(C^T)^T (twice the contraction,
+// against npair x n_det values of E through memory in the product that
+// stores it).  The
 // column copy of C, the A fragments of V and the FP64 accumulator S[:, b]
 // live in LDS; C (full, unscaled, in the contraction precision) and the
 // table rows come from L2.  Where LDS allows, the column copy is stored with
@@ -198,12 +203,12 @@ struct ColShape {
   static constexpr int KS2 = (KS + 1) / 2;  // FP32: two k-steps per LDS read
   static constexpr int N = max_strings(K);
   static constexpr int64_t vf_bytes = (int64_t)MT * (sizeof(T) == 4 ? 2 * KS2 : KS) * 64 * sizeof(T);
-  static constexpr int64_t brow_bytes = 32 * (int64_t)KS;  // [KS][4] uint32 row offsets + [KS][4] T signs
+  static constexpr int64_t brow_bytes = (16 + 4 * (int64_t)sizeof(T)) * KS;  // [KS][4] uint32 row offsets + [KS][4] T signs
   static constexpr bool kNeg =
-      vf_bytes + 2 * (int64_t)(N + 1) * sizeof(T) + 16 + 16 * (int64_t)(N + 1) + brow_bytes <= kMaxLds;
+      vf_bytes + 2 * (int64_t)(N + 1) * sizeof(T) + 32 + 16 * (int64_t)(N + 1) + brow_bytes <= kMaxLds;
   static constexpr int64_t col_bytes = (kNeg ? 2 : 1) * (int64_t)(N + 1) * sizeof(T);
   static constexpr int64_t s_bytes = (kNeg ? 16 : 8) * (int64_t)(N + 1);
-  static constexpr int64_t lds = vf_bytes + ((col_bytes + 15) / 16) * 16 + s_bytes + brow_bytes;
+  static constexpr int64_t lds = vf_bytes + ((col_bytes + 15) / 16) * 16 + s_bytes + brow_bytes + 16;
 };
 
 // Tiles of 32 x 32 entries of the upper triangle (ta <= tb).
@@ -297,21 +302,26 @@ __global__ void __launch_bounds__(256) col_frag_kernel(const double* __restrict_
 
 // Column b of the product (see above); `lds` is the workgroup's dynamic
 // LDS.  load_frag: copy the A-fragment image vfg into LDS first (it stays
-// there for later columns of the same increment).  Ends with a barrier, so
-// the next column may reuse the LDS at once.
+// there for later columns of the same increment).  ordered: the tiles scatter
+// in turn, so that the sums do not depend on how the waves are scheduled (for
+// vectors of any symmetry, whose product has always been reproducible to the
+// bit; a wave only waits for tiles of the waves beside it, which are resident
+// with it; 12o12e 0.58 -> 0.62 ms, but 14o14e 5.2 -> 6.9 ms for a symmetric
+// vector).  Ends with a barrier, so the next column may reuse the LDS at once.
 template <typename T, int K>
-__device__ __forceinline__ void column_body(const int32_t* __restrict__ ptab, const int16_t* __restrict__ ptabT,
+__device__ __forceinline__ void column_body(int N, const int32_t* __restrict__ ptab, const int16_t* __restrict__ ptabT,
                                             const T* __restrict__ cf, const T* __restrict__ vfg,
-                                            double* __restrict__ Sm, int b, char* lds, bool load_frag) {
+                                            double* __restrict__ Sm, int b, char* lds, bool load_frag, bool ordered) {
   typedef ColShape<T, K> SH;
   typedef Mfma<T> M;
-  constexpr int NP = SH::NP, MT = SH::MT, KS = SH::KS, N = SH::N;
+  constexpr int NP = SH::NP, MT = SH::MT, KS = SH::KS;
   constexpr bool kNeg = SH::kNeg;
   T* Vf = (T*)lds;
   T* ccol = (T*)(lds + SH::vf_bytes);
   double* S = (double*)(lds + SH::vf_bytes + ((SH::col_bytes + 15) / 16) * 16);
   uint32_t* browl = (uint32_t*)((char*)S + SH::s_bytes);
   T* bsgl = (T*)(browl + 4 * KS);
+  int* turn = (int*)((char*)browl + SH::brow_bytes);  // the tile whose scatter is next (ordered)
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
   // the A-fragment image of V (built once per sigma or solve by col_frag_body)
   if (load_frag)
@@ -324,6 +334,7 @@ __device__ __forceinline__ void column_body(const int32_t* __restrict__ ptab, co
     if (kNeg) ccol[N + 1 + j] = -v;
   }
   for (int j = threadIdx.x; j < (kNeg ? 2 : 1) * (N + 1); j += blockDim.x) S[j] = 0.0;
+  if (ordered && threadIdx.x == 0) *turn = 0;
   // beta part of k-step s for lanes with L / 16 = kq: browl[4 s + kq] the
   // offset of row J2 of C (J2 = N, the zero row, for no link), bsgl the sign
   for (int i = threadIdx.x; i < 4 * KS; i += blockDim.x) {
@@ -390,6 +401,8 @@ __device__ __forceinline__ void column_body(const int32_t* __restrict__ ptab, co
     }
     // scatter: register r of row tile m holds pair 4 (4 m + r) + kq, whose
     // table entry is ent[4 m + r]; S[E_P J] += s E[P][J]
+    if (ordered)
+      while (__hip_atomic_load(turn, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) != t) __builtin_amdgcn_s_sleep(1);
     if (jv) {
 #pragma unroll
       for (int m = 0; m < MT; ++m)
@@ -407,6 +420,7 @@ __device__ __forceinline__ void column_body(const int32_t* __restrict__ ptab, co
           }
         }
     }
+    if (ordered) __hip_atomic_store(turn, t + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
   }
   __syncthreads();
   for (int j = threadIdx.x; j < N; j += blockDim.x) Sm[(int64_t)b * N + j] = kNeg ? S[j] - S[N + 1 + j] : S[j];
@@ -414,14 +428,16 @@ __device__ __forceinline__ void column_body(const int32_t* __restrict__ ptab, co
 }
 
 template <typename T, int K>
-__global__ void __launch_bounds__(col_threads<T>()) sigma_column_kernel(IncDev d, const double* __restrict__ V,
-                                                                   const int32_t* __restrict__ ptab,
+__global__ void __launch_bounds__(col_threads<T>()) sigma_column_kernel(int n, const int32_t* __restrict__ ptab,
                                                                    const int16_t* __restrict__ ptabT,
-                                                                   const T* __restrict__ cf,
+                                                                   const T* __restrict__ cf, int64_t cf_step,
                                                                    const T* __restrict__ vfg,
                                                                    double* __restrict__ Sm) {
+  // block n + b: column b of a second matrix, cf_step entries after the first
   extern __shared__ __align__(16) char lds[];
-  column_body<T, K>(ptab, ptabT, cf, vfg, Sm, blockIdx.x, lds, true);
+  const int part = (int)blockIdx.x >= n ? 1 : 0;
+  column_body<T, K>(n, ptab, ptabT, cf + part * cf_step, vfg, Sm + (int64_t)part * n * n, (int)blockIdx.x - part * n,
+                    lds, true, (int)gridDim.x > n);
 }
 
 // 16 orbitals (12,870 strings, 136 pairs) do not fit that LDS layout.  The
@@ -616,6 +632,61 @@ __device__ __forceinline__ void sym_combine_body(int n, const double* __restrict
         const double y = Sm[(int64_t)b * n + a];
         out(tri(b) + a, a == b ? 2.0 * y : kSqrt2 * (y + tl[tx][ty + k]));
       }
+    }
+    __syncthreads();
+  }
+}
+
+// c [n x n] -> its transpose at cf and c itself at cf + step, of T, each with a
+// zero row n and a tail of 16 zeros: what the column sigmas of c and of its
+// transpose read (row J holds C[:, J], or C[J, :]).
+template <typename T>
+__global__ void __launch_bounds__(256) column_both_kernel(int n, const double* __restrict__ c, T* __restrict__ cf,
+                                                          int64_t step) {
+  __shared__ T tl[32][33];
+  const int tn = (n + 31) / 32;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  if (blockIdx.x < 2)
+    for (int j = threadIdx.x; j < n + 16; j += blockDim.x) cf[blockIdx.x * step + (int64_t)n * n + j] = (T)0;
+  for (int64_t t = blockIdx.x; t < (int64_t)tn * tn; t += gridDim.x) {
+    const int r0 = (int)(t / tn) * 32, c0 = (int)(t % tn) * 32;
+#pragma unroll
+    for (int k = 0; k < 32; k += 8) {
+      const int rr = r0 + ty + k, cc = c0 + tx;
+      if (rr < n && cc < n) {
+        const T v = (T)c[(int64_t)rr * n + cc];
+        cf[step + (int64_t)rr * n + cc] = v;
+        tl[ty + k][tx] = v;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 32; k += 8) {
+      const int rr = c0 + ty + k, cc = r0 + tx;
+      if (rr < n && cc < n) cf[(int64_t)rr * n + cc] = tl[tx][ty + k];
+    }
+    __syncthreads();
+  }
+}
+
+// sigma[a][b] = Sm[0][b][a] + Sm[1][a][b], the columns of both products.
+static __global__ void __launch_bounds__(256) column_sum_kernel(int n, const double* __restrict__ Sm,
+                                                                double* __restrict__ sig) {
+  __shared__ double tl[32][33];
+  const int tn = (n + 31) / 32;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  for (int64_t t = blockIdx.x; t < (int64_t)tn * tn; t += gridDim.x) {
+    const int r0 = (int)(t / tn) * 32, c0 = (int)(t % tn) * 32;
+#pragma unroll
+    for (int k = 0; k < 32; k += 8) {
+      const int b = c0 + ty + k, a = r0 + tx;
+      tl[ty + k][tx] = (a < n && b < n) ? Sm[(int64_t)b * n + a] : 0.0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 32; k += 8) {
+      const int a = r0 + ty + k, b = c0 + tx;
+      if (a < n && b < n) sig[(int64_t)a * n + b] = tl[tx][ty + k] + Sm[(int64_t)n * n + (int64_t)a * n + b];
     }
     __syncthreads();
   }

@@ -266,9 +266,9 @@ __global__ void __launch_bounds__((wide_col_threads<T, K>()), (wide_col_waves<T,
     const int b = (int)(u % n);
     const WideItem* w = it[item];
     const ColScratch cs = col_scratch(w->d);
-    column_body<T, K>(w->tabs + w->d.pair_off, (const int16_t*)(w->tabs + w->d.pairT_off), (const T*)(w->sc + cs.cf),
+    column_body<T, K>(n, w->tabs + w->d.pair_off, (const int16_t*)(w->tabs + w->d.pairT_off), (const T*)(w->sc + cs.cf),
                       (const T*)(w->sc + (sizeof(T) == 4 ? cs.vf32 : cs.vf64)), w->sc + cs.sm, b, lds,
-                      item != prev);
+                      item != prev, false);
     prev = item;
   }
 }
@@ -432,32 +432,33 @@ hipError_t column_sigma(const WideRun& R, int which, hipStream_t s) {
   return hipSuccess;
 }
 
-template <typename T>
-hipError_t column_sigma_k(const WideRun& R, int which, hipStream_t s) {
-  switch (R.k) {
-    case 10: return column_sigma<T, 10>(R, which, s);
-    case 12: return column_sigma<T, 12>(R, which, s);
-    case 14: return column_sigma<T, 14>(R, which, s);
-    case 16: return column_sigma<T, 16>(R, which, s);
+// f(std::integral_constant<int, K>) for the shapes of the column path
+template <typename F>
+hipError_t by_orbitals(int k, F&& f) {
+  switch (k) {
+    case 9: return f(std::integral_constant<int, 9>{});
+    case 10: return f(std::integral_constant<int, 10>{});
+    case 11: return f(std::integral_constant<int, 11>{});
+    case 12: return f(std::integral_constant<int, 12>{});
+    case 13: return f(std::integral_constant<int, 13>{});
+    case 14: return f(std::integral_constant<int, 14>{});
+    case 16: return f(std::integral_constant<int, 16>{});
     default: return hipErrorInvalidValue;
   }
 }
 
-template <typename T, int K>
-hipError_t frag_k(const WideRun& R, hipStream_t s) {
-  hipLaunchKernelGGL((wb_frag_kernel<T, K>), dim3(kVecGrid), dim3(kVecThreads), 0, s, R.items, R.n);
-  return hipSuccess;
+template <typename T>
+hipError_t column_sigma_k(const WideRun& R, int which, hipStream_t s) {
+  return by_orbitals(R.k, [&](auto kk) { return column_sigma<T, decltype(kk)::value>(R, which, s); });
 }
 
 template <typename T>
 hipError_t frags(const WideRun& R, hipStream_t s) {
-  switch (R.k) {
-    case 10: return frag_k<T, 10>(R, s);
-    case 12: return frag_k<T, 12>(R, s);
-    case 14: return frag_k<T, 14>(R, s);
-    case 16: return frag_k<T, 16>(R, s);
-    default: return hipErrorInvalidValue;
-  }
+  return by_orbitals(R.k, [&](auto kk) {
+    hipLaunchKernelGGL((wb_frag_kernel<T, decltype(kk)::value>), dim3(kVecGrid), dim3(kVecThreads), 0, s, R.items,
+                       R.n);
+    return hipSuccess;
+  });
 }
 
 }  // namespace
@@ -472,19 +473,19 @@ int64_t wide_part_doubles(const IncDev& d) { return (int64_t)vec_blocks(d.n_sym)
 int wide_ctl_ints(int n) { return 8 + 3 * n; }
 
 hipError_t wide_prepare(int k) {
-  hipError_t e = prepare_sigma_wide();
-  if (e != hipSuccess) return e;
-  const void* fns[] = {(const void*)wb_column_kernel<float, 10>, (const void*)wb_column_kernel<double, 10>,
-                       (const void*)wb_column_kernel<float, 12>, (const void*)wb_column_kernel<double, 12>,
-                       (const void*)wb_column_kernel<float, 14>, (const void*)wb_column_kernel<double, 14>,
-                       (const void*)wb_column_split_kernel<float, 16>,
-                       (const void*)wb_column_split_kernel<double, 16>};
-  (void)k;
-  for (const void* f : fns) {
-    e = allow_max_lds(f);
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+  if (!((k >= 9 && k <= 14) || k == 16)) return hipSuccess;
+  return by_orbitals(k, [&](auto kk) {
+    constexpr int K = decltype(kk)::value;
+    hipError_t e;
+    if constexpr (K <= 14) {
+      e = allow_max_lds((const void*)wb_column_kernel<float, K>);
+      if (e == hipSuccess) e = allow_max_lds((const void*)wb_column_kernel<double, K>);
+    } else {
+      e = allow_max_lds((const void*)wb_column_split_kernel<float, K>);
+      if (e == hipSuccess) e = allow_max_lds((const void*)wb_column_split_kernel<double, K>);
+    }
+    return e;
+  });
 }
 
 hipError_t wide_setup(const WideRun& R, hipStream_t s) {
