@@ -13,12 +13,20 @@
 // energies handed back.
 //
 // Device data, all in the caller's work buffer:
-//  * the variational space V: keys in insertion order, an open-addressing
-//    hash table key -> index (linear probing, MurmurHash3's 64-bit
-//    finaliser), every key's spin-flipped partner, the diagonal;
-//  * H over V without its diagonal as CSR, rebuilt after every selection;
-//  * the Davidson basis and sigma vectors;
-//  * the PT2 external space: a second hash table key -> N_a.
+//  * the variational space V of a solve: keys in insertion order, and one bit
+//    per determinant of the increment's full space (the reference is a closed
+//    shell and every replacement keeps both electron counts, so a key is a pair
+//    of string ranks: 20.7 MB of bits at 16 orbitals) with the count of bits
+//    before each word.  Membership is one bit test, and the count is a
+//    determinant's place in key order, the order of the full vectors and of
+//    H's columns;
+//  * H over V without its diagonal as CSR, one row per flip pair, extended
+//    after every selection;
+//  * the Davidson basis and sigma vectors, over flip pairs;
+//  * the PT2 external space: a hash table key -> N_a (linear probing,
+//    MurmurHash3's 64-bit finaliser);
+//  * a caller's list of keys (the single steps, for checking them) in a hash
+//    table key -> index: its keys may be of any electron count.
 // Kernels that walk the excitations of a determinant give it one wavefront;
 // the lanes share its occupied/empty orbital lists in LDS and stride over
 // the flat list of its single and double replacements.  The integrals sit
@@ -29,7 +37,7 @@
 #include <string>
 #include <vector>
 
-#include "device_common.hpp"
+#include "hbci_davidson.hpp"
 #include "launch.hpp"
 
 namespace ifci {
@@ -44,10 +52,6 @@ constexpr int kNB = 512;        // workgroups of the vector kernels
 // orbitals (77 KB) two workgroups fit a CU, so 16 waves each keep 32 waves
 // of table probes in flight per CU.
 constexpr int kWaves = 16;
-constexpr int kMaxM = 16;       // largest Davidson subspace
-constexpr int kParts = kMaxM + 1;
-constexpr int kKeepRitz = 4;    // Ritz vectors kept at a Davidson restart
-
 enum : unsigned { kFlagDetCap = 1u, kFlagExtCap = 2u, kFlagDuplicate = 4u, kFlagNoPartner = 8u };
 
 struct HbciCtl {
@@ -57,14 +61,7 @@ struct HbciCtl {
   unsigned int pad;
   double e_core;
   long long nnz;
-};
-
-struct Coef {
-  double v[kMaxM];
-};
-
-struct CoefKeep {
-  double v[kMaxM][kKeepRitz];
+  unsigned long long n_rep;  // flip pairs and flip-invariant keys of V
 };
 
 __device__ __forceinline__ uint64_t hmix(uint64_t x) {
@@ -141,6 +138,10 @@ struct Space {
   HbciCtl* ctl;
 };
 
+__device__ __forceinline__ bool has_det(const Space& V, uint64_t key) {
+  return ht_find(V.keys, V.vals, V.mask, key) >= 0;
+}
+
 __device__ __forceinline__ void add_det(const Space& V, uint64_t key) {
   bool fresh = false;
   const int64_t h = ht_insert(V.keys, V.mask, key, &fresh);
@@ -157,6 +158,45 @@ __device__ __forceinline__ void add_det(const Space& V, uint64_t key) {
     V.vals[h] = -1;
     atomicOr(&V.ctl->flags, kFlagDetCap);
   }
+}
+
+// V of a solve as bits over pairs of string ranks: row ra holds the strings
+// rb of the other spin in W words, pre[word] counts the bits before it.
+struct Bits {
+  uint64_t* w;
+  int32_t* pre;
+  const uint16_t* rank;  // string -> its rank among those of its electron count, in numeric order
+  int W, n_str;
+  uint64_t* dets;
+  int64_t cap;
+  HbciCtl* ctl;
+};
+
+__device__ __forceinline__ bool has_pair(const Bits& V, int ra, int rb) {
+  return V.w[ra * V.W + (rb >> 6)] >> (rb & 63) & 1ull;
+}
+
+// place of the pair in key order, -1 when it is not in V
+__device__ __forceinline__ int32_t place_of(const Bits& V, int ra, int rb) {
+  const int i = ra * V.W + (rb >> 6);
+  const uint64_t w = V.w[i], bit = 1ull << (rb & 63);
+  return w & bit ? V.pre[i] + __popcll(w & (bit - 1ull)) : -1;
+}
+
+__device__ __forceinline__ bool has_det(const Bits& V, uint64_t key) {
+  return has_pair(V, V.rank[(uint32_t)key], V.rank[(uint32_t)(key >> 32)]);
+}
+
+__device__ __forceinline__ void add_det(const Bits& V, uint64_t key) {
+  const int ra = V.rank[(uint32_t)key], rb = V.rank[(uint32_t)(key >> 32)];
+  unsigned long long* w = (unsigned long long*)(V.w + ra * V.W + (rb >> 6));
+  const unsigned long long bit = 1ull << (rb & 63);
+  if ((*w & bit) || (atomicOr(w, bit) & bit)) return;
+  const unsigned long long idx = atomicAdd(&V.ctl->n_det, 1ull);
+  if ((int64_t)idx < V.cap)
+    V.dets[idx] = key;
+  else
+    atomicOr(&V.ctl->flags, kFlagDetCap);
 }
 
 // A slot of the external table: the key and its N_a side by side, so that a
@@ -201,7 +241,9 @@ struct Lds {
   double* g;       // packed (pq|rs)
   uint8_t* lo;     // pair decode: u = hi (hi - 1) / 2 + lo, lo < hi < 16
   uint8_t* hi;
-  uint8_t* lists;  // per wave: occ alpha, empty alpha, occ beta, empty beta (16 each)
+  float* bound;    // kernels that screen: largest |(rp|wq)|, w != q, of each pair rp; then the two below
+  double b_single, b_same;  // largest |H| over single and same-spin double replacements
+  uint8_t* lists;  // per wave: occupied then empty orbitals of either spin (16 each), then kWaveBytes for the kernel
 };
 
 __host__ __device__ inline int packed_count(int k) {
@@ -209,23 +251,42 @@ __host__ __device__ inline int packed_count(int k) {
   return np * (np + 1) / 2;
 }
 
-__host__ inline int lds_bytes_for(int k) { return (k * k + packed_count(k)) * 8 + 256 + kWaves * 64; }
+// integral buffer: h', packed (pq|rs), the pair bounds, the two other bounds
+__host__ __device__ inline int bounds_at(int k) { return k * k + packed_count(k); }
+__host__ __device__ inline int ints_count(int k) { return bounds_at(k) + k * (k + 1) / 2 + 2; }
 
+// Bytes of a wave's lists: 32 of orbitals, and the string ranks of its 64
+// single replacements of either spin (rows of H) or their orbital pairs (steps
+// that screen).  At 16 orbitals both sizes leave two workgroups to a CU.
+constexpr int kListRanks = 32 + 256, kListPairs = 32 + 128;
+
+__host__ inline int lds_bytes_for(int k, int list, bool screen) {
+  return (k * k + packed_count(k)) * 8 + 256 + (screen ? (k * (k + 1) / 2 + 3) / 4 * 16 : 0) + kWaves * list;
+}
+
+template <bool SCREEN = false>
 __device__ Lds load_lds(const double* ints, int k) {
   extern __shared__ __align__(16) unsigned char smem[];
   Lds s;
-  const int nint = k * k + packed_count(k);
+  const int nint = k * k + packed_count(k), np = k * (k + 1) / 2;
   s.h1 = (double*)smem;
   s.g = s.h1 + k * k;
   s.lo = smem + nint * 8;
   s.hi = s.lo + 128;
-  s.lists = s.lo + 256;
+  s.bound = (float*)(s.lo + 256);
+  s.lists = s.lo + 256 + (SCREEN ? (np + 3) / 4 * 16 : 0);
   for (int t = threadIdx.x; t < nint; t += blockDim.x) s.h1[t] = ints[t];
   for (int t = threadIdx.x; t < 120; t += blockDim.x) {
     int j = 1;
     while ((j + 1) * j / 2 <= t) ++j;
     s.lo[t] = (uint8_t)(t - j * (j - 1) / 2);
     s.hi[t] = (uint8_t)j;
+  }
+  if (SCREEN) {
+    const double* b = ints + bounds_at(k);
+    for (int t = threadIdx.x; t < np; t += blockDim.x) s.bound[t] = __double2float_ru(b[t]);
+    s.b_single = b[np];
+    s.b_same = b[np + 1];
   }
   __syncthreads();
   return s;
@@ -282,32 +343,30 @@ struct Det {
   uint32_t A, B;
   int na, nb, va, vb, ca2, cb2;
   int sa, sb, daa, dbb, total;
-  const uint8_t* L;
+  const uint8_t *oa, *ea, *ob, *eb;  // occupied and empty orbitals
 };
 
 __device__ __forceinline__ Det make_det(uint64_t key, int k, uint8_t* L, int lane) {
   Det d;
   d.A = (uint32_t)key;
   d.B = (uint32_t)(key >> 32);
+  const uint32_t all = (1u << k) - 1u;
   __builtin_amdgcn_wave_barrier();
   if (lane < k) {
     const int below = __popc(d.A & ((1u << lane) - 1u));
-    if (d.A >> lane & 1u)
-      L[below] = (uint8_t)lane;
-    else
-      L[16 + lane - below] = (uint8_t)lane;
+    L[d.A >> lane & 1u ? below : __popc(d.A & all) + lane - below] = (uint8_t)lane;
   } else if (lane >= 32 && lane < 32 + k) {
     const int p = lane - 32;
     const int below = __popc(d.B & ((1u << p) - 1u));
-    if (d.B >> p & 1u)
-      L[32 + below] = (uint8_t)p;
-    else
-      L[48 + p - below] = (uint8_t)p;
+    L[16 + (d.B >> p & 1u ? below : __popc(d.B & all) + p - below)] = (uint8_t)p;
   }
   __builtin_amdgcn_wave_barrier();
-  d.L = L;
   d.na = __popc(d.A);
   d.nb = __popc(d.B);
+  d.oa = L;
+  d.ea = L + d.na;
+  d.ob = L + 16;
+  d.eb = L + 16 + d.nb;
   d.va = k - d.na;
   d.vb = k - d.nb;
   d.ca2 = d.va * (d.va - 1) / 2;
@@ -323,31 +382,30 @@ __device__ __forceinline__ Det make_det(uint64_t key, int k, uint8_t* L, int lan
 // Target key of replacement t; its matrix element into *val when VAL.
 template <bool VAL>
 __device__ __forceinline__ uint64_t replacement(const Det& d, int t, const Lds& s, int k, double* val) {
-  const uint8_t* L = d.L;
   uint32_t A = d.A, B = d.B;
   if (t < d.sa) {
-    const int p = L[t / d.va], r = L[16 + t % d.va];
+    const int p = d.oa[t / d.va], r = d.ea[t % d.va];
     A ^= (1u << p) | (1u << r);
     if (VAL) *val = single_val(s, k, d.A, d.B, p, r);
   } else if ((t -= d.sa) < d.sb) {
-    const int p = L[32 + t / d.vb], r = L[48 + t % d.vb];
+    const int p = d.ob[t / d.vb], r = d.eb[t % d.vb];
     B ^= (1u << p) | (1u << r);
     if (VAL) *val = single_val(s, k, d.B, d.A, p, r);
   } else if ((t -= d.sb) < d.daa) {
     const int u = t / d.ca2, v = t - u * d.ca2;
-    const int p = L[s.lo[u]], q = L[s.hi[u]], r = L[16 + s.lo[v]], w = L[16 + s.hi[v]];
+    const int p = d.oa[s.lo[u]], q = d.oa[s.hi[u]], r = d.ea[s.lo[v]], w = d.ea[s.hi[v]];
     A ^= (1u << p) | (1u << q) | (1u << r) | (1u << w);
     if (VAL) *val = double_same(s.g, d.A, p, q, r, w);
   } else if ((t -= d.daa) < d.dbb) {
     const int u = t / d.cb2, v = t - u * d.cb2;
-    const int p = L[32 + s.lo[u]], q = L[32 + s.hi[u]], r = L[48 + s.lo[v]], w = L[48 + s.hi[v]];
+    const int p = d.ob[s.lo[u]], q = d.ob[s.hi[u]], r = d.eb[s.lo[v]], w = d.eb[s.hi[v]];
     B ^= (1u << p) | (1u << q) | (1u << r) | (1u << w);
     if (VAL) *val = double_same(s.g, d.B, p, q, r, w);
   } else {
     t -= d.dbb;
     const int u = t / d.sb, v = t - u * d.sb;
-    const int p = L[u / d.va], r = L[16 + u % d.va];
-    const int q = L[32 + v / d.vb], w = L[48 + v % d.vb];
+    const int p = d.oa[u / d.va], r = d.ea[u % d.va];
+    const int q = d.ob[v / d.vb], w = d.eb[v % d.vb];
     A ^= (1u << p) | (1u << r);
     B ^= (1u << q) | (1u << w);
     if (VAL) *val = phase(d.A, p, r) * phase(d.B, q, w) * G(s.g, r, p, w, q);
@@ -355,23 +413,102 @@ __device__ __forceinline__ uint64_t replacement(const Det& d, int t, const Lds& 
   return (uint64_t)A | ((uint64_t)B << 32);
 }
 
+// The string ranks of d's 64 or fewer single replacements of either spin, in
+// the order of the flat list (k <= 16: at most 8 * 8), after its orbital lists.
+struct Ranks {
+  const uint16_t *a, *b;
+  int ra, rb;
+};
+
+__device__ __forceinline__ Ranks make_ranks(const Det& d, const uint16_t* rank, uint8_t* L, int lane) {
+  uint16_t* R = (uint16_t*)(L + 32);
+  if (lane < d.sa) R[lane] = rank[d.A ^ (1u << d.oa[lane / d.va]) ^ (1u << d.ea[lane % d.va])];
+  if (lane < d.sb) R[64 + lane] = rank[d.B ^ (1u << d.ob[lane / d.vb]) ^ (1u << d.eb[lane % d.vb])];
+  __builtin_amdgcn_wave_barrier();
+  return Ranks{R, R + 64, rank[d.A], rank[d.B]};
+}
+
+// Ranks of replacement t's strings.
+__device__ __forceinline__ void replaced_ranks(const Det& d, const Ranks& R, int t, const Lds& s, const uint16_t* rank,
+                                               float inv_sb, int* ra, int* rb) {
+  const int doubles = d.sa + d.sb + d.daa + d.dbb;
+  *ra = R.ra;
+  *rb = R.rb;
+  if (t >= doubles) {
+    t -= doubles;
+    const int u = (int)((t + 0.5f) * inv_sb);  // t / sb: both below 2^12, off by less than 0.5 / 64
+    *ra = R.a[u];
+    *rb = R.b[t - u * d.sb];
+  } else if (t < d.sa) {
+    *ra = R.a[t];
+  } else if (t < d.sa + d.sb) {
+    *rb = R.b[t - d.sa];
+  } else {
+    double v;
+    const uint64_t key = replacement<false>(d, t, s, 0, &v);
+    if (t < d.sa + d.sb + d.daa)
+      *ra = rank[(uint32_t)key];
+    else
+      *rb = rank[(uint32_t)(key >> 32)];
+  }
+}
+
+// The replacements of d that can pass |H_ai c_i| > eps, by the bounds on H:
+// the single ones, the same-spin doubles, and the alpha-beta doubles of those
+// single replacements of either spin whose orbital pair has an integral large
+// enough.  (All bounds hold in floating point too: rounding is monotone, and
+// the sums of a single replacement are given a margin.)
+struct Screen {
+  int singles, same, na, nb, total;
+  const uint8_t *a, *b;  // kept pairs, empty orbital << 4 | occupied
+};
+
+__device__ __forceinline__ Screen make_screen(const Det& d, const Lds& s, double c, double eps, uint8_t* L, int lane) {
+  Screen S;
+  const double ac = fabs(c);
+  S.singles = s.b_single * ac > eps ? d.sa + d.sb : 0;
+  S.same = s.b_same * ac > eps ? d.daa + d.dbb : 0;
+  uint8_t* P = L + 32;
+  const uint64_t below = (1ull << lane) - 1ull;
+  auto keep = [&](int n, int nv, const uint8_t* occ, const uint8_t* emp, uint8_t* out) {
+    int p = 0, r = 0;
+    bool k = false;
+    if (lane < n) {
+      p = occ[lane / nv];
+      r = emp[lane % nv];
+      k = (double)s.bound[tri2(p, r)] * ac > eps;
+    }
+    const uint64_t m = __ballot(k);
+    if (k) out[__popcll(m & below)] = (uint8_t)(r << 4 | p);
+    return (int)__popcll(m);
+  };
+  S.na = keep(d.sa, d.va, d.oa, d.ea, P);
+  S.nb = keep(d.sb, d.vb, d.ob, d.eb, P + 64);
+  S.a = P;
+  S.b = P + 64;
+  S.total = S.singles + S.same + S.na * S.nb;
+  __builtin_amdgcn_wave_barrier();
+  return S;
+}
+
+// Target key and matrix element of the screened list's entry t.
+__device__ __forceinline__ uint64_t screened(const Det& d, const Screen& S, int t, const Lds& s, int k, float inv_nb,
+                                             double* val) {
+  if (t < S.singles) return replacement<true>(d, t, s, k, val);
+  t -= S.singles;
+  if (t < S.same) return replacement<true>(d, d.sa + d.sb + t, s, k, val);
+  t -= S.same;
+  const int u = (int)((t + 0.5f) * inv_nb);
+  const int x = S.a[u], y = S.b[t - u * S.nb];
+  const int p = x & 15, r = x >> 4, q = y & 15, w = y >> 4;
+  *val = phase(d.A, p, r) * phase(d.B, q, w) * G(s.g, r, p, w, q);
+  return (uint64_t)(d.A ^ (1u << p) ^ (1u << r)) | ((uint64_t)(d.B ^ (1u << q) ^ (1u << w)) << 32);
+}
+
 __device__ __forceinline__ int wave_sum_int(int v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
-}
-
-// Sum over the workgroup (256 threads); the result in thread 0.
-__device__ __forceinline__ double group_sum(double v, double* red) {
-  v = wave_sum(v);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  __syncthreads();
-  if (lane == 0) red[wave] = v;
-  __syncthreads();
-  double s = 0.0;
-  if (threadIdx.x == 0)
-    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) s += red[w];
-  return s;
 }
 
 // ------------------------------------------------------------------ kernels
@@ -400,12 +537,47 @@ __global__ void hbci_prep_kernel(const double* __restrict__ h, const double* __r
     const int b = Q - a * (a + 1) / 2;
     ints[k * k + t] = E4(act[i], act[j], act[a], act[b]);
   }
+  __syncthreads();
+  // bounds on H (make_screen)
+  const double* h1 = ints;
+  const double* g = ints + k * k;
+  double* bound = ints + bounds_at(k);
+  const int np = k * (k + 1) / 2;
+  __shared__ unsigned long long top[2];  // non-negative doubles order as their bits
+  if (threadIdx.x < 2) top[threadIdx.x] = 0ull;
+  __syncthreads();
+  for (int t = threadIdx.x; t < np; t += blockDim.x) {
+    int i = 0;
+    while ((i + 1) * (i + 2) / 2 <= t) ++i;
+    const int j = t - i * (i + 1) / 2;
+    double m = 0.0, one = fabs(h1[i * k + j]);
+    for (int w = 0; w < k; ++w) {
+      for (int q = 0; q < w; ++q) m = fmax(m, fabs(G(g, i, j, w, q)));
+      one += 2.0 * fabs(G(g, i, j, w, w)) + fabs(G(g, i, w, w, j));
+    }
+    bound[t] = m;
+    atomicMax(&top[0], (unsigned long long)__double_as_longlong(one * (1.0 + 1e-12)));
+  }
+  const int nd = k * (k - 1) / 2;
+  double same = 0.0;
+  for (int t = threadIdx.x; t < nd * nd; t += blockDim.x) {
+    int p = 1, r = 1;
+    const int u = t / nd, v = t % nd;
+    while ((p + 1) * p / 2 <= u) ++p;
+    while ((r + 1) * r / 2 <= v) ++r;
+    const int q = u - p * (p - 1) / 2, w = v - r * (r - 1) / 2;
+    same = fmax(same, fabs(G(g, r, p, w, q) - G(g, r, q, w, p)));
+  }
+  atomicMax(&top[1], (unsigned long long)__double_as_longlong(same));
+  __syncthreads();
+  if (threadIdx.x < 2) bound[np + threadIdx.x] = __longlong_as_double((long long)top[threadIdx.x]);
   if (threadIdx.x == 0) {
     ctl->n_det = 0;
     ctl->n_ext = 0;
     ctl->flags = 0;
     ctl->e_core = *e_core;
     ctl->nnz = 0;
+    ctl->n_rep = 0;
   }
 }
 
@@ -422,15 +594,26 @@ __global__ void fill_f64_kernel(double* p, int64_t n, double v) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = v;
 }
 
-// V := the caller's keys (or the reference and its partner), in order.
-__global__ void hbci_load_kernel(const uint64_t* __restrict__ in, int64_t n, uint64_t ref, Space V) {
-  if (!in) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-      add_det(V, ref);
-      if (flip_key(ref) != ref) add_det(V, flip_key(ref));
-    }
-    return;
+// rank[s] of every string of the reference's electron count
+__global__ void hbci_rank_kernel(int k, int na, uint16_t* __restrict__ rank) {
+  const int s = blockIdx.x * blockDim.x + threadIdx.x;
+  if (s >= 1 << k || __popc(s) != na) return;
+  int r = 0, i = 0;
+  for (int m = s; m; m &= m - 1) {
+    const int p = __builtin_ctz(m);
+    int b = 1;  // p over ++i
+    ++i;
+    for (int j = 0; j < i; ++j) b = b * (p - j) / (j + 1);
+    r += b;
   }
+  rank[s] = (uint16_t)r;
+}
+
+// V := the reference (a closed shell)
+__global__ void hbci_ref_kernel(uint64_t ref, Bits V) { add_det(V, ref); }
+
+// V := the caller's keys, in order.
+__global__ void hbci_load_kernel(const uint64_t* __restrict__ in, int64_t n, Space V) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
     const uint64_t key = in[i];
     V.dets[i] = key;
@@ -446,22 +629,149 @@ __global__ void hbci_load_kernel(const uint64_t* __restrict__ in, int64_t n, uin
   if (blockIdx.x == 0 && threadIdx.x == 0) V.ctl->n_det = (unsigned long long)n;
 }
 
-// One selection step: every replacement a of a determinant i < n_src with
-// |H_ai c_i| > eps joins V, with its flip partner.
-__global__ void __launch_bounds__(64 * kWaves) hbci_select_kernel(const double* __restrict__ ints, int k,
-                                                                  const double* __restrict__ c, int64_t n_src,
-                                                                  double eps, Space V, int half) {
-  const Lds s = load_lds(ints, k);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint8_t* L = s.lists + wave * 64;
-  for (int64_t i = (int64_t)blockIdx.x * kWaves + wave; i < n_src; i += (int64_t)gridDim.x * kWaves) {
-    const double ci = c[i];
+// Bits before each word, bits before each row's first flip pair, in three
+// passes: rows counted (one wave each), row counts summed, words summed.
+__global__ void __launch_bounds__(256) hbci_row_count_kernel(Bits V, int32_t* __restrict__ cnt) {
+  const int lane = threadIdx.x & 63;
+  const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (r >= V.n_str) return;
+  int all = 0, rep = 0;
+  for (int i = lane; i < V.W; i += 64) {
+    const uint64_t w = V.w[r * V.W + i];
+    all += __popcll(w);
+    // representatives: the strings up to r
+    const int left = r + 1 - i * 64;
+    rep += left >= 64 ? __popcll(w) : left > 0 ? __popcll(w & ((1ull << left) - 1ull)) : 0;
+  }
+  all = wave_sum_int(all);
+  rep = wave_sum_int(rep);
+  if (lane == 0) {
+    cnt[r] = all;
+    cnt[V.n_str + r] = rep;
+  }
+}
+
+__global__ void __launch_bounds__(1024) hbci_row_scan_kernel(int n_str, int32_t* __restrict__ cnt, HbciCtl* ctl) {
+  __shared__ int sh[1024];
+  for (int half = 0; half < 2; ++half) {
+    int32_t* c = cnt + half * n_str;
+    const int per = (n_str + 1023) / 1024, lo = threadIdx.x * per, hi = lo + per < n_str ? lo + per : n_str;
+    int own = 0;
+    for (int i = lo; i < hi; ++i) own += c[i];
+    sh[threadIdx.x] = own;
+    __syncthreads();
+    for (int o = 1; o < 1024; o <<= 1) {
+      const int v = threadIdx.x >= (unsigned)o ? sh[threadIdx.x - o] : 0;
+      __syncthreads();
+      sh[threadIdx.x] += v;
+      __syncthreads();
+    }
+    int at = sh[threadIdx.x] - own;
+    for (int i = lo; i < hi; ++i) {
+      const int v = c[i];
+      c[i] = at;
+      at += v;
+    }
+    if (half && threadIdx.x == 1023) ctl->n_rep = (unsigned long long)sh[1023];
+    __syncthreads();
+  }
+}
+
+__global__ void __launch_bounds__(256) hbci_word_scan_kernel(Bits V, const int32_t* __restrict__ start) {
+  const int lane = threadIdx.x & 63;
+  const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (r >= V.n_str) return;
+  int base = start[r];
+  for (int i0 = 0; i0 < V.W; i0 += 64) {
+    const int i = i0 + lane;
+    const int own = i < V.W ? __popcll(V.w[r * V.W + i]) : 0;
+    int sum = own;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int v = __shfl_up(sum, o, 64);
+      if (lane >= o) sum += v;
+    }
+    if (i < V.W) V.pre[r * V.W + i] = base + sum - own;
+    base += __shfl(sum, 63, 64);
+  }
+}
+
+// Per determinant of V, by insertion: its place in key order and its flip
+// pair's number, now and (for those before lo) before the selection step.
+struct Order {
+  int32_t* place;   // by insertion
+  int32_t* pair;    // by insertion: flip pair's number
+  int32_t* moved;   // old place -> new place
+  int32_t* row_of;  // place -> flip pair's number; its complement for keys new in this step
+  double* diag_in;  // by insertion
+  // by flip pair, for its representative
+  uint64_t* key;
+  int32_t* pos;
+  int32_t* fpos;
+  int32_t* old;     // its number before the step, -1 for a new one
+  double* diag;
+};
+
+// The new order after a selection step, and x (in the old order) moved to it.
+__global__ void hbci_order_kernel(Bits V, int64_t lo, int64_t n, const int32_t* __restrict__ start, Order O,
+                                  const double* __restrict__ x_old, double* __restrict__ x) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
     const uint64_t key = V.dets[i];
-    if (ci == 0.0 || (half && !canonical(key))) continue;
-    const Det d = make_det(key, k, L, lane);
-    for (int t = lane; t < d.total; t += 64) {
+    const int ra = V.rank[(uint32_t)key], rb = V.rank[(uint32_t)(key >> 32)];
+    const int32_t p = place_of(V, ra, rb), f = place_of(V, rb, ra);
+    if (f < 0) {  // V is closed under the flip
+      atomicOr(&V.ctl->flags, kFlagNoPartner);
+      continue;
+    }
+    const int32_t q = rb <= ra ? start[V.n_str + ra] + (p - start[ra]) : start[V.n_str + rb] + (f - start[rb]);
+    const bool old = i < lo;
+    if (rb <= ra) {
+      O.key[q] = key;
+      O.pos[q] = p;
+      O.fpos[q] = f;
+      O.old[q] = old ? O.pair[i] : -1;
+      O.diag[q] = O.diag_in[i];
+    }
+    O.row_of[p] = old ? q : ~q;
+    if (old) O.moved[O.place[i]] = p;
+    x[p] = old ? x_old[O.place[i]] : 0.0;
+    O.place[i] = p;
+    O.pair[i] = q;
+  }
+}
+
+// c_out[i] = x at the place of key i
+__global__ void hbci_by_insertion_kernel(const int32_t* __restrict__ place, const double* __restrict__ x, int64_t n,
+                                         double* __restrict__ out) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+    out[i] = x[place[i]];
+}
+
+// One selection step: every replacement a of a determinant i < n_src with
+// |H_ai c_i| > eps joins V, with its flip partner.  src lists the sources and
+// pos the places of their c (null: in order); in the solve path, whose
+// vectors are flip-symmetric, only representatives are walked.
+//
+// Bound by the elements of H it forms; most determinants of a converged
+// vector can pass the threshold with few of their replacements or none, which
+// the bounds of make_screen show before any element is formed.
+template <typename VSpace>
+__global__ void __launch_bounds__(64 * kWaves, 8) hbci_select_kernel(const double* __restrict__ ints, int k,
+                                                                  const uint64_t* __restrict__ src,
+                                                                  const int32_t* __restrict__ pos,
+                                                                  const double* __restrict__ c, int64_t n_src,
+                                                                  double eps, VSpace V) {
+  const Lds s = load_lds<true>(ints, k);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint8_t* L = s.lists + wave * kListPairs;
+  for (int64_t i = (int64_t)blockIdx.x * kWaves + wave; i < n_src; i += (int64_t)gridDim.x * kWaves) {
+    const double ci = c[pos ? pos[i] : i];
+    if (ci == 0.0) continue;
+    const Det d = make_det(src[i], k, L, lane);
+    const Screen S = make_screen(d, s, ci, eps, L, lane);
+    const float inv_nb = 1.0f / (float)S.nb;
+    for (int t = lane; t < S.total; t += 64) {
       double v;
-      const uint64_t a = replacement<true>(d, t, s, k, &v);
+      const uint64_t a = screened(d, S, t, s, k, inv_nb, &v);
       if (fabs(v * ci) > eps) {
         add_det(V, a);
         if (flip_key(a) != a) add_det(V, flip_key(a));
@@ -470,35 +780,23 @@ __global__ void __launch_bounds__(64 * kWaves) hbci_select_kernel(const double* 
   }
 }
 
-// The diagonal (and, with partners, each key's flip partner) of rows lo..n-1.
-__global__ void __launch_bounds__(64 * kWaves) hbci_diag_kernel(const double* __restrict__ ints, int k, const Space V,
-                                                        int64_t lo, int64_t n, int partners, double* __restrict__ diag,
-                                                        int32_t* __restrict__ flip) {
+// The diagonal of rows lo..n-1.
+__global__ void __launch_bounds__(64 * kWaves) hbci_diag_kernel(const double* __restrict__ ints, int k,
+                                                                const uint64_t* __restrict__ dets, int64_t lo,
+                                                                int64_t n, double* __restrict__ diag) {
   const Lds s = load_lds(ints, k);
-  for (int64_t i = lo + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    const uint64_t key = V.dets[i];
-    diag[i] = diag_val(s, k, (uint32_t)key, (uint32_t)(key >> 32));
-    if (partners) {
-      const int32_t f = ht_find(V.keys, V.vals, V.mask, flip_key(key));
-      flip[i] = f;
-      if (f < 0) atomicOr(&V.ctl->flags, kFlagNoPartner);
-    }
-  }
+  for (int64_t i = lo + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+    diag[i] = diag_val(s, k, (uint32_t)dets[i], (uint32_t)(dets[i] >> 32));
 }
 
-// Nonzeros of each row of H over V (replacements that land in V).
+// Nonzeros of each row of H over a list of keys (replacements that land in it).
 __global__ void __launch_bounds__(64 * kWaves) hbci_count_kernel(const double* __restrict__ ints, int k, const Space V,
-                                                                 int64_t n, int half, int32_t* __restrict__ cnt) {
+                                                                 int64_t n, int32_t* __restrict__ cnt) {
   const Lds s = load_lds(ints, k);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint8_t* L = s.lists + wave * 64;
+  uint8_t* L = s.lists + wave * kListRanks;
   for (int64_t a = (int64_t)blockIdx.x * kWaves + wave; a < n; a += (int64_t)gridDim.x * kWaves) {
-    const uint64_t key = V.dets[a];
-    if (half && !canonical(key)) {
-      if (lane == 0) cnt[a] = 0;
-      continue;
-    }
-    const Det d = make_det(key, k, L, lane);
+    const Det d = make_det(V.dets[a], k, L, lane);
     int c = 0;
     for (int t = lane; t < d.total; t += 64) {
       double v;
@@ -560,16 +858,14 @@ __global__ void scan_add_kernel(int64_t* __restrict__ ptr, int64_t n, const int6
 
 // Column indices and values of each row, in replacement order.
 __global__ void __launch_bounds__(64 * kWaves) hbci_fill_kernel(const double* __restrict__ ints, int k, const Space V,
-                                                                int64_t n, int half, const int64_t* __restrict__ ptr,
+                                                                int64_t n, const int64_t* __restrict__ ptr,
                                                                 int32_t* __restrict__ col, double* __restrict__ val) {
   const Lds s = load_lds(ints, k);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint8_t* L = s.lists + wave * 64;
+  uint8_t* L = s.lists + wave * kListRanks;
   const uint64_t below = (1ull << lane) - 1ull;
   for (int64_t a = (int64_t)blockIdx.x * kWaves + wave; a < n; a += (int64_t)gridDim.x * kWaves) {
-    const uint64_t key = V.dets[a];
-    if (half && !canonical(key)) continue;
-    const Det d = make_det(key, k, L, lane);
+    const Det d = make_det(V.dets[a], k, L, lane);
     int64_t base = ptr[a];
     for (int t0 = 0; t0 < d.total; t0 += 64) {
       const int t = t0 + lane;
@@ -591,275 +887,295 @@ __global__ void __launch_bounds__(64 * kWaves) hbci_fill_kernel(const double* __
   }
 }
 
-// The rows of the determinants lo..n-1 added by a selection step, in a
-// space of representatives (flip-symmetric vectors): each such row is
-// counted from scratch, and each of its nonzeros (r, b) with b older than lo
-// also counts the entries it implies in the old rows, which H's symmetry and
-// its commuting with the flip fix: (b, r) when b is a representative, and
-// (flip b, flip r) when r is not flip-invariant and flip b is a
-// representative (for a flip-invariant r that entry is (flip b, r), reached
-// from r's own nonzero (r, flip b)).
-__global__ void __launch_bounds__(64 * kWaves) hbci_count_new_kernel(const double* __restrict__ ints, int k,
-                                                                     const Space V, int64_t lo, int64_t n,
-                                                                     const int32_t* __restrict__ flip,
+// Rows of H by flip pair: row q is that of the pair's representative, with
+// columns in the full space (places in key order).  After a selection step the
+// rows of the pairs it added are formed from scratch, and each of their
+// nonzeros (r, b) with b older also gives the entries that it implies in
+// the old rows, which H's symmetry and its commuting with the flip fix:
+// (b, r) when b is a representative, and (flip b, flip r) when r is not
+// flip-invariant and flip b is a representative (for a flip-invariant r that
+// entry is (flip b, r), reached from r's own nonzero (r, flip b)).
+//
+// Bound by the membership tests, 5792 for a row of a half-filled 16-orbital
+// space of which one in seven lands in V.  The ranks of a row's single
+// replacements are looked up once; an alpha-beta double, five of seven tests,
+// is then two LDS reads and one bit, whose words lie on few lines for one
+// replacement of the first string.  (Hash probes: count 1.35 ms and fill
+// 1.74 ms a step on average at 285020 keys.)
+__global__ void __launch_bounds__(64 * kWaves, 8) hbci_count_new_kernel(const double* __restrict__ ints, int k,
+                                                                     const Bits V, const Order O, int64_t n_rep,
                                                                      int32_t* __restrict__ cnt,
                                                                      int32_t* __restrict__ addc) {
   const Lds s = load_lds(ints, k);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint8_t* L = s.lists + wave * 64;
-  for (int64_t r = lo + (int64_t)blockIdx.x * kWaves + wave; r < n; r += (int64_t)gridDim.x * kWaves) {
-    const uint64_t key = V.dets[r];
-    if (!canonical(key)) {
-      if (lane == 0) cnt[r] = 0;
-      continue;
-    }
-    const bool self = flip_key(key) == key;
-    const Det d = make_det(key, k, L, lane);
+  uint8_t* L = s.lists + wave * kListRanks;
+  for (int64_t q = (int64_t)blockIdx.x * kWaves + wave; q < n_rep; q += (int64_t)gridDim.x * kWaves) {
+    if (O.old[q] >= 0) continue;
+    const Det d = make_det(O.key[q], k, L, lane);
+    const bool self = d.A == d.B;
+    const Ranks R = make_ranks(d, V.rank, L, lane);
+    const float inv_sb = 1.0f / (float)d.sb;
     int c = 0;
     for (int t = lane; t < d.total; t += 64) {
-      double v;
-      const int32_t j = ht_find(V.keys, V.vals, V.mask, replacement<false>(d, t, s, k, &v));
+      int ra, rb;
+      replaced_ranks(d, R, t, s, V.rank, inv_sb, &ra, &rb);
+      const int32_t j = place_of(V, ra, rb);
       if (j < 0) continue;
       ++c;
-      if (j < lo) {
-        const uint64_t kb = V.dets[j];
-        if (canonical(kb)) atomicAdd(addc + j, 1);
-        if (!self && canonical(flip_key(kb))) atomicAdd(addc + flip[j], 1);
+      const int32_t b = O.row_of[j];
+      if (b >= 0) {
+        const int add = (rb <= ra ? 1 : 0) + (!self && ra <= rb ? 1 : 0);
+        if (add) atomicAdd(addc + b, add);
       }
     }
     c = wave_sum_int(c);
-    if (lane == 0) cnt[r] = c;
+    if (lane == 0) cnt[q] = c;
   }
 }
 
-// cnt[a] = the old row's length plus its new entries, a < lo
-__global__ void hbci_rowlen_kernel(const int64_t* __restrict__ ptr_old, int64_t lo, const int32_t* __restrict__ addc,
-                                   int32_t* __restrict__ cnt) {
-  for (int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; a < lo; a += (int64_t)gridDim.x * blockDim.x)
-    cnt[a] = (int32_t)(ptr_old[a + 1] - ptr_old[a]) + addc[a];
-}
-
-// The old rows' entries to the front of their new rows (one wave per row).
-__global__ void __launch_bounds__(256) hbci_copy_rows_kernel(const int64_t* __restrict__ ptr_old,
-                                                             const int32_t* __restrict__ col_old,
-                                                             const double* __restrict__ val_old, int64_t lo,
-                                                             const int64_t* __restrict__ ptr_new,
-                                                             int32_t* __restrict__ col_new,
-                                                             double* __restrict__ val_new) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t nw = (int64_t)gridDim.x * (blockDim.x >> 6);
-  for (int64_t a = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave; a < lo; a += nw) {
-    const int64_t b = ptr_old[a], len = ptr_old[a + 1] - b, to = ptr_new[a];
-    for (int64_t e = lane; e < len; e += 64) {
-      col_new[to + e] = col_old[b + e];
-      val_new[to + e] = val_old[b + e];
-    }
+// cnt[q] = the old row's length plus its new entries, of the old pairs
+__global__ void hbci_rowlen_kernel(const int64_t* __restrict__ ptr_old, const int32_t* __restrict__ old, int64_t n_rep,
+                                   const int32_t* __restrict__ addc, int32_t* __restrict__ cnt) {
+  for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n_rep; q += (int64_t)gridDim.x * blockDim.x) {
+    const int32_t o = old[q];
+    if (o >= 0) cnt[q] = (int32_t)(ptr_old[o + 1] - ptr_old[o]) + addc[q];
   }
 }
 
 // The new rows in full (replacement order) and their implied entries in
-// the old rows, after the copied ones (in no fixed order).
-__global__ void __launch_bounds__(64 * kWaves) hbci_fill_new_kernel(const double* __restrict__ ints, int k,
-                                                                    const Space V, int64_t lo, int64_t n,
-                                                                    const int32_t* __restrict__ flip,
+// the old rows, after the place of those they have (in no fixed order).  The hits of a row
+// are gathered 64 at a time before their elements are formed, so that the
+// lanes that form them are full.
+__global__ void __launch_bounds__(64 * kWaves, 8) hbci_fill_new_kernel(const double* __restrict__ ints, int k,
+                                                                    const Bits V, const Order O, int64_t n_rep,
                                                                     const int64_t* __restrict__ ptr_old,
                                                                     const int64_t* __restrict__ ptr,
-                                                                    int32_t* __restrict__ pos, int32_t* __restrict__ col,
+                                                                    int32_t* __restrict__ used,
+                                                                    int32_t* __restrict__ col,
                                                                     double* __restrict__ val) {
   const Lds s = load_lds(ints, k);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint8_t* L = s.lists + wave * 64;
+  uint8_t* L = s.lists + wave * kListRanks;
   const uint64_t below = (1ull << lane) - 1ull;
-  for (int64_t r = lo + (int64_t)blockIdx.x * kWaves + wave; r < n; r += (int64_t)gridDim.x * kWaves) {
-    const uint64_t key = V.dets[r];
-    if (!canonical(key)) continue;
-    const bool self = flip_key(key) == key;
-    const int32_t fr = flip[r];
-    const Det d = make_det(key, k, L, lane);
-    int64_t base = ptr[r];
-    for (int t0 = 0; t0 < d.total; t0 += 64) {
-      const int t = t0 + lane;
-      int32_t j = -1;
-      double v = 0.0;
-      if (t < d.total) {
-        j = ht_find(V.keys, V.vals, V.mask, replacement<false>(d, t, s, k, &v));
-        if (j >= 0) replacement<true>(d, t, s, k, &v);
-      }
-      const uint64_t m = __ballot(j >= 0);
-      if (j >= 0) {
-        const int64_t at = base + __popcll(m & below);
-        col[at] = j;
-        val[at] = v;
-        if (j < lo) {
-          const uint64_t kb = V.dets[j];
-          if (canonical(kb)) {
-            const int64_t e = ptr[j] + (ptr_old[j + 1] - ptr_old[j]) + atomicAdd(pos + j, 1);
-            col[e] = (int32_t)r;
+  for (int64_t q = (int64_t)blockIdx.x * kWaves + wave; q < n_rep; q += (int64_t)gridDim.x * kWaves) {
+    if (O.old[q] >= 0) continue;
+    const Det d = make_det(O.key[q], k, L, lane);
+    const bool self = d.A == d.B;
+    const Ranks R = make_ranks(d, V.rank, L, lane);
+    const float inv_sb = 1.0f / (float)d.sb;
+    const int32_t r = O.pos[q], fr = O.fpos[q];
+    int64_t base = ptr[q];
+    // lane l holds gathered hit l: its replacement, place and order of ranks
+    int have = 0, gt = 0, gj = 0, gs = 0;
+    auto flush = [&](int m) {
+      if (lane < m) {
+        double v;
+        replacement<true>(d, gt, s, k, &v);
+        col[base + lane] = gj;
+        val[base + lane] = v;
+        const int32_t b = O.row_of[gj];
+        if (b >= 0) {
+          const int64_t at = ptr[b] + (ptr_old[O.old[b] + 1] - ptr_old[O.old[b]]);
+          if (gs >= 0) {
+            const int64_t e = at + atomicAdd(used + b, 1);
+            col[e] = r;
             val[e] = v;
           }
-          if (!self && canonical(flip_key(kb))) {
-            const int32_t f = flip[j];
-            const int64_t e = ptr[f] + (ptr_old[f + 1] - ptr_old[f]) + atomicAdd(pos + f, 1);
+          if (!self && gs <= 0) {
+            const int64_t e = at + atomicAdd(used + b, 1);
             col[e] = fr;
             val[e] = v;
           }
         }
       }
-      base += __popcll(m);
+      base += m;
+    };
+    for (int t0 = 0; t0 < d.total; t0 += 64) {
+      const int t = t0 + lane;
+      int32_t j = -1;
+      int ra = 0, rb = 0;
+      if (t < d.total) {
+        replaced_ranks(d, R, t, s, V.rank, inv_sb, &ra, &rb);
+        j = place_of(V, ra, rb);
+      }
+      const uint64_t m = __ballot(j >= 0);
+      const int hits = __popcll(m);
+      if (hits == 0) continue;
+      // hit h goes to lane (have + h) mod 64; where that wraps, the full set is written between.
+      // from: the lane that holds the hit for this lane, the src-th set bit of m
+      const int sg = ra > rb ? 1 : (ra < rb ? -1 : 0);
+      int from = -1, src = (lane - have) & 63;
+      if (src < hits) {
+        uint64_t mm = m;
+        from = 0;
+#pragma unroll
+        for (int w = 32; w > 0; w >>= 1) {
+          const int cnt = __popcll(mm & ((1ull << w) - 1ull));
+          if (src >= cnt) {
+            src -= cnt;
+            mm >>= w;
+            from += w;
+          }
+        }
+      }
+      const int st = __shfl(t, from & 63, 64), sj = __shfl(j, from & 63, 64), ss = __shfl(sg, from & 63, 64);
+      const bool early = from >= 0 && lane >= have;  // lands before the set is full
+      if (early) {
+        gt = st;
+        gj = sj;
+        gs = ss;
+      }
+      have += hits;
+      if (have >= 64) {
+        flush(64);
+        have -= 64;
+        if (from >= 0 && !early) {
+          gt = st;
+          gj = sj;
+          gs = ss;
+        }
+      }
     }
+    flush(have);
   }
 }
+
+// Each row's entries in order of their columns: what the step added is
+// sorted (bitonic, in LDS) and merged with the old row, whose columns keep
+// their order at the new places.  One workgroup per row of more than LO and at
+// most CAP entries.  Bound by reading and writing H once per step; in return
+// the products after it find the columns of 64 lanes on few lines.
+template <int NT, int LO, int CAP>
+__global__ void __launch_bounds__(NT) hbci_merge_rows_kernel(const int64_t* __restrict__ ptr_old,
+                                                             const int32_t* __restrict__ col_old,
+                                                             const double* __restrict__ val_old,
+                                                             const int32_t* __restrict__ old,
+                                                             const int32_t* __restrict__ moved, int64_t n_rep,
+                                                             const int64_t* __restrict__ ptr_new,
+                                                             int32_t* __restrict__ col_new,
+                                                             double* __restrict__ val_new) {
+  constexpr int kIndex = 13;  // bits of an entry's index, CAP <= 2^13
+  extern __shared__ __align__(16) unsigned char smem[];
+  uint64_t* key = (uint64_t*)smem;
+  int32_t* oc = (int32_t*)(key + CAP);
+  const int tid = threadIdx.x;
+  for (int64_t q = blockIdx.x; q < n_rep; q += gridDim.x) {
+    const int64_t to = ptr_new[q], len = ptr_new[q + 1] - to;
+    if (len <= LO || len > CAP) continue;
+    const int32_t o = old[q];
+    const int64_t b = o < 0 ? 0 : ptr_old[o];
+    const int no = o < 0 ? 0 : (int)(ptr_old[o + 1] - b), m = (int)len - no;
+    int P = 1;
+    while (P < m) P <<= 1;
+    for (int e = tid; e < no; e += NT) oc[e] = moved[col_old[b + e]];
+    for (int e = tid; e < P; e += NT) key[e] = e < m ? (uint64_t)col_new[to + no + e] << kIndex | (uint64_t)e : ~0ull;
+    for (int size = 2; size <= P; size <<= 1)
+      for (int half = size >> 1; half > 0; half >>= 1) {
+        __syncthreads();
+        for (int t = tid; t < P / 2; t += NT) {
+          const int i = 2 * t - (t & (half - 1)), j = i + half;
+          const uint64_t x = key[i], y = key[j];
+          if ((x > y) == ((i & size) == 0)) {
+            key[i] = y;
+            key[j] = x;
+          }
+        }
+      }
+    __syncthreads();
+    double v[CAP / NT];
+#pragma unroll
+    for (int r = 0; r < CAP / NT; ++r) {
+      const int e = tid + r * NT;
+      if (e < m) v[r] = val_new[to + no + (int)(key[e] & ((1u << kIndex) - 1u))];
+    }
+    __syncthreads();  // all values are read before any is written
+#pragma unroll
+    for (int r = 0; r < CAP / NT; ++r) {
+      const int e = tid + r * NT;
+      if (e < m) {
+        const int32_t c = (int32_t)(key[e] >> kIndex);
+        int lo = 0, hi = no;
+        while (lo < hi) {
+          const int mid = (lo + hi) >> 1;
+          if (oc[mid] < c)
+            lo = mid + 1;
+          else
+            hi = mid;
+        }
+        col_new[to + e + lo] = c;
+        val_new[to + e + lo] = v[r];
+      }
+    }
+    for (int e = tid; e < no; e += NT) {
+      const int32_t c = oc[e];
+      const uint64_t k = (uint64_t)c << kIndex;
+      int lo = 0, hi = m;
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (key[mid] < k)
+          lo = mid + 1;
+        else
+          hi = mid;
+      }
+      col_new[to + e + lo] = c;
+      val_new[to + e + lo] = val_old[b + e];
+    }
+    __syncthreads();
+  }
+}
+
+// Rows of up to kShortRow entries take 256 threads and 12 KB of LDS each, the
+// others (at most 5792 replacements at 16 orbitals) 1024 and 96 KB.
+constexpr int kShortRow = 1024, kLongRow = 8192;
 
 __global__ void fill_i32_kernel(int32_t* p, int64_t n, int32_t v) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = v;
 }
 
-// y = H x over V: the diagonal plus the CSR rows (one wave per row).  With
-// flip (flip-symmetric x, rows only for representatives) each row's value
-// is written to the row and to its partner.
+// y = H x over a list of keys: the diagonal plus the CSR rows (one wave per row).
 __global__ void __launch_bounds__(256) hbci_spmv_kernel(const int64_t* __restrict__ ptr, const int32_t* __restrict__ col,
                                                         const double* __restrict__ val, const double* __restrict__ diag,
-                                                        const uint64_t* __restrict__ dets,
-                                                        const int32_t* __restrict__ flip, const double* __restrict__ x,
-                                                        double* __restrict__ y, int64_t n) {
+                                                        const double* __restrict__ x, double* __restrict__ y,
+                                                        int64_t n) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t nw = (int64_t)gridDim.x * (blockDim.x >> 6);
   for (int64_t a = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave; a < n; a += nw) {
-    if (flip && !canonical(dets[a])) continue;
-    // four entries per lane in flight: their column and value loads, then
-    // the four gathers, are independent of each other
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-    const int64_t end = ptr[a + 1];
-    int64_t e = ptr[a] + lane;
-    for (; e + 192 < end; e += 256) {
-      const int32_t c0 = col[e], c1 = col[e + 64], c2 = col[e + 128], c3 = col[e + 192];
-      const double v0 = val[e], v1 = val[e + 64], v2 = val[e + 128], v3 = val[e + 192];
-      s0 += v0 * x[c0];
-      s1 += v1 * x[c1];
-      s2 += v2 * x[c2];
-      s3 += v3 * x[c3];
-    }
-    for (; e < end; e += 64) s0 += val[e] * x[col[e]];
-    double s = wave_sum((s0 + s1) + (s2 + s3));
-    if (lane == 0) {
-      const double ya = s + diag[a] * x[a];
-      y[a] = ya;
-      if (flip) y[flip[a]] = ya;
-    }
-  }
-}
-
-// part[j][block] = partial of B_j . v, j < m
-// part[row0 + j][block] = partial of B_j . v, j < m; with self, row
-// row0 + m holds the partial of v . v
-__global__ void __launch_bounds__(256) hbci_dots_kernel(const double* __restrict__ B, int64_t ld, int m,
-                                                        const double* __restrict__ v, int64_t n,
-                                                        double* __restrict__ part, int row0, int self) {
-  __shared__ double red[4];
-  for (int j = 0; j < m + self; ++j) {
-    const double* b = j < m ? B + j * ld : v;
     double s = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-      s += b[i] * v[i];
-    s = group_sum(s, red);
-    if (threadIdx.x == 0) part[(row0 + j) * kNB + blockIdx.x] = s;
-  }
-}
-
-// x = sum_j y_j V_j, w = sum_j y_j S_j, r = w - theta x; part = partial |r|^2
-__global__ void __launch_bounds__(256) hbci_ritz_kernel(const double* __restrict__ Vb, const double* __restrict__ Sb,
-                                                        int64_t ld, int m, Coef y, double theta, double* __restrict__ x,
-                                                        double* __restrict__ w, double* __restrict__ r, int64_t n,
-                                                        double* __restrict__ part) {
-  __shared__ double red[4];
-  double s = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    double xi = 0.0, wi = 0.0;
-    for (int j = 0; j < m; ++j) {
-      xi += y.v[j] * Vb[j * ld + i];
-      wi += y.v[j] * Sb[j * ld + i];
-    }
-    const double ri = wi - theta * xi;
-    x[i] = xi;
-    w[i] = wi;
-    r[i] = ri;
-    s += ri * ri;
-  }
-  s = group_sum(s, red);
-  if (threadIdx.x == 0) part[blockIdx.x] = s;
-}
-
-// t = the flip-symmetric part of (theta - D)^-1 r
-__global__ void hbci_precond_kernel(const double* __restrict__ r, const double* __restrict__ diag,
-                                    const int32_t* __restrict__ flip, double theta, double* __restrict__ t, int64_t n) {
-  auto q = [&](int64_t i) {
-    double den = theta - diag[i];
-    if (fabs(den) < 1e-10) den = den < 0.0 ? -1e-10 : 1e-10;
-    return r[i] / den;
-  };
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    t[i] = 0.5 * (q(i) + q(flip[i]));
-}
-
-// t -= sum_j d_j V_j; part = partial |t|^2
-__global__ void __launch_bounds__(256) hbci_orth_kernel(const double* __restrict__ Vb, int64_t ld, int m, Coef d,
-                                                        double* __restrict__ t, int64_t n, double* __restrict__ part) {
-  __shared__ double red[4];
-  double s = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    double ti = t[i];
-    for (int j = 0; j < m; ++j) ti -= d.v[j] * Vb[j * ld + i];
-    t[i] = ti;
-    s += ti * ti;
-  }
-  s = group_sum(s, red);
-  if (threadIdx.x == 0) part[blockIdx.x] = s;
-}
-
-__global__ void hbci_scale_kernel(const double* __restrict__ in, double f, double* __restrict__ out, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    out[i] = f * in[i];
-}
-
-// out_j = sum_l Y[l][j] B_l, j < keep (the kept Ritz vectors of a restart)
-__global__ void __launch_bounds__(256) hbci_combo_kernel(const double* __restrict__ B, int64_t ld, int m, CoefKeep Y,
-                                                         int keep, double* __restrict__ out, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    double b[kMaxM];
-    for (int l = 0; l < m; ++l) b[l] = B[l * ld + i];
-    for (int j = 0; j < keep; ++j) {
-      double a = 0.0;
-      for (int l = 0; l < m; ++l) a += Y.v[l][j] * b[l];
-      out[j * ld + i] = a;
-    }
+    for (int64_t e = ptr[a] + lane; e < ptr[a + 1]; e += 64) s += val[e] * x[col[e]];
+    s = wave_sum(s);
+    if (lane == 0) y[a] = s + diag[a] * x[a];
   }
 }
 
 // N_a += H_ai c_i for every replacement a outside V with |H_ai c_i| > eps.
-// With half (flip-symmetric c, flip-closed V) only representatives i are
-// walked and N is kept for representatives b only: the term (i, b) of a
+// With half (flip-symmetric c, flip-closed V) src lists the representatives
+// i, at places pos of c, and N is kept for representatives b only: the term (i, b) of a
 // non-representative i equals (flip i, flip b), so a representative i adds
 // each term to its target's representative (twice for a flip-invariant
 // target, which i and flip(i) both reach); a flip-invariant i (a closed
 // shell, whose replacements come in flip pairs) adds only the terms whose
 // target is a representative.
-__global__ void __launch_bounds__(64 * kWaves) hbci_pt2_kernel(const double* __restrict__ ints, int k, const Space V,
+template <typename VSpace>
+__global__ void __launch_bounds__(64 * kWaves, 8) hbci_pt2_kernel(const double* __restrict__ ints, int k, const VSpace V,
+                                                               const uint64_t* __restrict__ src,
+                                                               const int32_t* __restrict__ pos,
                                                                const double* __restrict__ c, int64_t n, double eps,
                                                                int half, ExtSlot* __restrict__ et,
                                                                int64_t* __restrict__ elist, uint64_t emask,
                                                                int64_t ecap) {
-  const Lds s = load_lds(ints, k);
+  const Lds s = load_lds<true>(ints, k);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint8_t* L = s.lists + wave * 64;
+  uint8_t* L = s.lists + wave * kListPairs;
   for (int64_t i = (int64_t)blockIdx.x * kWaves + wave; i < n; i += (int64_t)gridDim.x * kWaves) {
-    const double ci = c[i];
-    const uint64_t key = V.dets[i];
-    if (ci == 0.0 || (half && !canonical(key))) continue;
-    const bool self = flip_key(key) == key;
-    const Det d = make_det(key, k, L, lane);
-    for (int t = lane; t < d.total; t += 64) {
+    const double ci = c[pos ? pos[i] : i];
+    if (ci == 0.0) continue;
+    const Det d = make_det(src[i], k, L, lane);
+    const bool self = d.A == d.B;
+    const Screen S = make_screen(d, s, ci, eps, L, lane);
+    const float inv_nb = 1.0f / (float)S.nb;
+    for (int t = lane; t < S.total; t += 64) {
       double v;
-      uint64_t a = replacement<true>(d, t, s, k, &v);
+      uint64_t a = screened(d, S, t, s, k, inv_nb, &v);
       const double hc = v * ci;
       if (!(fabs(hc) > eps)) continue;
       double w = 1.0;
@@ -871,9 +1187,22 @@ __global__ void __launch_bounds__(64 * kWaves) hbci_pt2_kernel(const double* __r
           w = 2.0;  // i and flip(i) reach the flip-invariant a with equal terms
         }
       }
-      if (ht_find(V.keys, V.vals, V.mask, a) < 0) ext_add(et, elist, emask, ecap, a, w * hc, V.ctl);
+      if (!has_det(V, a)) ext_add(et, elist, emask, ecap, a, w * hc, V.ctl);
     }
   }
+}
+
+// Sum over the workgroup; the result in thread 0.
+__device__ __forceinline__ double group_sum(double v, double* red) {
+  v = wave_sum(v);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  __syncthreads();
+  if (lane == 0) red[wave] = v;
+  __syncthreads();
+  double s = 0.0;
+  if (threadIdx.x == 0)
+    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) s += red[w];
+  return s;
 }
 
 // part[block] = partial sum of N_a^2 / (e - H_aa); part[kNB + block] = count
@@ -902,213 +1231,6 @@ __global__ void __launch_bounds__(64 * kWaves) hbci_e2_kernel(const double* __re
   if (threadIdx.x == 0) part[kNB + blockIdx.x] = cnt;
 }
 
-// ------------------------------------- Davidson of a small space in one workgroup
-
-// Spaces of up to kSmallDav determinants solve their Davidson in a single
-// launch of one 1024-thread workgroup: the same iteration as the host-driven
-// form (thick restart, flip-symmetric diagonal preconditioner, classical
-// Gram-Schmidt twice), with the small eigenproblem on one wavefront (the
-// one-wave parallel Jacobi) and every reduction in LDS, so a step costs one
-// launch and one read-back instead of several per iteration.  The
-// increments of an expansion run on concurrent streams, one CU each.
-constexpr int64_t kSmallDav = 1024;
-constexpr int kSmallThreads = 1024;
-
-struct SmallDav {
-  const int64_t* ptr;
-  const int32_t* col;
-  const double* val;
-  const double* diag;
-  const uint64_t* dets;
-  const int32_t* flip;
-  double* x;
-  double* Vb;
-  double* Sb;
-  double* r;
-  int64_t ld, n;
-  int m_max, max_dav, half;
-  double r_tol;
-  double* out;  // theta, residual norm, converged (0/1), iterations
-};
-
-__device__ void small_spmv(const SmallDav& a, const double* __restrict__ xin, double* __restrict__ y) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  for (int64_t row = wave; row < a.n; row += nw) {
-    if (a.half && !canonical(a.dets[row])) continue;
-    double s = 0.0;
-    for (int64_t e = a.ptr[row] + lane; e < a.ptr[row + 1]; e += 64) s += a.val[e] * xin[a.col[e]];
-    s = wave_sum(s);
-    if (lane == 0) {
-      const double ya = s + a.diag[row] * xin[row];
-      y[row] = ya;
-      if (a.half) y[a.flip[row]] = ya;
-    }
-  }
-  __syncthreads();
-}
-
-// res[j] = sum over the workgroup of v[j], j < nv (v per thread, nv <= 17)
-__device__ __forceinline__ void small_sums(const double (&v)[kMaxM + 1], int nv, double* red, double* res) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-#pragma unroll
-  for (int j = 0; j < kMaxM + 1; ++j)
-    if (j < nv) {
-      const double t = wave_sum(v[j]);
-      if (lane == 0) red[wave * (kMaxM + 1) + j] = t;
-    }
-  __syncthreads();
-  if ((int)threadIdx.x < nv) {
-    double t = 0.0;
-    for (int w = 0; w < nw; ++w) t += red[w * (kMaxM + 1) + threadIdx.x];
-    res[threadIdx.x] = t;
-  }
-  __syncthreads();
-}
-
-__global__ void __launch_bounds__(kSmallThreads) hbci_dav_small_kernel(SmallDav a) {
-  __shared__ double Hs[256], A[256], Q[256], ev[16], yv[16], th[1];
-  __shared__ double red[(kSmallThreads / 64) * (kMaxM + 1)], res[kMaxM + 1];
-  __shared__ int perm[16];
-  const int tid = threadIdx.x, nt = blockDim.x;
-  const int64_t n = a.n, ld = a.ld;
-  double* Vb = a.Vb;
-  double* Sb = a.Sb;
-  for (int64_t i = tid; i < n; i += nt) Vb[i] = a.x[i];
-  for (int t = tid; t < 256; t += nt) Hs[t] = 0.0;
-  __syncthreads();
-  small_spmv(a, Vb, Sb);
-  {
-    double v[kMaxM + 1] = {};
-    for (int64_t i = tid; i < n; i += nt) v[0] += Vb[i] * Sb[i];
-    small_sums(v, 1, red, res);
-  }
-  if (tid == 0) Hs[0] = res[0];
-  __syncthreads();
-  int m = 1, conv = 0, it = 0;
-  double theta = res[0], rn = 1e300;
-  // Ritz pair of the current basis: x, r = H x - theta x, |r|
-  auto ritz = [&]() {
-    if (tid < 64) {
-      for (int t = tid; t < 256; t += 64) A[t] = Hs[t];
-      jacobi_lowest(A, Q, m, th, yv, ev, perm);
-    }
-    __syncthreads();
-    theta = th[0];
-    double v[kMaxM + 1] = {};
-    for (int64_t i = tid; i < n; i += nt) {
-      double xi = 0.0, wi = 0.0;
-      for (int j = 0; j < m; ++j) {
-        xi += yv[j] * Vb[j * ld + i];
-        wi += yv[j] * Sb[j * ld + i];
-      }
-      const double ri = wi - theta * xi;
-      a.x[i] = xi;
-      a.r[i] = ri;
-      v[0] += ri * ri;
-    }
-    small_sums(v, 1, red, res);
-    rn = sqrt(res[0]);
-  };
-  for (it = 0; it < a.max_dav; ++it) {
-    ritz();
-    if (rn <= a.r_tol) {
-      conv = 1;
-      break;
-    }
-    if (m == a.m_max) {  // thick restart, in place: each thread owns its entries of every vector
-      const int keep = a.m_max / 2 < kKeepRitz ? a.m_max / 2 : kKeepRitz;
-      for (int64_t i = tid; i < n; i += nt) {
-        double bv[kMaxM], bs[kMaxM];
-        for (int l = 0; l < kMaxM; ++l)
-          if (l < m) {
-            bv[l] = Vb[l * ld + i];
-            bs[l] = Sb[l * ld + i];
-          }
-        for (int j = 0; j < keep; ++j) {
-          double cv = 0.0, cs = 0.0;
-          for (int l = 0; l < kMaxM; ++l)
-            if (l < m) {
-              const double q = Q[l * 16 + perm[j]];
-              cv += q * bv[l];
-              cs += q * bs[l];
-            }
-          Vb[j * ld + i] = cv;
-          Sb[j * ld + i] = cs;
-        }
-      }
-      __syncthreads();
-      if (tid < 256) Hs[tid] = ((tid >> 4) == (tid & 15) && (tid & 15) < keep) ? ev[tid & 15] : 0.0;
-      __syncthreads();
-      m = keep;
-    }
-    // the correction, flip-symmetrised, into the next basis slot
-    double* T = Vb + m * ld;
-    for (int64_t i = tid; i < n; i += nt) {
-      double d1 = theta - a.diag[i];
-      if (fabs(d1) < 1e-10) d1 = d1 < 0.0 ? -1e-10 : 1e-10;
-      const int64_t f = a.flip[i];
-      double d2 = theta - a.diag[f];
-      if (fabs(d2) < 1e-10) d2 = d2 < 0.0 ? -1e-10 : 1e-10;
-      T[i] = 0.5 * (a.r[i] / d1 + a.r[f] / d2);
-    }
-    double t2 = 0.0;
-    for (int pass = 0; pass < 2; ++pass) {
-      double v[kMaxM + 1] = {};
-      for (int64_t i = tid; i < n; i += nt) {
-        const double ti = T[i];
-#pragma unroll
-        for (int j = 0; j < kMaxM; ++j)
-          if (j < m) v[j] += Vb[j * ld + i] * ti;
-      }
-      small_sums(v, m, red, res);
-      double w[kMaxM + 1] = {};
-      for (int64_t i = tid; i < n; i += nt) {
-        double ti = T[i];
-        for (int j = 0; j < m; ++j) ti -= res[j] * Vb[j * ld + i];
-        T[i] = ti;
-        w[0] += ti * ti;
-      }
-      if (pass == 1) {
-        small_sums(w, 1, red, res);
-        t2 = res[0];
-      } else {
-        __syncthreads();
-      }
-    }
-    if (!(t2 > 1e-28)) break;  // the space is exhausted
-    const double inv = 1.0 / sqrt(t2);
-    for (int64_t i = tid; i < n; i += nt) T[i] *= inv;
-    __syncthreads();
-    small_spmv(a, T, Sb + m * ld);
-    {
-      double v[kMaxM + 1] = {};
-      for (int64_t i = tid; i < n; i += nt) {
-        const double si = Sb[m * ld + i];
-#pragma unroll
-        for (int j = 0; j < kMaxM + 1; ++j)
-          if (j <= m) v[j] += Vb[j * ld + i] * si;
-      }
-      small_sums(v, m + 1, red, res);
-    }
-    if (tid <= m) {
-      Hs[tid * 16 + m] = res[tid];
-      Hs[m * 16 + tid] = res[tid];
-    }
-    __syncthreads();
-    ++m;
-  }
-  if (!conv) {  // ended on the iteration limit or an exhausted space: the Ritz pair of the basis
-    ritz();
-    conv = rn <= a.r_tol ? 1 : 0;
-  }
-  if (tid == 0) {
-    a.out[0] = theta;
-    a.out[1] = rn;
-    a.out[2] = conv;
-    a.out[3] = it;
-  }
-}
-
 // ---------------------------------------------------------------- host side
 
 int64_t align256(int64_t x) { return (x + 255) & ~(int64_t)255; }
@@ -1120,8 +1242,9 @@ uint64_t pow2_at_least(int64_t x) {
 }
 
 struct Layout {
-  int64_t ints, ctl, part, bsum, dets, keys, vals, flip, diag, cnt, addc, pos, ptr[2], col[2], val[2], basis, sig, x, w,
-      r, t, keep, ext, elist;
+  int64_t ints, ctl, dav, part, bsum, dets, keys, vals, diag, cnt, addc, used, ptr[2], col[2], val[2], basis, sig, x[2],
+      ext, elist;
+  int64_t rank, bits, pre, start, place, pair, moved, row_of, key, pos, fpos, old, rdiag;
   int64_t bytes;
   uint64_t tcap, ecap;
 };
@@ -1137,18 +1260,29 @@ Layout layout(int k, const ifci_hbci_options& o) {
   const int64_t D = o.max_det;
   L.tcap = pow2_at_least(2 * D);
   L.ecap = pow2_at_least(2 * o.max_ext);
-  L.ints = take((int64_t)(k * k + packed_count(k)) * 8);
+  L.ints = take((int64_t)ints_count(k) * 8);
   L.ctl = take(sizeof(HbciCtl));
+  L.dav = take(sizeof(DavCtl));
   L.part = take((int64_t)kNB * kParts * 8);
   L.bsum = take(((D + 1023) / 1024 + 1) * 8);
   L.dets = take(D * 8);
   L.keys = take((int64_t)L.tcap * 8);
   L.vals = take((int64_t)L.tcap * 4);
-  L.flip = take(D * 4);
   L.diag = take(D * 8);
   L.cnt = take(D * 4);
   L.addc = take(D * 4);
-  L.pos = take(D * 4);
+  L.used = take(D * 4);
+  // the bits of the widest space of k orbitals (half filled)
+  int64_t strings = 1;
+  for (int i = 0; i < k / 2; ++i) strings = strings * (k - i) / (i + 1);
+  const int64_t words = strings * ((strings + 63) / 64);
+  L.rank = take(((int64_t)1 << k) * 2);
+  L.bits = take(words * 8);
+  L.pre = take(words * 4);
+  L.start = take(strings * 2 * 4);
+  for (int64_t* at : {&L.place, &L.pair, &L.moved, &L.row_of, &L.pos, &L.fpos, &L.old}) *at = take(D * 4);
+  L.key = take(D * 8);
+  L.rdiag = take(D * 8);
   // two CSR buffers: a selection step builds the new H from the old one
   for (int b = 0; b < 2; ++b) {
     L.ptr[b] = take((D + 1) * 8);
@@ -1157,76 +1291,11 @@ Layout layout(int k, const ifci_hbci_options& o) {
   }
   L.basis = take((int64_t)o.m_max * D * 8);
   L.sig = take((int64_t)o.m_max * D * 8);
-  L.x = take(D * 8);
-  L.w = take(D * 8);
-  L.r = take(D * 8);
-  L.t = take(D * 8);
-  L.keep = take((int64_t)2 * kKeepRitz * D * 8);
+  for (int b = 0; b < 2; ++b) L.x[b] = take(D * 8);
   L.ext = take((int64_t)L.ecap * (int64_t)sizeof(ExtSlot));
   L.elist = take(o.max_ext * 8);
   L.bytes = off;
   return L;
-}
-
-// Eigenpairs of the symmetric m x m matrix A (cyclic Jacobi), ascending:
-// evals[j] with the unit eigenvector in column j of Y.
-void sym_eigen(const double (&A0)[kMaxM][kMaxM], int m, double* evals, double (&Y)[kMaxM][kMaxM]) {
-  double A[kMaxM][kMaxM], Q[kMaxM][kMaxM];
-  for (int i = 0; i < m; ++i)
-    for (int j = 0; j < m; ++j) {
-      A[i][j] = A0[i][j];
-      Q[i][j] = i == j ? 1.0 : 0.0;
-    }
-  for (int sweep = 0; sweep < 64; ++sweep) {
-    double off = 0.0, tot = 0.0;
-    for (int i = 0; i < m; ++i)
-      for (int j = 0; j < m; ++j) {
-        tot += A[i][j] * A[i][j];
-        if (i != j) off += A[i][j] * A[i][j];
-      }
-    if (off <= 1e-30 * tot) break;
-    for (int p = 0; p < m - 1; ++p)
-      for (int q = p + 1; q < m; ++q) {
-        if (A[p][q] == 0.0) continue;
-        const double tau = (A[q][q] - A[p][p]) / (2.0 * A[p][q]);
-        const double t = (tau >= 0 ? 1.0 : -1.0) / (std::fabs(tau) + std::sqrt(1.0 + tau * tau));
-        const double c = 1.0 / std::sqrt(1.0 + t * t), s = t * c;
-        for (int r = 0; r < m; ++r) {
-          const double arp = A[r][p], arq = A[r][q];
-          A[r][p] = c * arp - s * arq;
-          A[r][q] = s * arp + c * arq;
-        }
-        for (int r = 0; r < m; ++r) {
-          const double apr = A[p][r], aqr = A[q][r];
-          A[p][r] = c * apr - s * aqr;
-          A[q][r] = s * apr + c * aqr;
-        }
-        for (int r = 0; r < m; ++r) {
-          const double qrp = Q[r][p], qrq = Q[r][q];
-          Q[r][p] = c * qrp - s * qrq;
-          Q[r][q] = s * qrp + c * qrq;
-        }
-      }
-  }
-  int idx[kMaxM];
-  for (int i = 0; i < m; ++i) idx[i] = i;
-  for (int i = 1; i < m; ++i)  // insertion sort by eigenvalue
-    for (int j = i; j > 0 && A[idx[j]][idx[j]] < A[idx[j - 1]][idx[j - 1]]; --j) std::swap(idx[j], idx[j - 1]);
-  for (int j = 0; j < m; ++j) {
-    const int c = idx[j];
-    evals[j] = A[c][c];
-    double nrm = 0.0;
-    for (int i = 0; i < m; ++i) nrm += Q[i][c] * Q[i][c];
-    nrm = std::sqrt(nrm);
-    for (int i = 0; i < m; ++i) Y[i][j] = Q[i][c] / nrm;
-  }
-}
-
-void lowest_eigen(const double (&A)[kMaxM][kMaxM], int m, double* theta, double* y) {
-  double ev[kMaxM], Y[kMaxM][kMaxM];
-  sym_eigen(A, m, ev, Y);
-  *theta = ev[0];
-  for (int i = 0; i < m; ++i) y[i] = Y[i][0];
 }
 
 // Pinned host staging for read-backs, one per host thread.
@@ -1244,18 +1313,31 @@ struct Run {
   hipStream_t st;
   double* pin = nullptr;
   HbciCtl ctl{};
-  int lds = 0;
-  int half = 0;  // flip-symmetric vectors over a flip-closed space: walk representatives only
   int cur = 0;   // the CSR buffer that holds H
+  int curx = 0;  // the buffer that holds x
 
   template <typename T>
   T* at(int64_t off) const {
     return (T*)(w + off);
   }
-  Space space() const {
+  Space list() const {
     return Space{at<uint64_t>(L.dets), at<uint64_t>(L.keys), at<int32_t>(L.vals), L.tcap - 1, o.max_det,
                  at<HbciCtl>(L.ctl)};
   }
+  Bits bits() const {
+    const int na = __builtin_popcount((uint32_t)I.ref);
+    int64_t n = 1;
+    for (int i = 0; i < na; ++i) n = n * (I.k - i) / (i + 1);
+    return Bits{at<uint64_t>(L.bits), at<int32_t>(L.pre), at<uint16_t>(L.rank), (int)((n + 63) / 64), (int)n,
+                at<uint64_t>(L.dets), o.max_det, at<HbciCtl>(L.ctl)};
+  }
+  Order order() const {
+    return Order{at<int32_t>(L.place), at<int32_t>(L.pair), at<int32_t>(L.moved), at<int32_t>(L.row_of),
+                 at<double>(L.diag), at<uint64_t>(L.key), at<int32_t>(L.pos), at<int32_t>(L.fpos), at<int32_t>(L.old),
+                 at<double>(L.rdiag)};
+  }
+  double* x() const { return at<double>(L.x[curx]); }
+  int lds(int list, bool screen) const { return lds_bytes_for(I.k, list, screen); }
   static int blocks(int64_t n, int per, int cap) {
     const int64_t b = (n + per - 1) / per;
     return (int)(b < 1 ? 1 : (b > cap ? cap : b));
@@ -1283,44 +1365,76 @@ struct Run {
   hipError_t prepare() {
     pin = staging();
     if (!pin) return hipErrorOutOfMemory;
-    lds = lds_bytes_for(I.k);
     hipError_t e = hipSuccess;
-    for (const void* fn : {(const void*)hbci_select_kernel, (const void*)hbci_diag_kernel,
-                           (const void*)hbci_count_kernel, (const void*)hbci_fill_kernel, (const void*)hbci_pt2_kernel,
+    for (const void* fn : {(const void*)hbci_select_kernel<Space>, (const void*)hbci_select_kernel<Bits>,
+                           (const void*)hbci_diag_kernel, (const void*)hbci_count_kernel, (const void*)hbci_fill_kernel,
+                           (const void*)hbci_pt2_kernel<Space>, (const void*)hbci_pt2_kernel<Bits>,
                            (const void*)hbci_count_new_kernel, (const void*)hbci_fill_new_kernel,
-                           (const void*)hbci_e2_kernel})
+                           (const void*)hbci_e2_kernel,
+                           (const void*)hbci_merge_rows_kernel<1024, kShortRow, kLongRow>})
       if (e == hipSuccess) e = allow_max_lds(fn);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(hbci_prep_kernel, dim3(1), dim3(256), 0, st, I.h, I.eri, I.n_orb, I.act, I.k, I.core,
                        I.n_core, I.e_core, at<double>(L.ints), at<HbciCtl>(L.ctl));
+    return hipGetLastError();
+  }
+
+  // V := the caller's list; ctl read
+  hipError_t load(const uint64_t* dets, int64_t n) {
     hipLaunchKernelGGL(fill_u64_kernel, dim3(blocks((int64_t)L.tcap, 256, 4096)), dim3(256), 0, st,
                        at<uint64_t>(L.keys), (int64_t)L.tcap, kEmpty);
+    hipLaunchKernelGGL(hbci_load_kernel, dim3(blocks(n, 256, 4096)), dim3(256), 0, st, dets, n, list());
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? read_ctl() : e;
+  }
+
+  // V := the reference; ctl read
+  hipError_t load_reference() {
+    const Bits V = bits();
+    const int64_t words = (int64_t)V.n_str * V.W;
+    hipLaunchKernelGGL(hbci_rank_kernel, dim3(blocks((int64_t)1 << I.k, 256, 256)), dim3(256), 0, st, I.k,
+                       __builtin_popcount((uint32_t)I.ref), at<uint16_t>(L.rank));
+    hipLaunchKernelGGL(fill_u64_kernel, dim3(blocks(words, 256, 4096)), dim3(256), 0, st, V.w, words, (uint64_t)0);
+    hipLaunchKernelGGL(hbci_ref_kernel, dim3(1), dim3(1), 0, st, I.ref, V);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? read_ctl() : e;
+  }
+
+  hipError_t diag(int64_t lo, int64_t n) {
+    if (n <= lo) return hipSuccess;
+    hipLaunchKernelGGL(hbci_diag_kernel, dim3(blocks(n - lo, 64 * kWaves, 2048)), dim3(64 * kWaves),
+                       lds(kListRanks, false), st, at<double>(L.ints), I.k, at<uint64_t>(L.dets), lo, n,
+                       at<double>(L.diag));
+    return hipGetLastError();
+  }
+
+  // The places of the n keys after a step that added those from lo on, with
+  // the diagonal and x brought to them; ctl read
+  hipError_t reorder(int64_t lo, int64_t n) {
+    hipError_t e = diag(lo, n);
+    if (e != hipSuccess) return e;
+    const Bits V = bits();
+    int32_t* start = at<int32_t>(L.start);
+    const int rows = (V.n_str + 3) / 4;
+    hipLaunchKernelGGL(hbci_row_count_kernel, dim3(rows), dim3(256), 0, st, V, start);
+    hipLaunchKernelGGL(hbci_row_scan_kernel, dim3(1), dim3(1024), 0, st, V.n_str, start, at<HbciCtl>(L.ctl));
+    hipLaunchKernelGGL(hbci_word_scan_kernel, dim3(rows), dim3(256), 0, st, V, start);
+    hipLaunchKernelGGL(hbci_order_kernel, dim3(blocks(n, 256, 4096)), dim3(256), 0, st, V, lo, n, start, order(),
+                       at<double>(L.x[curx]), at<double>(L.x[curx ^ 1]));
+    curx ^= 1;
     e = hipGetLastError();
     if (e == hipSuccess) e = read_ctl();
     return e;
   }
 
-  hipError_t load(const uint64_t* dets, int64_t n) {
-    hipLaunchKernelGGL(hbci_load_kernel, dim3(dets ? blocks(n, 256, 4096) : 1), dim3(256), 0, st, dets, n, I.ref,
-                       space());
-    return hipGetLastError();
-  }
-
-  hipError_t diag(int64_t lo, int64_t n, bool partners) {
-    if (n <= lo) return hipSuccess;
-    hipLaunchKernelGGL(hbci_diag_kernel, dim3(blocks(n - lo, 64 * kWaves, 2048)), dim3(64 * kWaves), lds, st, at<double>(L.ints), I.k,
-                       space(), lo, n, partners ? 1 : 0, at<double>(L.diag), at<int32_t>(L.flip));
-    return hipGetLastError();
-  }
-
-  // CSR of H over the n keys; IFCI_ERR_OOM past max_nnz
+  // CSR of H over the n keys of a list; IFCI_ERR_OOM past max_nnz
   ifci_status build_h(int64_t n, hipError_t* he) {
-    hipLaunchKernelGGL(hbci_count_kernel, dim3(blocks(n, kWaves, 8192)), dim3(64 * kWaves), lds, st,
-                       at<double>(L.ints), I.k, space(), n, half, at<int32_t>(L.cnt));
+    hipLaunchKernelGGL(hbci_count_kernel, dim3(blocks(n, kWaves, 8192)), dim3(64 * kWaves), lds(kListRanks, false), st,
+                       at<double>(L.ints), I.k, list(), n, at<int32_t>(L.cnt));
     ifci_status s = scan_rows(n, L.ptr[cur], he);
     if (s != IFCI_OK) return s;
-    hipLaunchKernelGGL(hbci_fill_kernel, dim3(blocks(n, kWaves, 8192)), dim3(64 * kWaves), lds, st,
-                       at<double>(L.ints), I.k, space(), n, half, at<int64_t>(L.ptr[cur]), at<int32_t>(L.col[cur]),
+    hipLaunchKernelGGL(hbci_fill_kernel, dim3(blocks(n, kWaves, 8192)), dim3(64 * kWaves), lds(kListRanks, false), st,
+                       at<double>(L.ints), I.k, list(), n, at<int64_t>(L.ptr[cur]), at<int32_t>(L.col[cur]),
                        at<double>(L.val[cur]));
     *he = hipGetLastError();
     return *he == hipSuccess ? IFCI_OK : IFCI_ERR_DEVICE;
@@ -1344,58 +1458,77 @@ struct Run {
     return IFCI_OK;
   }
 
-  // H over n keys from H over the first lo (representative rows, flip
-  // partners known): the new rows from scratch, the old ones copied and
-  // extended by the entries the new rows imply; the result in the other
-  // buffer, which becomes current.
-  ifci_status extend_h(int64_t lo, int64_t n, hipError_t* he) {
+  // H over the n_rep pairs of the new order from H before the step (none at
+  // first): the new rows from scratch, the old ones copied and extended by
+  // the entries the new rows imply; the result in the other buffer, which
+  // becomes current.
+  ifci_status extend_h(int64_t n_rep, hipError_t* he) {
     const int nxt = cur ^ 1;
-    hipLaunchKernelGGL(fill_i32_kernel, dim3(blocks(lo, 256, 4096)), dim3(256), 0, st, at<int32_t>(L.addc), lo, 0);
-    hipLaunchKernelGGL(fill_i32_kernel, dim3(blocks(lo, 256, 4096)), dim3(256), 0, st, at<int32_t>(L.pos), lo, 0);
-    hipLaunchKernelGGL(hbci_count_new_kernel, dim3(blocks(n - lo, kWaves, 8192)), dim3(64 * kWaves), lds, st,
-                       at<double>(L.ints), I.k, space(), lo, n, at<int32_t>(L.flip), at<int32_t>(L.cnt),
-                       at<int32_t>(L.addc));
-    hipLaunchKernelGGL(hbci_rowlen_kernel, dim3(blocks(lo, 256, 4096)), dim3(256), 0, st, at<int64_t>(L.ptr[cur]), lo,
+    const Bits V = bits();
+    const Order O = order();
+    const int gb = blocks(n_rep, 256, 4096), gw = blocks(n_rep, kWaves, 8192);
+    hipLaunchKernelGGL(fill_i32_kernel, dim3(gb), dim3(256), 0, st, at<int32_t>(L.addc), n_rep, 0);
+    hipLaunchKernelGGL(fill_i32_kernel, dim3(gb), dim3(256), 0, st, at<int32_t>(L.used), n_rep, 0);
+    hipLaunchKernelGGL(hbci_count_new_kernel, dim3(gw), dim3(64 * kWaves), lds(kListRanks, false), st,
+                       at<double>(L.ints), I.k, V, O, n_rep, at<int32_t>(L.cnt), at<int32_t>(L.addc));
+    hipLaunchKernelGGL(hbci_rowlen_kernel, dim3(gb), dim3(256), 0, st, at<int64_t>(L.ptr[cur]), O.old, n_rep,
                        at<int32_t>(L.addc), at<int32_t>(L.cnt));
-    ifci_status s = scan_rows(n, L.ptr[nxt], he);
+    ifci_status s = scan_rows(n_rep, L.ptr[nxt], he);
     if (s != IFCI_OK) return s;
-    hipLaunchKernelGGL(hbci_copy_rows_kernel, dim3(blocks(lo, 4, 8192)), dim3(256), 0, st, at<int64_t>(L.ptr[cur]),
-                       at<int32_t>(L.col[cur]), at<double>(L.val[cur]), lo, at<int64_t>(L.ptr[nxt]),
-                       at<int32_t>(L.col[nxt]), at<double>(L.val[nxt]));
-    hipLaunchKernelGGL(hbci_fill_new_kernel, dim3(blocks(n - lo, kWaves, 8192)), dim3(64 * kWaves), lds, st,
-                       at<double>(L.ints), I.k, space(), lo, n, at<int32_t>(L.flip), at<int64_t>(L.ptr[cur]),
-                       at<int64_t>(L.ptr[nxt]), at<int32_t>(L.pos), at<int32_t>(L.col[nxt]), at<double>(L.val[nxt]));
+    hipLaunchKernelGGL(hbci_fill_new_kernel, dim3(gw), dim3(64 * kWaves), lds(kListRanks, false), st,
+                       at<double>(L.ints), I.k, V, O, n_rep, at<int64_t>(L.ptr[cur]), at<int64_t>(L.ptr[nxt]),
+                       at<int32_t>(L.used), at<int32_t>(L.col[nxt]), at<double>(L.val[nxt]));
+    const int na = __builtin_popcount((uint32_t)I.ref), s1 = na * (I.k - na);
+    const int longest = s1 * (s1 + 2) + na * (na - 1) / 2 * (I.k - na) * (I.k - na - 1);
+    hipLaunchKernelGGL((hbci_merge_rows_kernel<256, 0, kShortRow>), dim3(blocks(n_rep, 1, 8192)), dim3(256),
+                       kShortRow * 12, st, at<int64_t>(L.ptr[cur]), at<int32_t>(L.col[cur]), at<double>(L.val[cur]),
+                       O.old, O.moved, n_rep, at<int64_t>(L.ptr[nxt]), at<int32_t>(L.col[nxt]),
+                       at<double>(L.val[nxt]));
+    if (longest > kShortRow)
+      hipLaunchKernelGGL((hbci_merge_rows_kernel<1024, kShortRow, kLongRow>), dim3(blocks(n_rep, 1, 8192)), dim3(1024),
+                         kLongRow * 12, st, at<int64_t>(L.ptr[cur]), at<int32_t>(L.col[cur]), at<double>(L.val[cur]),
+                         O.old, O.moved, n_rep, at<int64_t>(L.ptr[nxt]), at<int32_t>(L.col[nxt]),
+                         at<double>(L.val[nxt]));
     *he = hipGetLastError();
     if (*he != hipSuccess) return IFCI_ERR_DEVICE;
     cur = nxt;
     return IFCI_OK;
   }
 
-  hipError_t spmv(const double* x, double* y, int64_t n) {
-    hipLaunchKernelGGL(hbci_spmv_kernel, dim3(blocks(n, 4, 8192)), dim3(256), 0, st, at<int64_t>(L.ptr[cur]),
-                       at<int32_t>(L.col[cur]), at<double>(L.val[cur]), at<double>(L.diag), at<uint64_t>(L.dets),
-                       half ? at<int32_t>(L.flip) : nullptr, x, y, n);
-    return hipGetLastError();
+  template <int M>
+  void dav_step(const DavSpace& a, int m, bool check_only) {
+    const dim3 g(blocks(a.n, 256, kVecBlocks)), b(256);
+    hipLaunchKernelGGL(hbci_dav_residual_kernel<M>, g, b, 0, st, a, m, o.r_tol);
+    if (check_only) return;
+    hipLaunchKernelGGL((hbci_dav_orth_kernel<M, false>), g, b, 0, st, a, m);
+    hipLaunchKernelGGL((hbci_dav_orth_kernel<M, true>), g, b, 0, st, a, m);
+  }
+  void dav_step(const DavSpace& a, int m, bool check_only) {
+    if (m <= 4) dav_step<4>(a, m, check_only);
+    else if (m <= 8) dav_step<8>(a, m, check_only);
+    else if (m <= 12) dav_step<12>(a, m, check_only);
+    else dav_step<16>(a, m, check_only);
+  }
+  void dav_product(const DavSpace& a, int m) {
+    const int nb = blocks(a.n, 16, kRowBlocks);
+    hipLaunchKernelGGL(hbci_dav_product_kernel, dim3(nb), dim3(1024), 0, st, a, m);
+    hipLaunchKernelGGL(hbci_dav_subspace_kernel, dim3(1), dim3(256), 0, st, a, nb, m, o.m_max);
   }
 
-  hipError_t dots(const double* B, int m, const double* v, int64_t n, double* out) {
-    hipLaunchKernelGGL(hbci_dots_kernel, dim3(kNB), dim3(256), 0, st, B, o.max_det, m, v, n, at<double>(L.part), 0,
-                       0);
-    hipError_t e = hipGetLastError();
-    return e == hipSuccess ? read_parts(m, out) : e;
-  }
-
-  // Davidson for the lowest root over the n keys from the unit,
-  // flip-symmetric start vector in x; the Ritz vector is left in x.
-  hipError_t davidson(int64_t n, double* theta_out, double* res_out, bool* conv) {
+  // Davidson for the lowest root over the n keys (n_rep pairs) from the unit,
+  // flip-symmetric start vector in x; the Ritz vector is left in x.  The
+  // steps are queued kBatch at a time between two looks at their state; those
+  // after the last one do nothing.
+  hipError_t davidson(int64_t n, int64_t n_rep, double* theta_out, double* res_out, bool* conv) {
+    constexpr int kBatch = 4;
+    const DavSpace a{at<int64_t>(L.ptr[cur]), at<int32_t>(L.col[cur]), at<double>(L.val[cur]), at<double>(L.rdiag),
+                     at<int32_t>(L.pos), at<int32_t>(L.fpos), x(), at<double>(L.basis), at<double>(L.sig),
+                     at<double>(L.part), at<DavCtl>(L.dav), o.max_det, n_rep};
     if (n <= kSmallDav) {
-      SmallDav a{at<int64_t>(L.ptr[cur]), at<int32_t>(L.col[cur]), at<double>(L.val[cur]), at<double>(L.diag),
-                 at<uint64_t>(L.dets), at<int32_t>(L.flip), at<double>(L.x), at<double>(L.basis),
-                 at<double>(L.sig), at<double>(L.r), o.max_det, n, o.m_max, o.max_dav, half, o.r_tol,
-                 at<double>(L.part)};
-      hipLaunchKernelGGL(hbci_dav_small_kernel, dim3(1), dim3(kSmallThreads), 0, st, a);
+      const SmallDav s{a, o.m_max, o.max_dav, o.r_tol, at<double>(L.part)};
+      hipLaunchKernelGGL(hbci_dav_small_kernel, dim3(1), dim3(kSmallThreads), 0, st, s);
       hipError_t e = hipGetLastError();
-      if (e == hipSuccess) e = hipMemcpyAsync(pin, a.out, 4 * sizeof(double), hipMemcpyDeviceToHost, st);
+      if (e == hipSuccess) e = hipMemcpyAsync(pin, s.out, 3 * sizeof(double), hipMemcpyDeviceToHost, st);
       if (e == hipSuccess) e = hipStreamSynchronize(st);
       if (e != hipSuccess) return e;
       *theta_out = pin[0];
@@ -1403,134 +1536,74 @@ struct Run {
       *conv = pin[2] != 0.0;
       return hipSuccess;
     }
-    double* Vb = at<double>(L.basis);
-    double* Sb = at<double>(L.sig);
-    double* x = at<double>(L.x);
-    double* w = at<double>(L.w);
-    double* r = at<double>(L.r);
-    double* t = at<double>(L.t);
-    const int64_t ld = o.max_det;
-    const int gb = blocks(n, 256, kNB);
-    double Hs[kMaxM][kMaxM] = {};
-    double hv[kMaxM];
-    hipError_t e = hipSuccess;
-    hipLaunchKernelGGL(hbci_scale_kernel, dim3(gb), dim3(256), 0, st, x, 1.0, Vb, n);
-    if ((e = spmv(Vb, Sb, n)) != hipSuccess) return e;
-    if ((e = dots(Vb, 1, Sb, n, hv)) != hipSuccess) return e;
-    Hs[0][0] = hv[0];
-    int m = 1;
-    double theta = hv[0], rn = INFINITY;
-    *conv = false;
-    // Per iteration three read-backs: the residual norm with the first
-    // Gram-Schmidt overlaps (the correction is formed before the
-    // convergence test is known, and dropped if it passes), the second
-    // overlaps with the correction's norm (|t - V d|^2 = |t|^2 - |d|^2 for an
-    // orthonormal V), and the new column of the subspace matrix.
-    double* part = at<double>(L.part);
-    double rd[kParts];
-    for (int it = 0; it < o.max_dav; ++it) {
-      Coef y{};
-      lowest_eigen(Hs, m, &theta, y.v);
-      hipLaunchKernelGGL(hbci_ritz_kernel, dim3(kNB), dim3(256), 0, st, Vb, Sb, ld, m, y, theta, x, w, r, n, part);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-      if (m == o.m_max) {
-        double r2;
-        if ((e = read_parts(1, &r2)) != hipSuccess) return e;
-        rn = std::sqrt(r2);
-        if (rn <= o.r_tol) {
-          *conv = true;
-          break;
+    const auto look = [&](int* done) {
+      hipError_t e = hipGetLastError();
+      if (e == hipSuccess) e = hipMemcpyAsync(pin, a.ctl, 3 * sizeof(double), hipMemcpyDeviceToHost, st);
+      if (e == hipSuccess) e = hipStreamSynchronize(st);
+      if (e != hipSuccess) return e;
+      *theta_out = pin[0];
+      *res_out = pin[1];
+      std::memcpy(done, pin + 2, sizeof(int));
+      return hipSuccess;
+    };
+    hipLaunchKernelGGL(hbci_dav_start_kernel, dim3(blocks(n_rep, 256, 1 << 30)), dim3(256), 0, st, a);
+    dav_product(a, 0);
+    int m = 1, done = 0;
+    for (int it = 0; it < o.max_dav && !done;) {
+      for (int b = 0; b < kBatch && it < o.max_dav; ++b, ++it) {
+        dav_step(a, m, false);
+        dav_product(a, m);
+        if (++m == o.m_max) {
+          const dim3 g(blocks(n_rep, 256, kVecBlocks)), t(256);
+          const int keep = kept_ritz(m);
+          if (m <= 12)
+            hipLaunchKernelGGL(hbci_dav_restart_kernel<12>, g, t, 0, st, a, m, keep);
+          else
+            hipLaunchKernelGGL(hbci_dav_restart_kernel<16>, g, t, 0, st, a, m, keep);
+          m = keep;
         }
-        // thick restart: the lowest Ritz vectors and their sigmas
-        const int keep = std::min(kKeepRitz, o.m_max / 2);
-        double ev[kMaxM], Y[kMaxM][kMaxM];
-        sym_eigen(Hs, m, ev, Y);
-        CoefKeep K{};
-        for (int l = 0; l < m; ++l)
-          for (int j = 0; j < keep; ++j) K.v[l][j] = Y[l][j];
-        double* kv = at<double>(L.keep);
-        double* ks = kv + (int64_t)kKeepRitz * ld;
-        hipLaunchKernelGGL(hbci_combo_kernel, dim3(gb), dim3(256), 0, st, Vb, ld, m, K, keep, kv, n);
-        hipLaunchKernelGGL(hbci_combo_kernel, dim3(gb), dim3(256), 0, st, Sb, ld, m, K, keep, ks, n);
-        for (int j = 0; j < keep; ++j) {
-          hipLaunchKernelGGL(hbci_scale_kernel, dim3(gb), dim3(256), 0, st, kv + j * ld, 1.0, Vb + j * ld, n);
-          hipLaunchKernelGGL(hbci_scale_kernel, dim3(gb), dim3(256), 0, st, ks + j * ld, 1.0, Sb + j * ld, n);
-        }
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        for (int i = 0; i < kMaxM; ++i)
-          for (int j = 0; j < kMaxM; ++j) Hs[i][j] = 0.0;
-        for (int j = 0; j < keep; ++j) Hs[j][j] = ev[j];
-        m = keep;
       }
-      hipLaunchKernelGGL(hbci_precond_kernel, dim3(gb), dim3(256), 0, st, r, at<double>(L.diag),
-                         at<int32_t>(L.flip), theta, t, n);
-      hipLaunchKernelGGL(hbci_dots_kernel, dim3(kNB), dim3(256), 0, st, Vb, ld, m, t, n, part, 1, 0);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-      if ((e = read_parts(m + 1, rd)) != hipSuccess) return e;  // row 0: |r|^2 of this Ritz pair
-      rn = std::sqrt(rd[0]);
-      if (rn <= o.r_tol) {
-        *conv = true;
-        break;
-      }
-      Coef d{};
-      for (int j = 0; j < m; ++j) d.v[j] = rd[j + 1];
-      hipLaunchKernelGGL(hbci_orth_kernel, dim3(kNB), dim3(256), 0, st, Vb, ld, m, d, t, n, part);
-      hipLaunchKernelGGL(hbci_dots_kernel, dim3(kNB), dim3(256), 0, st, Vb, ld, m, t, n, part, 0, 1);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-      if ((e = read_parts(m + 1, rd)) != hipSuccess) return e;
-      Coef d2{};
-      double dd = 0.0;
-      for (int j = 0; j < m; ++j) {
-        d2.v[j] = rd[j];
-        dd += rd[j] * rd[j];
-      }
-      const double tt = rd[m];
-      hipLaunchKernelGGL(hbci_orth_kernel, dim3(kNB), dim3(256), 0, st, Vb, ld, m, d2, t, n, part);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-      double t2 = tt - dd;
-      if (!(t2 > 1e-6 * tt)) {  // cancellation: the norm as summed by the second pass
-        if ((e = read_parts(1, &t2)) != hipSuccess) return e;
-      }
-      if (!(t2 > 1e-28)) break;  // the space is exhausted
-      hipLaunchKernelGGL(hbci_scale_kernel, dim3(gb), dim3(256), 0, st, t, 1.0 / std::sqrt(t2), Vb + m * ld, n);
-      if ((e = spmv(Vb + m * ld, Sb + m * ld, n)) != hipSuccess) return e;
-      if ((e = dots(Vb, m + 1, Sb + m * ld, n, hv)) != hipSuccess) return e;
-      for (int j = 0; j <= m; ++j) Hs[j][m] = Hs[m][j] = hv[j];
-      ++m;
+      const hipError_t e = look(&done);
+      if (e != hipSuccess) return e;
     }
-    if (!*conv && m >= 1) {
-      // the loop ended without a final Ritz step: refresh x from the basis
-      Coef y{};
-      lowest_eigen(Hs, m, &theta, y.v);
-      hipLaunchKernelGGL(hbci_ritz_kernel, dim3(kNB), dim3(256), 0, st, Vb, Sb, ld, m, y, theta, x, w, r, n,
-                         at<double>(L.part));
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-      double r2;
-      if ((e = read_parts(1, &r2)) != hipSuccess) return e;
-      rn = std::sqrt(r2);
-      *conv = rn <= o.r_tol;
+    if (!done) {  // out of steps: the residual of the last Ritz pair
+      dav_step(a, m, true);
+      const hipError_t e = look(&done);
+      if (e != hipSuccess) return e;
     }
-    *theta_out = theta;
-    *res_out = rn;
-    return hipSuccess;
+    *conv = done == 1;
+    hipLaunchKernelGGL(hbci_dav_vector_kernel, dim3(blocks(n_rep, 256, kVecBlocks)), dim3(256), 0, st, a);
+    return hipGetLastError();
   }
 
-  hipError_t pt2(int64_t n, const double* c, double e_act, double eps2, double* e2, int64_t* n_ext) {
+  // PT2 over the n keys (src, at places pos of c), V a list or the bits
+  template <typename VSpace>
+  hipError_t pt2(const VSpace& V, const uint64_t* src, const int32_t* pos, int64_t n, const double* c, double e_act,
+                 double eps2, bool half, double* e2, int64_t* n_ext) {
     hipLaunchKernelGGL(fill_slots_kernel, dim3(blocks((int64_t)L.ecap, 256, 4096)), dim3(256), 0, st,
                        at<ExtSlot>(L.ext), (int64_t)L.ecap);
-    hipLaunchKernelGGL(hbci_pt2_kernel, dim3(blocks(n, kWaves, 8192)), dim3(64 * kWaves), lds, st,
-                       at<double>(L.ints), I.k, space(), c, n, eps2, half, at<ExtSlot>(L.ext),
-                       at<int64_t>(L.elist), L.ecap - 1, o.max_ext);
-    hipLaunchKernelGGL(hbci_e2_kernel, dim3(kNB), dim3(64 * kWaves), lds, st, at<double>(L.ints), I.k,
-                       at<ExtSlot>(L.ext), at<int64_t>(L.elist), o.max_ext, at<HbciCtl>(L.ctl), e_act, half,
-                       at<double>(L.part));
+    hipLaunchKernelGGL(hbci_pt2_kernel<VSpace>, dim3(blocks(n, kWaves, 8192)), dim3(64 * kWaves),
+                       lds(kListPairs, true), st, at<double>(L.ints), I.k, V, src, pos, c, n, eps2, half ? 1 : 0,
+                       at<ExtSlot>(L.ext), at<int64_t>(L.elist), L.ecap - 1, o.max_ext);
+    hipLaunchKernelGGL(hbci_e2_kernel, dim3(kNB), dim3(64 * kWaves), lds(kListRanks, false), st, at<double>(L.ints),
+                       I.k, at<ExtSlot>(L.ext), at<int64_t>(L.elist), o.max_ext, at<HbciCtl>(L.ctl), e_act,
+                       half ? 1 : 0, at<double>(L.part));
     hipError_t e = hipGetLastError();
     double s[2];
     if (e == hipSuccess) e = read_parts(2, s);
     if (e == hipSuccess) e = read_ctl();
+    if (e != hipSuccess) return e;
     *e2 = s[0];
     *n_ext = (int64_t)std::llround(s[1]);
     return e;
+  }
+
+  template <typename VSpace>
+  hipError_t select(const VSpace& V, const uint64_t* src, const int32_t* pos, int64_t n, const double* c, double eps) {
+    hipLaunchKernelGGL(hbci_select_kernel<VSpace>, dim3(blocks(n, kWaves, 8192)), dim3(64 * kWaves),
+                       lds(kListPairs, true), st, at<double>(L.ints), I.k, src, pos, c, n, eps, V);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? read_ctl() : e;
   }
 };
 
@@ -1560,38 +1633,40 @@ int64_t hbci_work_bytes(int k, const ifci_hbci_options& o) { return layout(k, o)
 ifci_status hbci_solve(const HbciInc& I, const ifci_hbci_options& o, void* work, double* result, uint64_t* dets_out,
                        double* c_out, hipStream_t st) {
   Run R{I, o, layout(I.k, o), (char*)work, st};
-  R.half = 1;
   HB_TRY(R.prepare(), "hbci prepare");
+  HB_TRY(R.load_reference(), "hbci load");
   const double shift = R.ctl.e_core + I.e_const;
-  HB_TRY(R.load(nullptr, 0), "hbci load");
-  HB_TRY(R.read_ctl(), "hbci load");
-  int64_t n = (int64_t)R.ctl.n_det;
+  int64_t n = (int64_t)R.ctl.n_det, n_rep = 0;
   if (R.ctl.flags) return capacity_failure(R.ctl.flags);
-  HB_TRY(R.diag(0, n, true), "hbci diagonal");
-  // V = {reference}: c = 1 (over the reference and, for an open shell, the
-  // normalised symmetric pair), E = its diagonal
-  double* x = R.at<double>(R.L.x);
-  hipLaunchKernelGGL(fill_f64_kernel, dim3(1), dim3(64), 0, st, x, n, 1.0 / std::sqrt((double)n));
-  HB_TRY(hipGetLastError(), "hbci start");
+  const Bits V = R.bits();
+  const Order O = R.order();
   double theta = 0.0, res = 0.0;
   bool all_conv = true;
-  {
+  // the places of V's keys after those from lo on were added, H over them and its lowest root
+  auto solve = [&](int64_t lo, bool first) -> ifci_status {
+    HB_TRY(R.reorder(lo, n), "hbci order");
+    if (R.ctl.flags) return capacity_failure(R.ctl.flags);
+    n_rep = (int64_t)R.ctl.n_rep;
+    if (first) {  // V = {reference}: c = 1
+      hipLaunchKernelGGL(fill_f64_kernel, dim3(1), dim3(64), 0, st, R.x(), n, 1.0);
+      HB_TRY(hipGetLastError(), "hbci start");
+    }
     hipError_t he;
-    ifci_status s = R.build_h(n, &he);
+    const ifci_status s = R.extend_h(n_rep, &he);
     if (s == IFCI_ERR_DEVICE) return device_failure(he, "hbci H");
     if (s != IFCI_OK) return s;
     bool cv;
-    HB_TRY(R.davidson(n, &theta, &res, &cv), "hbci davidson");
+    HB_TRY(R.davidson(n, n_rep, &theta, &res, &cv), "hbci davidson");
     all_conv = all_conv && cv;
-  }
+    return IFCI_OK;
+  };
+  ifci_status s = solve(0, true);
+  if (s != IFCI_OK) return s;
   int steps = 0;
   bool fixed = false;
   while (steps < o.max_iter) {
     const int64_t n_old = n;
-    hipLaunchKernelGGL(hbci_select_kernel, dim3(Run::blocks(n_old, kWaves, 8192)), dim3(64 * kWaves), R.lds, st,
-                       R.at<double>(R.L.ints), I.k, x, n_old, o.eps1, R.space(), R.half);
-    HB_TRY(hipGetLastError(), "hbci select");
-    HB_TRY(R.read_ctl(), "hbci select");
+    HB_TRY(R.select(V, O.key, O.pos, n_rep, R.x(), o.eps1), "hbci select");
     ++steps;
     if (R.ctl.flags) return capacity_failure(R.ctl.flags);
     n = (int64_t)R.ctl.n_det;
@@ -1599,26 +1674,18 @@ ifci_status hbci_solve(const HbciInc& I, const ifci_hbci_options& o, void* work,
       fixed = true;
       break;
     }
-    HB_TRY(R.diag(n_old, n, true), "hbci diagonal");
-    hipLaunchKernelGGL(fill_f64_kernel, dim3(Run::blocks(n - n_old, 256, 4096)), dim3(256), 0, st, x + n_old,
-                       n - n_old, 0.0);
-    HB_TRY(hipGetLastError(), "hbci start");
-    hipError_t he;
-    ifci_status s = R.extend_h(n_old, n, &he);
-    if (s == IFCI_ERR_DEVICE) return device_failure(he, "hbci H");
-    if (s != IFCI_OK) return s;
-    bool cv;
-    HB_TRY(R.davidson(n, &theta, &res, &cv), "hbci davidson");
-    all_conv = all_conv && cv;
-    HB_TRY(R.read_ctl(), "hbci davidson");
-    if (R.ctl.flags) return capacity_failure(R.ctl.flags);
+    if ((s = solve(n_old, false)) != IFCI_OK) return s;
   }
   double e2 = 0.0;
   int64_t n_ext = 0;
-  HB_TRY(R.pt2(n, x, theta, o.eps2, &e2, &n_ext), "hbci pt2");
+  HB_TRY(R.pt2(V, O.key, O.pos, n_rep, R.x(), theta, o.eps2, true, &e2, &n_ext), "hbci pt2");
   if (R.ctl.flags) return capacity_failure(R.ctl.flags);
   if (dets_out) HB_TRY(hipMemcpyAsync(dets_out, R.at<uint64_t>(R.L.dets), n * 8, hipMemcpyDeviceToDevice, st), "copy");
-  if (c_out) HB_TRY(hipMemcpyAsync(c_out, x, n * 8, hipMemcpyDeviceToDevice, st), "copy");
+  if (c_out) {
+    hipLaunchKernelGGL(hbci_by_insertion_kernel, dim3(Run::blocks(n, 256, 4096)), dim3(256), 0, st, O.place, R.x(), n,
+                       c_out);
+    HB_TRY(hipGetLastError(), "hbci");
+  }
   HB_TRY(hipStreamSynchronize(st), "hbci");
   result[0] = theta + shift;
   result[1] = e2;
@@ -1636,14 +1703,15 @@ ifci_status hbci_sigma(const HbciInc& I, const ifci_hbci_options& o, void* work,
   Run R{I, o, layout(I.k, o), (char*)work, st};
   HB_TRY(R.prepare(), "hbci prepare");
   HB_TRY(R.load(dets, n), "hbci load");
-  HB_TRY(R.read_ctl(), "hbci load");
   if (R.ctl.flags) return capacity_failure(R.ctl.flags);
-  HB_TRY(R.diag(0, n, false), "hbci diagonal");
+  HB_TRY(R.diag(0, n), "hbci diagonal");
   hipError_t he;
   ifci_status s = R.build_h(n, &he);
   if (s == IFCI_ERR_DEVICE) return device_failure(he, "hbci H");
   if (s != IFCI_OK) return s;
-  HB_TRY(R.spmv(c, sigma, n), "hbci sigma");
+  hipLaunchKernelGGL(hbci_spmv_kernel, dim3(Run::blocks(n, 4, 8192)), dim3(256), 0, st, R.at<int64_t>(R.L.ptr[R.cur]),
+                     R.at<int32_t>(R.L.col[R.cur]), R.at<double>(R.L.val[R.cur]), R.at<double>(R.L.diag), c, sigma, n);
+  HB_TRY(hipGetLastError(), "hbci sigma");
   HB_TRY(hipStreamSynchronize(st), "hbci sigma");
   return IFCI_OK;
 }
@@ -1653,12 +1721,8 @@ ifci_status hbci_select(const HbciInc& I, const ifci_hbci_options& o, void* work
   Run R{I, o, layout(I.k, o), (char*)work, st};
   HB_TRY(R.prepare(), "hbci prepare");
   HB_TRY(R.load(dets, n), "hbci load");
-  HB_TRY(R.read_ctl(), "hbci load");
   if (R.ctl.flags) return capacity_failure(R.ctl.flags);
-  hipLaunchKernelGGL(hbci_select_kernel, dim3(Run::blocks(n, kWaves, 8192)), dim3(64 * kWaves), R.lds, st,
-                     R.at<double>(R.L.ints), I.k, c, n, eps1, R.space(), 0);
-  HB_TRY(hipGetLastError(), "hbci select");
-  HB_TRY(R.read_ctl(), "hbci select");
+  HB_TRY(R.select(R.list(), R.at<uint64_t>(R.L.dets), nullptr, n, c, eps1), "hbci select");
   if (R.ctl.flags) return capacity_failure(R.ctl.flags);
   const int64_t m = (int64_t)R.ctl.n_det - n;
   if (m > 0)
@@ -1673,10 +1737,10 @@ ifci_status hbci_pt2(const HbciInc& I, const ifci_hbci_options& o, void* work, c
   Run R{I, o, layout(I.k, o), (char*)work, st};
   HB_TRY(R.prepare(), "hbci prepare");
   HB_TRY(R.load(dets, n), "hbci load");
-  HB_TRY(R.read_ctl(), "hbci load");
   if (R.ctl.flags) return capacity_failure(R.ctl.flags);
   const double shift = R.ctl.e_core + I.e_const;
-  HB_TRY(R.pt2(n, c, e_var - shift, eps2, e_pt2, n_ext), "hbci pt2");
+  HB_TRY(R.pt2(R.list(), R.at<uint64_t>(R.L.dets), nullptr, n, c, e_var - shift, eps2, false, e_pt2, n_ext),
+         "hbci pt2");
   if (R.ctl.flags) return capacity_failure(R.ctl.flags);
   return IFCI_OK;
 }
