@@ -1244,7 +1244,7 @@ uint64_t pow2_at_least(int64_t x) {
 struct Layout {
   int64_t ints, ctl, dav, part, bsum, dets, keys, vals, diag, cnt, addc, used, ptr[2], col[2], val[2], basis, sig, x[2],
       ext, elist;
-  int64_t rank, bits, pre, start, place, pair, moved, row_of, key, pos, fpos, old, rdiag;
+  int64_t bound, off, bptr, rank, bits, pre, start, place, pair, moved, row_of, key, pos, fpos, old, rdiag;
   int64_t bytes;
   uint64_t tcap, ecap;
 };
@@ -1276,6 +1276,11 @@ Layout layout(int k, const ifci_hbci_options& o) {
   int64_t strings = 1;
   for (int i = 0; i < k / 2; ++i) strings = strings * (k - i) / (i + 1);
   const int64_t words = strings * ((strings + 63) / 64);
+  // of spaces in blocked form
+  const int64_t bd = D < kBlockMax ? D : kBlockMax, bw = (bd + kWin - 1) / kWin;
+  L.bound = take((kShares + 1) * 4);
+  L.off = take((bw + 1) * (bd < kBlockMaxRows ? bd : kBlockMaxRows) * 2);
+  L.bptr = take((kShares * bw + 1) * 8);
   L.rank = take(((int64_t)1 << k) * 2);
   L.bits = take(words * 8);
   L.pre = take(words * 4);
@@ -1370,7 +1375,7 @@ struct Run {
                            (const void*)hbci_diag_kernel, (const void*)hbci_count_kernel, (const void*)hbci_fill_kernel,
                            (const void*)hbci_pt2_kernel<Space>, (const void*)hbci_pt2_kernel<Bits>,
                            (const void*)hbci_count_new_kernel, (const void*)hbci_fill_new_kernel,
-                           (const void*)hbci_e2_kernel,
+                           (const void*)hbci_e2_kernel, (const void*)hbci_dav_block_kernel, (const void*)hbci_block_fill_kernel,
                            (const void*)hbci_merge_rows_kernel<1024, kShortRow, kLongRow>})
       if (e == hipSuccess) e = allow_max_lds(fn);
     if (e != hipSuccess) return e;
@@ -1509,9 +1514,28 @@ struct Run {
     else if (m <= 12) dav_step<12>(a, m, check_only);
     else dav_step<16>(a, m, check_only);
   }
+  static bool blocked(const DavSpace& a) {
+    return a.n_full > kBlockMin && a.n_full <= kBlockMax && a.n <= kBlockMaxRows;
+  }
+  // the blocked form of H, in the CSR buffer that the next step builds its H in
+  void block_h(const DavSpace& a) {
+    const int nwin = (int)((a.n_full + kWin - 1) / kWin);
+    int32_t* bound = at<int32_t>(L.bound);
+    uint16_t* off = at<uint16_t>(L.off);
+    int64_t* bptr = at<int64_t>(L.bptr);
+    hipLaunchKernelGGL(hbci_share_kernel, dim3(1), dim3(512), 0, st, a.ptr, a.n, bound);
+    hipLaunchKernelGGL(hbci_win_offsets_kernel, dim3(blocks(a.n, 4, 8192)), dim3(256), 0, st, a.ptr, a.col, a.n, nwin,
+                       off);
+    hipLaunchKernelGGL(hbci_block_ptr_kernel, dim3(kShares), dim3(1024), 0, st, a.ptr, a.n, nwin, bound, off, bptr);
+    hipLaunchKernelGGL(hbci_block_fill_kernel, dim3(kShares, nwin), dim3(1024), kBlockFillLds, st, a.ptr, a.col, a.val, a.n, nwin,
+                       bound, off, bptr, at<uint32_t>(L.col[cur ^ 1]), at<double>(L.val[cur ^ 1]));
+  }
   void dav_product(const DavSpace& a, int m) {
-    const int nb = blocks(a.n, 16, kRowBlocks);
-    hipLaunchKernelGGL(hbci_dav_product_kernel, dim3(nb), dim3(1024), 0, st, a, m);
+    const int nb = blocked(a) ? kShares : blocks(a.n, 16, kRowBlocks);
+    if (blocked(a))
+      hipLaunchKernelGGL(hbci_dav_block_kernel, dim3(nb), dim3(1024), kBlockLds, st, a, m);
+    else
+      hipLaunchKernelGGL(hbci_dav_product_kernel, dim3(nb), dim3(1024), 0, st, a, m);
     hipLaunchKernelGGL(hbci_dav_subspace_kernel, dim3(1), dim3(256), 0, st, a, nb, m, o.m_max);
   }
 
@@ -1523,7 +1547,8 @@ struct Run {
     constexpr int kBatch = 4;
     const DavSpace a{at<int64_t>(L.ptr[cur]), at<int32_t>(L.col[cur]), at<double>(L.val[cur]), at<double>(L.rdiag),
                      at<int32_t>(L.pos), at<int32_t>(L.fpos), x(), at<double>(L.basis), at<double>(L.sig),
-                     at<double>(L.part), at<DavCtl>(L.dav), o.max_det, n_rep};
+                     at<double>(L.part), at<DavCtl>(L.dav), o.max_det, n_rep, n, at<int32_t>(L.bound),
+                     at<int64_t>(L.bptr), at<uint32_t>(L.col[cur ^ 1]), at<double>(L.val[cur ^ 1])};
     if (n <= kSmallDav) {
       const SmallDav s{a, o.m_max, o.max_dav, o.r_tol, at<double>(L.part)};
       hipLaunchKernelGGL(hbci_dav_small_kernel, dim3(1), dim3(kSmallThreads), 0, st, s);
@@ -1546,6 +1571,7 @@ struct Run {
       std::memcpy(done, pin + 2, sizeof(int));
       return hipSuccess;
     };
+    if (blocked(a)) block_h(a);
     hipLaunchKernelGGL(hbci_dav_start_kernel, dim3(blocks(n_rep, 256, 1 << 30)), dim3(256), 0, st, a);
     dav_product(a, 0);
     int m = 1, done = 0;

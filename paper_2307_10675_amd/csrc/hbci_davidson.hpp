@@ -57,7 +57,22 @@ struct DavSpace {
   double* part;
   DavCtl* ctl;
   int64_t ld, n;        // n representatives
+  int64_t n_full;       // entries of x
+  // the blocked form of H (below)
+  const int32_t* bound;
+  const int64_t* bptr;
+  const uint32_t* bcol;
+  const double* bval;
 };
+
+// The blocked form of H: shares of the rows (one workgroup each, about equal
+// in entries) by windows of x.  An entry holds its column in the window and
+// its row in the share.
+constexpr int kWinBits = 13, kWin = 1 << kWinBits, kShareRows = 8192, kShares = 256;
+constexpr int64_t kBlockMin = 1024;                               // full spaces in blocked form: more keys,
+constexpr int64_t kBlockMax = (int64_t)64 * kWin;                 // at most this many
+constexpr int64_t kBlockMaxRows = (int64_t)(kShareRows / 8 - 1) * kShares;  // and this many rows (hbci_share_kernel)
+constexpr int kBlockLds = (kWin + kShareRows + 16 * kMaxM) * 8;
 
 constexpr double kRoot2 = 1.4142135623730951, kRRoot2 = 0.70710678118654752;
 
@@ -264,8 +279,260 @@ __global__ void __launch_bounds__(1024, 8) hbci_dav_product_kernel(DavSpace a, i
   if ((int)threadIdx.x <= m) {
     double t = 0.0;
     for (int w = 0; w < 16; ++w) t += red[w * kMaxM + threadIdx.x];
-    __hip_atomic_store(a.part + (int)threadIdx.x * kRowBlocks + blockIdx.x, t, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
+    a.part[(int)threadIdx.x * kRowBlocks + blockIdx.x] = t;
+  }
+}
+
+// bound[b]: first row of share b.  A share holds 1 / kShares of 7/8 of the
+// entries and 1/8 of the rows, so that it has at most 8 n / kShares rows, and
+// at most 8/7 of its part of the entries.
+__global__ void hbci_share_kernel(const int64_t* __restrict__ ptr, int64_t n, int32_t* __restrict__ bound) {
+  const int b = threadIdx.x;
+  if (b > kShares) return;
+  // weight before row r, in units of 1 / (8 n nnz), against b / kShares
+  const double nnz = (double)(ptr[n] > 0 ? ptr[n] : 1), want = (double)b / kShares;
+  int64_t lo = 0, hi = n;
+  while (lo < hi) {
+    const int64_t mid = (lo + hi) >> 1;
+    if (0.875 * ((double)ptr[mid] / nnz) + 0.125 * ((double)mid / (double)n) < want)
+      lo = mid + 1;
+    else
+      hi = mid;
+  }
+  bound[b] = b == kShares ? (int32_t)n : (int32_t)lo;
+}
+
+// off[w][q]: entries of row q before window w, w <= nwin (one wave per row; its columns ascend)
+__global__ void __launch_bounds__(256) hbci_win_offsets_kernel(const int64_t* __restrict__ ptr,
+                                                               const int32_t* __restrict__ col, int64_t n, int nwin,
+                                                               uint16_t* __restrict__ off) {
+  const int lane = threadIdx.x & 63;
+  const int64_t nw = (int64_t)gridDim.x * 4;
+  for (int64_t q = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); q < n; q += nw) {
+    const int64_t b = ptr[q];
+    const int len = (int)(ptr[q + 1] - b);
+    for (int e = lane; e <= len; e += 64) {
+      const int w = e < len ? col[b + e] >> kWinBits : nwin, v = e > 0 ? col[b + e - 1] >> kWinBits : -1;
+      for (int u = v + 1; u <= w; ++u) off[u * n + q] = (uint16_t)e;
+    }
+  }
+}
+
+// bptr[share][w]: place of block (share, w); a share's blocks lie where its
+// rows lie in H.  One workgroup per share, a wave per window.
+__global__ void __launch_bounds__(1024) hbci_block_ptr_kernel(const int64_t* __restrict__ ptr, int64_t n, int nwin,
+                                                              const int32_t* __restrict__ bound,
+                                                              const uint16_t* __restrict__ off,
+                                                              int64_t* __restrict__ bptr) {
+  __shared__ int cnt[kBlockMax / kWin];
+  const int lane = threadIdx.x & 63;
+  const int r0 = bound[blockIdx.x], r1 = bound[blockIdx.x + 1];
+  for (int w = threadIdx.x >> 6; w < nwin; w += 16) {
+    int c = 0;
+    for (int64_t q = r0 + lane; q < r1; q += 64) c += (int)off[(w + 1) * n + q] - (int)off[w * n + q];
+    for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o, 64);
+    if (lane == 0) cnt[w] = c;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int64_t at = ptr[r0];
+    for (int w = 0; w < nwin; ++w) {
+      bptr[(int64_t)blockIdx.x * nwin + w] = at;
+      at += cnt[w];
+    }
+    if (blockIdx.x == kShares - 1) bptr[(int64_t)kShares * nwin] = at;
+  }
+}
+
+// Block (blockIdx.x, blockIdx.y) from the rows of H.  Its entries row by row
+// are cut into chunks of kChunk, and a chunk is laid out with its 64 parts
+// side by side: the lanes of a wave of the product then add to different rows.
+// A chunk is put together in LDS and written in one piece.  (Entries written
+// one by one to their places, 8 bytes of a line at a time, took 3.29 ms a step on
+// average at 285020 keys.)
+constexpr int kChunk = 3072, kChunkSlots = (kChunk / 64 + 1) * 65;
+constexpr int kBlockFillLds = (kShareRows + 1024) * 4 + kChunkSlots * 12;
+
+__global__ void __launch_bounds__(1024) hbci_block_fill_kernel(const int64_t* __restrict__ ptr,
+                                                               const int32_t* __restrict__ col,
+                                                               const double* __restrict__ val, int64_t n, int nwin,
+                                                               const int32_t* __restrict__ bound,
+                                                               const uint16_t* __restrict__ off,
+                                                               const int64_t* __restrict__ bptr,
+                                                               uint32_t* __restrict__ bcol, double* __restrict__ bval) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  double* sv = (double*)smem;
+  uint32_t* sc = (uint32_t*)(sv + kChunkSlots);
+  int* first = (int*)(sc + kChunkSlots);  // entries of the block before each row
+  int* part = first + kShareRows;
+  const int tid = threadIdx.x, w = blockIdx.y;
+  const int r0 = bound[blockIdx.x], rows = bound[blockIdx.x + 1] - r0;
+  const int64_t start = bptr[(int64_t)blockIdx.x * nwin + w];
+  const uint16_t* o0 = off + (int64_t)w * n + r0;
+  const uint16_t* o1 = o0 + n;
+  constexpr int per = kShareRows / 1024;
+  for (int i = tid; i < kShareRows; i += 1024) first[i] = i < rows ? (int)o1[i] - (int)o0[i] : 0;
+  __syncthreads();
+  int own = 0;
+  for (int i = 0; i < per; ++i) own += first[tid * per + i];
+  part[tid] = own;
+  __syncthreads();
+  for (int o = 1; o < 1024; o <<= 1) {
+    const int v = tid >= o ? part[tid - o] : 0;
+    __syncthreads();
+    part[tid] += v;
+    __syncthreads();
+  }
+  int sum = part[tid] - own;
+  for (int i = 0; i < per; ++i) {
+    const int v = first[tid * per + i];
+    first[tid * per + i] = sum;
+    sum += v;
+  }
+  __syncthreads();
+  const int total = part[1023];
+  for (int c0 = 0; c0 < total; c0 += kChunk) {
+    const int nc = total - c0 < kChunk ? total - c0 : kChunk;
+    const int S = nc >> 6, rem = nc & 63;  // parts of S + 1 entries, rem of them, then of S
+    // the rows of this thread's entries (the last row that starts at or
+    // before one), then all their loads in flight
+    int row[kChunk / 1024];
+    uint32_t c[kChunk / 1024];
+    double v[kChunk / 1024];
+#pragma unroll
+    for (int u = 0; u < kChunk / 1024; ++u) {
+      const int e = c0 + u * 1024 + tid;
+      int lo = 0, hi = rows;
+      while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (first[mid] <= e)
+          lo = mid;
+        else
+          hi = mid;
+      }
+      row[u] = lo;
+    }
+#pragma unroll
+    for (int u = 0; u < kChunk / 1024; ++u)
+      if (u * 1024 + tid < nc) {
+        const int g = row[u];
+        const int64_t i = ptr[r0 + g] + o0[g] + (c0 + u * 1024 + tid - first[g]);
+        c[u] = (uint32_t)col[i];
+        v[u] = val[i];
+      }
+#pragma unroll
+    for (int u = 0; u < kChunk / 1024; ++u) {
+      const int e = u * 1024 + tid;
+      if (e >= nc) break;
+      int lane, step;
+      if (nc == kChunk) {
+        lane = e / (kChunk / 64);
+        step = e % (kChunk / 64);
+      } else if (e < rem * (S + 1)) {
+        lane = e / (S + 1);
+        step = e - lane * (S + 1);
+      } else {
+        const int d = e - rem * (S + 1), k = d / S;
+        lane = rem + k;
+        step = d - k * S;
+      }
+      sv[step * 65 + lane] = v[u];
+      sc[step * 65 + lane] = (c[u] & (kWin - 1)) | (uint32_t)row[u] << kWinBits;
+    }
+    __syncthreads();
+    for (int i = tid; i < nc; i += 1024) {
+      const int at = (i >> 6) * 65 + (i & 63);
+      bval[start + c0 + i] = sv[at];
+      bcol[start + c0 + i] = sc[at];
+    }
+    __syncthreads();
+  }
+}
+
+// The product from the blocked form: a workgroup takes its share of the rows
+// through the windows one after the other, x of the window in LDS (loaded to
+// registers while the window before is worked on) and the sums of its rows
+// beside it.  Gathers and sums are LDS accesses, and what is left of global
+// memory is the stream of H.  (The row form's gathers miss the first-level
+// cache: the 16 rows of a chunk touch 414 lines each and 1212 together, and
+// there is 32 KB.  At 285020 keys and 114.7e6 nonzeros it takes 608 us, with
+// 73.7e6 line requests, of which 12e6 for H.)
+__global__ void __launch_bounds__(1024) hbci_dav_block_kernel(DavSpace a, int m) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  double* xw = (double*)smem;
+  double* sum = xw + kWin;
+  double* red = sum + kShareRows;
+  if (a.ctl->done) return;
+  constexpr int kPer = kWin / 1024;
+  const int tid = threadIdx.x;
+  const int64_t r0 = a.bound[blockIdx.x];
+  const int rows = a.bound[blockIdx.x + 1] - (int)r0;
+  const int nwin = (int)((a.n_full + kWin - 1) / kWin);
+  const int64_t* bp = a.bptr + (int64_t)blockIdx.x * nwin;
+  double xr[kPer];
+  auto fetch = [&](int w) {
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const int64_t p = (int64_t)w * kWin + i * 1024 + tid;
+      xr[i] = p < a.n_full ? a.x[p] : 0.0;
+    }
+  };
+  fetch(0);
+  for (int i = tid; i < rows; i += 1024) sum[i] = 0.0;
+  for (int w = 0; w < nwin; ++w) {
+    const int64_t p0 = bp[w], p1 = bp[w + 1];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) xw[i * 1024 + tid] = xr[i];
+    __syncthreads();
+    if (w + 1 < nwin) fetch(w + 1);
+    // four entries of a lane follow each other in H: those of one row are summed first
+    for (int64_t p = p0 + (tid >> 6) * 256 + (tid & 63); p < p1; p += 4096) {
+      uint32_t c[4];
+      double v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {  // past the end the first entry again, with a zero value
+        const int64_t i = p + u * 64 < p1 ? p + u * 64 : p;
+        c[u] = __builtin_nontemporal_load(a.bcol + i);
+        v[u] = __builtin_nontemporal_load(a.bval + i);
+      }
+      double s = v[0] * xw[c[0] & (kWin - 1)];
+#pragma unroll
+      for (int u = 1; u < 4; ++u) {
+        const double t = (p + u * 64 < p1 ? v[u] : 0.0) * xw[c[u] & (kWin - 1)];
+        if (c[u] >> kWinBits != c[u - 1] >> kWinBits) {
+          lds_add(&sum[c[u - 1] >> kWinBits], s);
+          s = 0.0;
+        }
+        s += t;
+      }
+      lds_add(&sum[c[3] >> kWinBits], s);
+    }
+  }
+  __syncthreads();
+  double acc[kMaxM] = {};
+  for (int g = tid; g < rows; g += 1024) {
+    const int64_t row = r0 + g;
+    const int32_t p = a.pos[row];
+    double y = sum[g] + a.diag[row] * a.x[p];
+    if (p != a.fpos[row]) y *= kRoot2;
+    a.Sb[m * a.ld + row] = y;
+#pragma unroll
+    for (int j = 0; j < kMaxM; ++j)
+      if (j <= m) acc[j] += a.Vb[j * a.ld + row] * y;
+  }
+  const int lane = tid & 63, wave = tid >> 6;
+#pragma unroll
+  for (int j = 0; j < kMaxM; ++j)
+    if (j <= m) {
+      const double t = wave_sum(acc[j]);
+      if (lane == 0) red[wave * kMaxM + j] = t;
+    }
+  __syncthreads();
+  if (tid <= m) {
+    double t = 0.0;
+    for (int w = 0; w < 16; ++w) t += red[w * kMaxM + tid];
+    a.part[tid * kRowBlocks + blockIdx.x] = t;
   }
 }
 
