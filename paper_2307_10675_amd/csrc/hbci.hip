@@ -166,6 +166,7 @@ struct Bits {
   uint64_t* w;
   int32_t* pre;
   const uint16_t* rank;  // string -> its rank among those of its electron count, in numeric order
+  const uint16_t* str;   // rank -> string
   int W, n_str;
   uint64_t* dets;
   int64_t cap;
@@ -594,8 +595,8 @@ __global__ void fill_f64_kernel(double* p, int64_t n, double v) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = v;
 }
 
-// rank[s] of every string of the reference's electron count
-__global__ void hbci_rank_kernel(int k, int na, uint16_t* __restrict__ rank) {
+// rank[s] of every string of the reference's electron count, and the string of every rank
+__global__ void hbci_rank_kernel(int k, int na, uint16_t* __restrict__ rank, uint16_t* __restrict__ str) {
   const int s = blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= 1 << k || __popc(s) != na) return;
   int r = 0, i = 0;
@@ -607,6 +608,7 @@ __global__ void hbci_rank_kernel(int k, int na, uint16_t* __restrict__ rank) {
     r += b;
   }
   rank[s] = (uint16_t)r;
+  str[r] = (uint16_t)s;
 }
 
 // V := the reference (a closed shell)
@@ -1192,6 +1194,97 @@ __global__ void __launch_bounds__(64 * kWaves, 8) hbci_pt2_kernel(const double* 
   }
 }
 
+// The external space of a solve as an array over pairs of string ranks
+// (representatives ra >= rb), where it fits the room of the hash table: one
+// addition that nothing waits for in place of a probe, an addition and, for
+// a new key, a place in the list.  The pairs that no term has reached hold
+// -0, which no sum of nonzero terms is.
+__device__ __forceinline__ bool touched(double v) { return __double_as_longlong(v) != __double_as_longlong(-0.0); }
+
+// hbci_pt2_kernel (half) into that array.  Bound by the additions, 8 bytes
+// each at scattered places of 1.3 GB at 16 orbitals; sources in key order keep
+// to the rows of the same few first strings.  (Into the hash table, with a
+// counter that every new key passes: 33.2 ms at 285020 keys.)
+__global__ void __launch_bounds__(64 * kWaves, 8) hbci_pt2_array_kernel(const double* __restrict__ ints, int k,
+                                                                        const Bits V, const uint64_t* __restrict__ src,
+                                                                        const int32_t* __restrict__ pos,
+                                                                        const double* __restrict__ c, int64_t n,
+                                                                        double eps, double* __restrict__ N) {
+  const Lds s = load_lds<true>(ints, k);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint8_t* L = s.lists + wave * kListPairs;
+  for (int64_t i = (int64_t)blockIdx.x * kWaves + wave; i < n; i += (int64_t)gridDim.x * kWaves) {
+    const double ci = c[pos[i]];
+    if (ci == 0.0) continue;
+    const Det d = make_det(src[i], k, L, lane);
+    const bool self = d.A == d.B;
+    const Screen S = make_screen(d, s, ci, eps, L, lane);
+    const float inv_nb = 1.0f / (float)S.nb;
+    // lane l: the ranks of the strings of kept pairs l
+    auto kept = [&](uint32_t str, int x) { return (int)V.rank[str ^ (1u << (x & 15)) ^ (1u << (x >> 4))]; };
+    const int rank_a = lane < S.na ? kept(d.A, S.a[lane]) : 0, rank_b = lane < S.nb ? kept(d.B, S.b[lane]) : 0;
+    for (int t0 = 0; t0 < S.total; t0 += 64) {
+      const int t = t0 + lane, v = t - S.singles - S.same;
+      const int u = v >= 0 && v < S.na * S.nb ? (int)((v + 0.5f) * inv_nb) : 0;
+      int ra = __shfl(rank_a, u, 64), rb = __shfl(rank_b, v >= 0 ? (v - u * S.nb) & 63 : 0, 64);
+      if (t >= S.total) continue;
+      double h;
+      const uint64_t a = screened(d, S, t, s, k, inv_nb, &h);
+      const double hc = h * ci;
+      if (!(fabs(hc) > eps)) continue;
+      if (v < 0) {
+        ra = V.rank[(uint32_t)a];
+        rb = V.rank[(uint32_t)(a >> 32)];
+      }
+      double w = 1.0;
+      if (rb > ra) {
+        if (self) continue;
+        const int x = ra;
+        ra = rb;
+        rb = x;
+      } else if (!self && rb == ra) {
+        w = 2.0;
+      }
+      if (!has_pair(V, ra, rb)) unsafeAtomicAdd(N + (int64_t)ra * V.n_str + rb, w * hc);
+    }
+  }
+}
+
+// The touched pairs of the array, listed row by row.
+__global__ void __launch_bounds__(256) hbci_ext_list_kernel(const double* __restrict__ N, int n_str,
+                                                            int64_t* __restrict__ elist, int64_t cap, HbciCtl* ctl) {
+  __shared__ int cnt[4];
+  __shared__ unsigned long long base;
+  const int ra = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const double* row = N + (int64_t)ra * n_str;
+  int own = 0;
+  for (int rb = threadIdx.x; rb <= ra; rb += 256) own += touched(row[rb]);
+  own = wave_sum_int(own);
+  if (lane == 0) cnt[wave] = own;
+  __syncthreads();
+  const int all = cnt[0] + cnt[1] + cnt[2] + cnt[3];
+  if (all == 0) return;
+  if (threadIdx.x == 0) {
+    base = atomicAdd(&ctl->n_ext, (unsigned long long)all);
+    if ((int64_t)base + all > cap) atomicOr(&ctl->flags, kFlagExtCap);
+  }
+  __syncthreads();
+  int64_t at = (int64_t)base;
+  for (int r0 = 0; r0 <= ra; r0 += 256) {
+    const int rb = r0 + threadIdx.x;
+    const bool t = rb <= ra && touched(row[rb]);
+    const uint64_t m = __ballot(t);
+    __syncthreads();
+    if (lane == 0) cnt[wave] = (int)__popcll(m);
+    __syncthreads();
+    int64_t p = at;
+    for (int w = 0; w < wave; ++w) p += cnt[w];
+    p += __popcll(m & ((1ull << lane) - 1ull));
+    if (t && p < cap) elist[p] = (int64_t)ra * n_str + rb;
+    at += cnt[0] + cnt[1] + cnt[2] + cnt[3];
+  }
+}
+
 // Sum over the workgroup; the result in thread 0.
 __device__ __forceinline__ double group_sum(double v, double* red) {
   v = wave_sum(v);
@@ -1206,8 +1299,10 @@ __device__ __forceinline__ double group_sum(double v, double* red) {
 }
 
 // part[block] = partial sum of N_a^2 / (e - H_aa); part[kNB + block] = count
+// (of the listed slots of the hash table, or places of the array N over pairs of str)
 __global__ void __launch_bounds__(64 * kWaves) hbci_e2_kernel(const double* __restrict__ ints, int k,
-                                                      const ExtSlot* __restrict__ et,
+                                                      const ExtSlot* __restrict__ et, const double* __restrict__ N,
+                                                      const uint16_t* __restrict__ str, int n_str,
                                                       const int64_t* __restrict__ elist, int64_t cap,
                                                       const HbciCtl* __restrict__ ctl, double e, int half,
                                                       double* __restrict__ part) {
@@ -1217,12 +1312,22 @@ __global__ void __launch_bounds__(64 * kWaves) hbci_e2_kernel(const double* __re
   double sum = 0.0, cnt = 0.0;
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n_filled;
        t += (int64_t)gridDim.x * blockDim.x) {
-    const ExtSlot sl = et[elist[t]];
-    const uint64_t key = sl.key;
-    const double na = sl.val;
+    const int64_t p = elist[t];
+    uint32_t A, B;
+    double na;
+    if (N) {
+      A = str[p / n_str];
+      B = str[p % n_str];
+      na = N[p];
+    } else {
+      const ExtSlot sl = et[p];
+      A = (uint32_t)sl.key;
+      B = (uint32_t)(sl.key >> 32);
+      na = sl.val;
+    }
     // a representative stands for itself and its partner
-    const double w = (half && flip_key(key) != key) ? 2.0 : 1.0;
-    sum += w * (na * na / (e - diag_val(s, k, (uint32_t)key, (uint32_t)(key >> 32))));
+    const double w = (half && A != B) ? 2.0 : 1.0;
+    sum += w * (na * na / (e - diag_val(s, k, A, B)));
     cnt += w;
   }
   sum = group_sum(sum, red);
@@ -1244,7 +1349,7 @@ uint64_t pow2_at_least(int64_t x) {
 struct Layout {
   int64_t ints, ctl, dav, part, bsum, dets, keys, vals, diag, cnt, addc, used, ptr[2], col[2], val[2], basis, sig, x[2],
       ext, elist;
-  int64_t bound, off, bptr, rank, bits, pre, start, place, pair, moved, row_of, key, pos, fpos, old, rdiag;
+  int64_t bound, off, bptr, rank, str, bits, pre, start, place, pair, moved, row_of, key, pos, fpos, old, rdiag;
   int64_t bytes;
   uint64_t tcap, ecap;
 };
@@ -1282,6 +1387,7 @@ Layout layout(int k, const ifci_hbci_options& o) {
   L.off = take((bw + 1) * (bd < kBlockMaxRows ? bd : kBlockMaxRows) * 2);
   L.bptr = take((kShares * bw + 1) * 8);
   L.rank = take(((int64_t)1 << k) * 2);
+  L.str = take(strings * 2);
   L.bits = take(words * 8);
   L.pre = take(words * 4);
   L.start = take(strings * 2 * 4);
@@ -1333,7 +1439,7 @@ struct Run {
     const int na = __builtin_popcount((uint32_t)I.ref);
     int64_t n = 1;
     for (int i = 0; i < na; ++i) n = n * (I.k - i) / (i + 1);
-    return Bits{at<uint64_t>(L.bits), at<int32_t>(L.pre), at<uint16_t>(L.rank), (int)((n + 63) / 64), (int)n,
+    return Bits{at<uint64_t>(L.bits), at<int32_t>(L.pre), at<uint16_t>(L.rank), at<uint16_t>(L.str), (int)((n + 63) / 64), (int)n,
                 at<uint64_t>(L.dets), o.max_det, at<HbciCtl>(L.ctl)};
   }
   Order order() const {
@@ -1374,6 +1480,7 @@ struct Run {
     for (const void* fn : {(const void*)hbci_select_kernel<Space>, (const void*)hbci_select_kernel<Bits>,
                            (const void*)hbci_diag_kernel, (const void*)hbci_count_kernel, (const void*)hbci_fill_kernel,
                            (const void*)hbci_pt2_kernel<Space>, (const void*)hbci_pt2_kernel<Bits>,
+                           (const void*)hbci_pt2_array_kernel,
                            (const void*)hbci_count_new_kernel, (const void*)hbci_fill_new_kernel,
                            (const void*)hbci_e2_kernel, (const void*)hbci_dav_block_kernel, (const void*)hbci_block_fill_kernel,
                            (const void*)hbci_merge_rows_kernel<1024, kShortRow, kLongRow>})
@@ -1398,7 +1505,7 @@ struct Run {
     const Bits V = bits();
     const int64_t words = (int64_t)V.n_str * V.W;
     hipLaunchKernelGGL(hbci_rank_kernel, dim3(blocks((int64_t)1 << I.k, 256, 256)), dim3(256), 0, st, I.k,
-                       __builtin_popcount((uint32_t)I.ref), at<uint16_t>(L.rank));
+                       __builtin_popcount((uint32_t)I.ref), at<uint16_t>(L.rank), at<uint16_t>(L.str));
     hipLaunchKernelGGL(fill_u64_kernel, dim3(blocks(words, 256, 4096)), dim3(256), 0, st, V.w, words, (uint64_t)0);
     hipLaunchKernelGGL(hbci_ref_kernel, dim3(1), dim3(1), 0, st, I.ref, V);
     const hipError_t e = hipGetLastError();
@@ -1515,7 +1622,7 @@ struct Run {
     else dav_step<16>(a, m, check_only);
   }
   static bool blocked(const DavSpace& a) {
-    return a.n_full > kBlockMin && a.n_full <= kBlockMax && a.n <= kBlockMaxRows;
+    return a.n_full <= kBlockMax && a.n <= kBlockMaxRows;
   }
   // the blocked form of H, in the CSR buffer that the next step builds its H in
   void block_h(const DavSpace& a) {
@@ -1611,9 +1718,27 @@ struct Run {
     hipLaunchKernelGGL(hbci_pt2_kernel<VSpace>, dim3(blocks(n, kWaves, 8192)), dim3(64 * kWaves),
                        lds(kListPairs, true), st, at<double>(L.ints), I.k, V, src, pos, c, n, eps2, half ? 1 : 0,
                        at<ExtSlot>(L.ext), at<int64_t>(L.elist), L.ecap - 1, o.max_ext);
+    return e2_sum(nullptr, 0, e_act, half, e2, n_ext);
+  }
+
+  // the same of a solve (half), with the external space as an array where it
+  // fits the table's room: 16 bytes a slot, at least two slots per key
+  hipError_t pt2_solve(const Bits& V, const Order& O, int64_t n_rep, double e_act, double* e2, int64_t* n_ext) {
+    const int64_t pairs = (int64_t)V.n_str * V.n_str;
+    if (pairs > 2 * (int64_t)L.ecap) return pt2(V, O.key, O.pos, n_rep, x(), e_act, o.eps2, true, e2, n_ext);
+    double* N = at<double>(L.ext);
+    hipLaunchKernelGGL(fill_f64_kernel, dim3(blocks(pairs, 256, 4096)), dim3(256), 0, st, N, pairs, -0.0);
+    hipLaunchKernelGGL(hbci_pt2_array_kernel, dim3(blocks(n_rep, kWaves, 8192)), dim3(64 * kWaves),
+                       lds(kListPairs, true), st, at<double>(L.ints), I.k, V, O.key, O.pos, x(), n_rep, o.eps2, N);
+    hipLaunchKernelGGL(hbci_ext_list_kernel, dim3(V.n_str), dim3(256), 0, st, N, V.n_str, at<int64_t>(L.elist),
+                       o.max_ext, at<HbciCtl>(L.ctl));
+    return e2_sum(N, V.n_str, e_act, true, e2, n_ext);
+  }
+
+  hipError_t e2_sum(const double* N, int n_str, double e_act, bool half, double* e2, int64_t* n_ext) {
     hipLaunchKernelGGL(hbci_e2_kernel, dim3(kNB), dim3(64 * kWaves), lds(kListRanks, false), st, at<double>(L.ints),
-                       I.k, at<ExtSlot>(L.ext), at<int64_t>(L.elist), o.max_ext, at<HbciCtl>(L.ctl), e_act,
-                       half ? 1 : 0, at<double>(L.part));
+                       I.k, at<ExtSlot>(L.ext), N, at<uint16_t>(L.str), n_str, at<int64_t>(L.elist), o.max_ext,
+                       at<HbciCtl>(L.ctl), e_act, half ? 1 : 0, at<double>(L.part));
     hipError_t e = hipGetLastError();
     double s[2];
     if (e == hipSuccess) e = read_parts(2, s);
@@ -1704,7 +1829,7 @@ ifci_status hbci_solve(const HbciInc& I, const ifci_hbci_options& o, void* work,
   }
   double e2 = 0.0;
   int64_t n_ext = 0;
-  HB_TRY(R.pt2(V, O.key, O.pos, n_rep, R.x(), theta, o.eps2, true, &e2, &n_ext), "hbci pt2");
+  HB_TRY(R.pt2_solve(V, O, n_rep, theta, &e2, &n_ext), "hbci pt2");
   if (R.ctl.flags) return capacity_failure(R.ctl.flags);
   if (dets_out) HB_TRY(hipMemcpyAsync(dets_out, R.at<uint64_t>(R.L.dets), n * 8, hipMemcpyDeviceToDevice, st), "copy");
   if (c_out) {

@@ -69,9 +69,10 @@ struct DavSpace {
 // in entries) by windows of x.  An entry holds its column in the window and
 // its row in the share.
 constexpr int kWinBits = 13, kWin = 1 << kWinBits, kShareRows = 8192, kShares = 256;
-constexpr int64_t kBlockMin = 1024;                               // full spaces in blocked form: more keys,
-constexpr int64_t kBlockMax = (int64_t)64 * kWin;                 // at most this many
-constexpr int64_t kBlockMaxRows = (int64_t)(kShareRows / 8 - 1) * kShares;  // and this many rows (hbci_share_kernel)
+// Spaces in blocked form: at most this many keys (64 windows; a row's piece of a
+// window then still has 13 entries at 850 a row) ...
+constexpr int64_t kBlockMax = (int64_t)64 * kWin;
+constexpr int64_t kBlockMaxRows = (int64_t)(kShareRows / 8 - 1) * kShares;  // ... and rows (hbci_share_kernel)
 constexpr int kBlockLds = (kWin + kShareRows + 16 * kMaxM) * 8;
 
 constexpr double kRoot2 = 1.4142135623730951, kRRoot2 = 0.70710678118654752;
