@@ -1720,17 +1720,30 @@ __device__ __forceinline__ void solve_dav(const SolveArgs& A, int id, char* lds,
     double rx[NE], rax[NE], rt[NE];
 #pragma unroll
     for (int e = 0; e < NE; ++e) rx[e] = rax[e] = 0.0;
-#pragma unroll 4
-    for (int j = 0; j <= m; ++j) {
-      const double yj = L.yp[j];
-      const double* vj = base + j * sti;
-      const double* sj = base + mst + j * sti;
+    // (JA vectors at a time, all their loads in flight: left alone, the
+    // compiler waits on each load in turn, 50k of pass A's 55k cycles at 8 orbitals)
+    constexpr int JA = 4;
+    for (int j0 = 0; j0 <= m; j0 += JA) {
+      double v[JA][NE], sv[JA][NE], y[JA];
 #pragma unroll
-      for (int e = 0; e < NE; ++e) {
-        const int i = min(tix + e * kBatchThreads, nsi - 1);
-        rx[e] += yj * vj[i];
-        rax[e] += yj * sj[i];
+      for (int u = 0; u < JA; ++u) {
+        const int j = min(j0 + u, m);
+        y[u] = j0 + u <= m ? L.yp[j] : 0.0;
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+          const int i = min(tix + e * kBatchThreads, nsi - 1);
+          v[u][e] = base[j * sti + i];
+          sv[u][e] = base[mst + j * sti + i];
+        }
       }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < JA; ++u)
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+          rx[e] += y[u] * v[u][e];
+          rax[e] += y[u] * sv[u][e];
+        }
     }
     double accr = 0.0;
 #pragma unroll
@@ -1754,40 +1767,38 @@ __device__ __forceinline__ void solve_dav(const SolveArgs& A, int id, char* lds,
       const bool in_p = i < nsi && (hd < ps_h || (hd == ps_h && i <= ps_i));
       const double t = in_p ? L.tv[i] : rt[e] / den;
       rt[e] = i < nsi ? t : 0.0;
+      if (i < nsi) L.tv[i] = rt[e];
       acct += rt[e] * rt[e];
     }
     IFCI_MARK(kPhPassA);
-    // ---- pass B: c_j = V_j.t, d_j = S_j.t (j <= m), wave sums into wpart
-#pragma unroll 4
-    for (int j = 0; j <= m; ++j) {
-      const double* vj = base + j * sti;
-      const double* sj = base + mst + j * sti;
-      double c = 0.0, dd = 0.0;
-#pragma unroll
-      for (int e = 0; e < NE; ++e) {
-        const int i = min(tix + e * kBatchThreads, nsi - 1);
-        c += vj[i] * rt[e];
-        dd += sj[i] * rt[e];
-      }
-      c = wave_sum(c);
-      dd = wave_sum(dd);
-      if (lane == 0) {
-        wpart[(2 * j) * 8 + wave] = c;
-        wpart[(2 * j + 1) * 8 + wave] = dd;
-      }
-    }
+    // ---- pass B: c_j = V_j.t, d_j = S_j.t (j <= m) into Gs [0, 16), [16, 32).
+    // A wave takes one product at a time, t from LDS: one wave sum per product,
+    // where every wave summing its part of every product takes eight.
     double tt0;
     {
       double a2[2] = {accr, acct};
-      block_sum_1b<2>(a2, L.red, bsp);
+      block_sum_1b<2>(a2, L.red, bsp);  // its barrier also completes t
       resid = sqrt(a2[0]);
       tt0 = a2[1];
-      // Gs [0, 16) c, [16, 32) d: the wave partials in a fixed order
-      if (tid < 2 * (m + 1)) {
-        const int j = tid >> 1, w = tid & 1;
-        double sum = 0.0;
-        for (int q = 0; q < nw; ++q) sum += wpart[(2 * j + w) * 8 + q];
-        L.Gs[w * kMaxSpace + j] = sum;
+    }
+    {
+      constexpr int NL = (max_strings(K) * (max_strings(K) + 1) / 2 + 63) / 64, NI = NL < 20 ? NL : 20;
+      for (int q = wave; q < 2 * (m + 1); q += nw) {
+        const double* vec = base + ((q & 1) ? mst : 0) + (q >> 1) * sti;
+        double s0 = 0.0;
+        for (int i0 = lane; i0 < nsi; i0 += 64 * NI) {
+          double v[NI];  // all in flight
+#pragma unroll
+          for (int u = 0; u < NI; ++u) v[u] = vec[min(i0 + 64 * u, nsi - 1)];
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int u = 0; u < NI; ++u) {
+            const double x = i0 + 64 * u < nsi ? L.tv[i0 + 64 * u] : 0.0;
+            s0 += v[u] * x;
+          }
+        }
+        const double sum = wave_sum(s0);
+        if (lane == 0) L.Gs[(q & 1) * kMaxSpace + (q >> 1)] = sum;
       }
     }
     IFCI_MARK(kPhRestart);
@@ -1844,14 +1855,24 @@ __device__ __forceinline__ void solve_dav(const SolveArgs& A, int id, char* lds,
         double nv[kKeep], nsg[kKeep];
 #pragma unroll
         for (int k = 0; k < kKeep; ++k) nv[k] = nsg[k] = 0.0;
-        for (int j = 0; j <= m; ++j) {
-          const double v = base[j * sti + i], sv = base[mst + j * sti + i];
+        constexpr int JR = 6;
+        for (int j0 = 0; j0 <= m; j0 += JR) {
+          double v[JR], sv[JR];
 #pragma unroll
-          for (int k = 1; k < kKeep; ++k) {
-            const double q = L.Qp[j * 16 + qc[k]];
-            nv[k] += q * v;
-            nsg[k] += q * sv;
+          for (int u = 0; u < JR; ++u) {
+            const int j = min(j0 + u, m);
+            v[u] = base[j * sti + i];
+            sv[u] = base[mst + j * sti + i];
           }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int u = 0; u < JR; ++u)
+#pragma unroll
+            for (int k = 1; k < kKeep; ++k) {
+              const double q = j0 + u <= m ? L.Qp[(j0 + u) * 16 + qc[k]] : 0.0;
+              nv[k] += q * v[u];
+              nsg[k] += q * sv[u];
+            }
         }
         if (in) {
           base[i] = rx[e];
@@ -1898,12 +1919,21 @@ __device__ __forceinline__ void solve_dav(const SolveArgs& A, int id, char* lds,
     double tt = 0.0;
 #pragma unroll 1
     for (int pass = 0; pass < 2; ++pass) {
-#pragma unroll 2
-      for (int j = 0; j <= mb; ++j) {
-        const double c = L.Gs[(pass == 0 ? 64 : 0) + j];
-        const double* bj = base + j * sti;
+      constexpr int JC = NE > 1 ? 6 : 4;
+      for (int j0 = 0; j0 <= mb; j0 += JC) {
+        double v[JC][NE], c[JC];
 #pragma unroll
-        for (int e = 0; e < NE; ++e) rt[e] -= c * bj[min(tix + e * kBatchThreads, nsi - 1)];
+        for (int u = 0; u < JC; ++u) {
+          const int j = min(j0 + u, mb);
+          c[u] = j0 + u <= mb ? L.Gs[(pass == 0 ? 64 : 0) + j] : 0.0;
+#pragma unroll
+          for (int e = 0; e < NE; ++e) v[u][e] = base[j * sti + min(tix + e * kBatchThreads, nsi - 1)];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < JC; ++u)
+#pragma unroll
+          for (int e = 0; e < NE; ++e) rt[e] -= c[u] * v[u][e];
       }
       double a1[1] = {0.0};
 #pragma unroll
