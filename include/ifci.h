@@ -191,18 +191,20 @@ ifci_status ifci_set_integrals(ifci_plan_t plan, const double* h, const double* 
  * bodies of the increment).  c and sigma: device
  * [n_det] FP64, C[A][B] layout, any c (no symmetry needed); precision is
  * IFCI_FP64 or IFCI_MIXED (FP32 arithmetic, results widened to FP64).
- * Uses the workspace; c and sigma must not alias.  Materialises E
- * (npair x n_det); where the plan's workspace is sized only for the column
- * path (half-filled 16-orbital increments, 180 GB of E otherwise) it returns
- * IFCI_ERR_UNSUPPORTED: use ifci_sigma_sector there. */
+ * Uses the workspace; c and sigma must not alias.  At 9 to 14 orbitals the
+ * fused column kernel runs on c and on its transpose (E never leaves LDS);
+ * elsewhere E (npair x n_det) is materialised, and where the plan's workspace
+ * is sized only for the column path (half-filled 16-orbital increments, 180
+ * GB of E otherwise) the call returns IFCI_ERR_UNSUPPORTED: use
+ * ifci_sigma_sector there. */
 ifci_status ifci_sigma(ifci_plan_t plan, int64_t inc, const double* c, double* sigma,
                        int32_t precision, ifci_stream_t stream);
 
 /* ifci_sigma for callers that cannot allocate device memory: code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
  * Same product, arguments, layout and errors as ifci_sigma, but the
- * product's scratch (E, npair x n_det values of the contraction precision)
- * lives in a fixed array of 32 MiB that the library holds on every device
+ * product's scratch (at most E, npair x n_det values of the contraction
+ * precision) lives in a fixed array of 32 MiB that the library holds on every device
  * it runs on until the process ends, instead of in the plan's workspace.
  * The call allocates nothing (the plan, its workspace and integrals are set
  * up beforehand).  Increments whose E exceeds 32 MiB (in FP64: 10o10e fits,
@@ -214,10 +216,11 @@ ifci_status ifci_sigma_noalloc(ifci_plan_t plan, int64_t inc, const double* c, d
                                int32_t precision, ifci_stream_t stream);
 
 /* Same product restricted to symmetric c (C = C^T, the sector the solvers
- * search): c and sigma are packed scaled vectors (entry (a <= b) at
- * b (b + 1) / 2 + a, off-diagonal entries times sqrt 2), n_str (n_str + 1) / 2
- * FP64 each.  Increments that fit the batched solver (up to 8 active
- * orbitals) run as that solver computes sigma, in one workgroup; half-filled
+ * search).  Increments that fit the batched solver (up to 8 active
+ * orbitals) run as that solver computes sigma, in one workgroup, on full
+ * [n_det] vectors.  Above, c and sigma are packed scaled vectors (entry (a <=
+ * b) at b (b + 1) / 2 + a, off-diagonal entries times sqrt 2), n_str (n_str +
+ * 1) / 2 FP64 each: half-filled
  * increments of 10, 12, 14 or 16 orbitals run the fused column kernel (one
  * workgroup per beta string, E never leaves LDS; uses the workspace).
  * Other shapes: IFCI_ERR_UNSUPPORTED.  c and sigma must not alias. */
@@ -412,7 +415,8 @@ ifci_status ifci_set_tuning(ifci_plan_t plan, int32_t k, int32_t precision, int3
  * max_iter steps.  PT2: for every a outside V,
  * N_a = sum over i in V with |H_ai c_i| > eps2 of H_ai c_i and
  * E_PT2 = sum_a N_a^2 / (E_var - H_aa).  Every step runs in device kernels
- * over hash tables in the caller's work buffer; the host drives the loop.
+ * in the caller's work buffer (the selected space as bits over pairs of
+ * strings); the host drives the loop.
  * ------------------------------------------------------------------------- */
 typedef struct {
   double eps1;       /* variational selection threshold (Eh), >= 0 */

@@ -49,8 +49,8 @@ namespace {
 constexpr uint64_t kEmpty = ~0ull;
 constexpr int kNB = 512;        // workgroups of the vector kernels
 // Waves per workgroup of the kernels that hold the integrals in LDS: at 16
-// orbitals (77 KB) two workgroups fit a CU, so 16 waves each keep 32 waves
-// of table probes in flight per CU.
+// orbitals (80 KB) two workgroups fit a CU, so 16 waves each, of at most 64
+// VGPRs, keep 32 waves in flight per CU.
 constexpr int kWaves = 16;
 enum : unsigned { kFlagDetCap = 1u, kFlagExtCap = 2u, kFlagDuplicate = 4u, kFlagNoPartner = 8u };
 

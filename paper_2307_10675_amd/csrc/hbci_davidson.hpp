@@ -10,8 +10,9 @@
 // A step is five launches, none of which the host waits for: the small state
 // (subspace matrix, coefficients, the end of the loop) lives on the device and
 // is advanced by the block of a pass that ends last, from the partials of all
-// blocks.  (The host-driven form took 13 launches and 3 read-backs, 0.19 ms a
-// step beside the product at 285020 keys; this one takes 0.05 ms.)
+// blocks.  (Driven from the host a step was 13 launches and 3 read-backs: 29 ms
+// of passes and most of 83 ms of waiting in a 376 ms solve of a 16-orbital
+// increment with 285020 keys; now 22 ms and 11 ms in 159 ms.)
 #pragma once
 
 #include "device_common.hpp"
@@ -238,15 +239,12 @@ __global__ void __launch_bounds__(256) hbci_dav_orth_kernel(DavSpace a, int m) {
   }
 }
 
-// S_m = H V_m from the spread x, and its overlaps with the basis.
-//
-// One wave per row, 16 rows of a chunk side by side in a workgroup.  Bound by
-// the loads of x: the entries of a row and of its neighbours in key order
-// fall on the same few strings of either spin, so with rows and columns in key
-// order a load instruction touches few lines, and those the CU's first-level
-// cache holds.  (Rows and columns in order of selection: 391 us on average
-// over the solve of a 16-orbital increment with 114.7e6 nonzeros at its end.)
-// The entries of H are read once and bypass the caches.
+// S_m = H V_m from the spread x, and its overlaps with the basis, for spaces
+// past the limits of the blocked form (below), which is the faster one at every
+// size that it takes (on average over a solve: 16.1 us here and 11.1 there at 10
+// orbitals, 41.8 and 23.3 at 12, both at eps1 = 1 mEh; 48 and 26 at 14 and 2
+// mEh; 338 and 154 at 16, 285020 keys).  One wave per row, 16 neighbouring rows in a workgroup.  Bound by
+// first-level cache misses of the gathers.
 __global__ void __launch_bounds__(1024, 8) hbci_dav_product_kernel(DavSpace a, int m) {
   __shared__ double red[16 * kMaxM];
   if (a.ctl->done) return;

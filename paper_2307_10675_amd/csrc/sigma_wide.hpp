@@ -306,8 +306,7 @@ __global__ void __launch_bounds__(256) col_frag_kernel(const double* __restrict_
 // in turn, so that the sums do not depend on how the waves are scheduled (for
 // vectors of any symmetry, whose product has always been reproducible to the
 // bit; a wave only waits for tiles of the waves beside it, which are resident
-// with it; 12o12e 0.58 -> 0.62 ms, but 14o14e 5.2 -> 6.9 ms for a symmetric
-// vector).  Ends with a barrier, so the next column may reuse the LDS at once.
+// with it; for a symmetric vector it would cost 14o14e 5.2 -> 6.9 ms).  Ends with a barrier, so the next column may reuse the LDS at once.
 template <typename T, int K>
 __device__ __forceinline__ void column_body(int N, const int32_t* __restrict__ ptab, const int16_t* __restrict__ ptabT,
                                             const T* __restrict__ cf, const T* __restrict__ vfg,
