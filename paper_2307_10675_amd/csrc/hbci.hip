@@ -1126,9 +1126,11 @@ __global__ void __launch_bounds__(NT) hbci_merge_rows_kernel(const int64_t* __re
   }
 }
 
-// Rows of up to kShortRow entries take 256 threads and 12 KB of LDS each, the
-// others (at most 5792 replacements at 16 orbitals) 1024 and 96 KB.
-constexpr int kShortRow = 1024, kLongRow = 8192;
+// Rows of up to kShortRow entries take 256 threads and 12 KB of LDS each, up
+// to kMidRow twice the LDS, the others (at most 5792 replacements at 16
+// orbitals) 1024 threads and 96 KB, one workgroup a CU: that form for all rows
+// past kShortRow took 0.90 ms a step on average at 316208 keys.
+constexpr int kShortRow = 1024, kMidRow = 2048, kLongRow = 8192;
 
 __global__ void fill_i32_kernel(int32_t* p, int64_t n, int32_t v) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = v;
@@ -1483,7 +1485,7 @@ struct Run {
                            (const void*)hbci_pt2_array_kernel,
                            (const void*)hbci_count_new_kernel, (const void*)hbci_fill_new_kernel,
                            (const void*)hbci_e2_kernel, (const void*)hbci_dav_block_kernel, (const void*)hbci_block_fill_kernel,
-                           (const void*)hbci_merge_rows_kernel<1024, kShortRow, kLongRow>})
+                           (const void*)hbci_merge_rows_kernel<1024, kMidRow, kLongRow>})
       if (e == hipSuccess) e = allow_max_lds(fn);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(hbci_prep_kernel, dim3(1), dim3(256), 0, st, I.h, I.eri, I.n_orb, I.act, I.k, I.core,
@@ -1597,7 +1599,12 @@ struct Run {
                        O.old, O.moved, n_rep, at<int64_t>(L.ptr[nxt]), at<int32_t>(L.col[nxt]),
                        at<double>(L.val[nxt]));
     if (longest > kShortRow)
-      hipLaunchKernelGGL((hbci_merge_rows_kernel<1024, kShortRow, kLongRow>), dim3(blocks(n_rep, 1, 8192)), dim3(1024),
+      hipLaunchKernelGGL((hbci_merge_rows_kernel<256, kShortRow, kMidRow>), dim3(blocks(n_rep, 1, 8192)), dim3(256),
+                         kMidRow * 12, st, at<int64_t>(L.ptr[cur]), at<int32_t>(L.col[cur]), at<double>(L.val[cur]),
+                         O.old, O.moved, n_rep, at<int64_t>(L.ptr[nxt]), at<int32_t>(L.col[nxt]),
+                         at<double>(L.val[nxt]));
+    if (longest > kMidRow)
+      hipLaunchKernelGGL((hbci_merge_rows_kernel<1024, kMidRow, kLongRow>), dim3(blocks(n_rep, 1, 8192)), dim3(1024),
                          kLongRow * 12, st, at<int64_t>(L.ptr[cur]), at<int32_t>(L.col[cur]), at<double>(L.val[cur]),
                          O.old, O.moved, n_rep, at<int64_t>(L.ptr[nxt]), at<int32_t>(L.col[nxt]),
                          at<double>(L.val[nxt]));
@@ -1609,7 +1616,7 @@ struct Run {
 
   template <int M>
   void dav_step(const DavSpace& a, int m, bool check_only) {
-    const dim3 g(blocks(a.n, 256, kVecBlocks)), b(256);
+    const dim3 g(blocks(a.n, kVecThreads, kVecBlocks)), b(kVecThreads);
     hipLaunchKernelGGL(hbci_dav_residual_kernel<M>, g, b, 0, st, a, m, o.r_tol);
     if (check_only) return;
     hipLaunchKernelGGL((hbci_dav_orth_kernel<M, false>), g, b, 0, st, a, m);
@@ -1643,7 +1650,7 @@ struct Run {
       hipLaunchKernelGGL(hbci_dav_block_kernel, dim3(nb), dim3(1024), kBlockLds, st, a, m);
     else
       hipLaunchKernelGGL(hbci_dav_product_kernel, dim3(nb), dim3(1024), 0, st, a, m);
-    hipLaunchKernelGGL(hbci_dav_subspace_kernel, dim3(1), dim3(256), 0, st, a, nb, m, o.m_max);
+    hipLaunchKernelGGL(hbci_dav_subspace_kernel, dim3(1), dim3(1024), 0, st, a, nb, m, o.m_max);
   }
 
   // Davidson for the lowest root over the n keys (n_rep pairs) from the unit,

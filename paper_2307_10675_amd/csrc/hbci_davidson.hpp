@@ -23,7 +23,8 @@ namespace {
 constexpr int kMaxM = 16;       // largest Davidson subspace
 constexpr int kKeepRitz = 4;    // Ritz vectors kept at a Davidson restart
 constexpr int kParts = kMaxM + 1;
-constexpr int kVecBlocks = 512;   // most workgroups of a pass over the basis (256 threads)
+constexpr int kVecBlocks = 512;   // most workgroups of a pass over the basis
+constexpr int kVecThreads = 512;  // one entry a thread up to 262144 pairs: residual 15.6 -> 10.7 us at 158104 (256 threads: two rounds)
 constexpr int kRowBlocks = 512;   // most workgroups of the product (1024 threads)
 
 __host__ __device__ inline int kept_ritz(int m_max) { return m_max / 2 < kKeepRitz ? m_max / 2 : kKeepRitz; }
@@ -118,7 +119,7 @@ __device__ __forceinline__ void dav_totals(const double* part, int nv, int strid
   __syncthreads();
 }
 
-// part[j][block] = sum over the block of v[j], j < nv <= NV (256 threads)
+// part[j][block] = sum over the block of v[j], j < nv <= NV
 template <int NV>
 __device__ __forceinline__ void dav_partials(const double (&v)[NV], int nv, double* red, double* part) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -156,8 +157,8 @@ __global__ void hbci_dav_start_kernel(DavSpace a) {
 // Residual of the Ritz pair, the correction t into the slot of vector m, and
 // the overlaps of t with the basis.
 template <int M>
-__global__ void __launch_bounds__(256) hbci_dav_residual_kernel(DavSpace a, int m, double r_tol) {
-  __shared__ double red[4 * (M + 1)], tot[M + 1];
+__global__ void __launch_bounds__(kVecThreads) hbci_dav_residual_kernel(DavSpace a, int m, double r_tol) {
+  __shared__ double red[kVecThreads / 64 * (M + 1)], tot[M + 1];
   __shared__ int flag;
   DavCtl* c = a.ctl;
   if (c->done) return;
@@ -201,9 +202,9 @@ __global__ void __launch_bounds__(256) hbci_dav_residual_kernel(DavSpace a, int 
 // t -= sum_j d_j V_j; with LAST the second pass, which leaves the new basis
 // vector and spreads it to x, else the overlaps for that pass.
 template <int M, bool LAST>
-__global__ void __launch_bounds__(256) hbci_dav_orth_kernel(DavSpace a, int m) {
+__global__ void __launch_bounds__(kVecThreads) hbci_dav_orth_kernel(DavSpace a, int m) {
   constexpr int NV = LAST ? 1 : M;
-  __shared__ double red[4 * NV], tot[NV];
+  __shared__ double red[kVecThreads / 64 * NV], tot[NV];
   __shared__ int flag;
   DavCtl* c = a.ctl;
   if (c->done) return;
@@ -539,20 +540,22 @@ __global__ void __launch_bounds__(1024) hbci_dav_block_kernel(DavSpace a, int m)
 // and its lowest pair (at m + 1 = m_max all pairs: the next launch restarts).
 // A launch of its own: as the end of the product it took that kernel past 64
 // VGPRs, and with them half of its waves.
-__global__ void __launch_bounds__(256) hbci_dav_subspace_kernel(DavSpace a, int nblk, int m, int m_max) {
+__global__ void __launch_bounds__(1024) hbci_dav_subspace_kernel(DavSpace a, int nblk, int m, int m_max) {
   __shared__ double G[256], Q[256], ev[16], yv[16], tot[kMaxM], th;
   __shared__ int perm[16], large;
   DavCtl* c = a.ctl;
   if (c->done) return;
   dav_totals(a.part, m + 1, kRowBlocks, nblk, tot);
   const int n = m + 1, tid = threadIdx.x, lane = tid & 63;
-  double h = c->H[tid];
-  const int r = tid >> 4, q = tid & 15, j = r == m ? q : r;
-  if ((r == m || q == m) && r <= m && q <= m) {
-    h = c->f[j] * c->f[m] * tot[j];
-    c->H[tid] = h;
+  if (tid < 256) {
+    double h = c->H[tid];
+    const int r = tid >> 4, q = tid & 15, j = r == m ? q : r;
+    if ((r == m || q == m) && r <= m && q <= m) {
+      h = c->f[j] * c->f[m] * tot[j];
+      c->H[tid] = h;
+    }
+    G[tid] = h;
   }
-  G[tid] = h;
   if (tid < 16) yv[tid] = c->y[tid];
   __syncthreads();
   const bool restart = n == m_max;
@@ -579,7 +582,7 @@ __global__ void __launch_bounds__(256) hbci_dav_subspace_kernel(DavSpace a, int 
       c->Y[tid] = j < keep ? Q[l * 16 + perm[j]] * c->f[l] : 0.0;
     }
     __syncthreads();
-    c->H[tid] = ((tid >> 4) == (tid & 15) && (tid & 15) < keep) ? ev[tid & 15] : 0.0;
+    if (tid < 256) c->H[tid] = ((tid >> 4) == (tid & 15) && (tid & 15) < keep) ? ev[tid & 15] : 0.0;
     if (tid < kMaxM) {
       c->f[tid] = 1.0;
       c->y[tid] = c->yf[tid] = tid == 0 ? 1.0 : 0.0;
