@@ -322,11 +322,17 @@ __device__ __forceinline__ void sigma_scatter(const IncDev& d, const Lds& L, con
   const int16_t* pt = (const int16_t*)L.ptab;  // [a][q]: J | neg << 15, J = n: none
   double* const colb = L.cp + wave * (2 * CE);
   double* const scol = colb + CE;
+  // At 7 and 8 orbitals the solver's loop has no registers for the addresses of
+  // V's operands: hoisted out of it they are spilled, and reloading them one by
+  // one serialises the loads; found anew in each sigma they are all in flight
+  // (8o8e in a full launch 198k -> 194k cycles).
+  int fl = lane;
+  if constexpr (K > 6) asm volatile("" : "+v"(fl));
   double afr[MTA][KS];
 #pragma unroll
   for (int m = 0; m < MTA; ++m)
 #pragma unroll
-    for (int s = 0; s < KS; ++s) afr[m][s] = fragment<double, K>(V, m, s, lane);
+    for (int s = 0; s < KS; ++s) afr[m][s] = fragment<double, K>(V, m, s, fl);
   // entry of (string 16 t + col, position 4 s + kq) in the column copy and the
   // accumulator, as an LDS byte offset, two a register: J, ld + J (negated),
   // or where there is no link one of 16 entries (zeros of the copy, dump of
