@@ -336,8 +336,10 @@ __device__ inline int lowest_pair(const double* G, int n, int p, double tp, cons
 // the rotations of its two planes formed by itself.
 // Pivots below 1e-15 ||A||_F are not rotated (FP64 rounding keeps
 // regenerating off-diagonal noise near 1e-16 ||A||); sweeps stop after one
-// whose squared pivots sum below 1e-16 ||A||_F^2 (the rotations leave 1e-7 of
-// each pivot, so the off-diagonal part is then at rounding level).  Executed by one
+// whose squared pivots sum below 1e-24 ||A||_F^2.  (Not at 1e-16: where
+// eigenvalues lie as close to each other as the pivots are large, the angles
+// of a sweep are not small and the off-diagonal part after it is of the size
+// of the pivots before it; up to 1e-8 ||A|| was left there.)  Executed by one
 // full wavefront, which orders its own LDS accesses, so no workgroup
 // barrier is needed.  Returns the sorted eigenvalues in evals, their
 // columns of Q in perm, and the lowest pair in theta / y.
@@ -383,12 +385,16 @@ __device__ inline void jacobi_warm(double* A, double* Q, int n, double* theta, d
       const int i0 = kr < N ? kr : 0, i1 = kr + 8 < N ? kr + 8 : 0;
       const double u0 = Q[i0 * 16 + p2], v0 = Q[i0 * 16 + q2], u1 = Q[i1 * 16 + p2], v1 = Q[i1 * 16 + q2];
       auto rotation = [&](double app, double aqq, double apq, double& c, double& sn) {
-        // the tangent only steers the convergence, so single precision does
-        // (it leaves 1e-7 of the pivot for the next sweep); c and s are
-        // normalised to FP64 rounding, which keeps Q orthogonal
-        const float tau = (float)((aqq - app) * 0.5 * __builtin_amdgcn_rcp(apq));
+        // tangent of the angle in single precision, then one Newton step on
+        // apq (t^2 - 1) + (aqq - app) t = 0, whose slope keeps its sign there:
+        // 1e-14 of the pivot is left; c and s are normalised to FP64 rounding,
+        // which keeps Q orthogonal
+        const double d = aqq - app;
+        const float tau = (float)(d * 0.5 * __builtin_amdgcn_rcp(apq));
         const float tf = __builtin_amdgcn_rcpf(fabsf(tau) + __builtin_amdgcn_sqrtf(fmaf(tau, tau, 1.0f)));
-        const double t = fabs(apq) > tol ? (double)(tau >= 0.0f ? tf : -tf) : 0.0;
+        double t = (double)(tau >= 0.0f ? tf : -tf);
+        t -= fma(apq, fma(t, t, -1.0), d * t) * __builtin_amdgcn_rcp(fma(2.0 * apq, t, d));
+        t = fabs(apq) > tol ? t : 0.0;
         const double h = fma(t, t, 1.0);
         c = __builtin_amdgcn_rsq(h);
         c = fma(0.5 * c, fma(-h * c, c, 1.0), c);
@@ -425,7 +431,7 @@ __device__ inline void jacobi_warm(double* A, double* Q, int n, double* theta, d
       __builtin_amdgcn_wave_barrier();
     }
     piv2 = wave_sum(piv2);
-    if (!(piv2 > 1e-16 * f2)) break;
+    if (!(piv2 > 1e-24 * f2)) break;
   }
   __builtin_amdgcn_wave_barrier();
   // eigenvalues in increasing order (ties by index): perm[i] is the column
