@@ -238,7 +238,10 @@ ifci_status ifci_sigma_sector(ifci_plan_t plan, int64_t inc, const double* c, do
  * [count] or NULL -- increments whose byte is nonzero are abandoned after one
  * iteration and reported EVICTED (failure injection); iters_out/resid_out:
  * device [count] or NULL.  Converged vectors stay in the workspace for
- * ifci_vector and ifci_rdm.  Increments dropped by a screening mask
+ * ifci_vector and ifci_rdm.  A solve of device-wide increments made again
+ * gives the same bits at odd orbital counts and away from half filling;
+ * half-filled ones of 10 to 16 orbitals agree to rounding (their products add
+ * in no fixed order).  Increments dropped by a screening mask
  * (ifci_screen) are not solved: status IFCI_INC_SCREENED, energy NaN.
  * Increments that fit on chip run in one launch of the batched solver; the
  * others (more than 8 active orbitals) run in the batched device-wide

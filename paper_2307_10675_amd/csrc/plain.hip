@@ -67,7 +67,7 @@ static hipError_t launch_column_k(const IncDev& d, const double* V, const int32_
   else
     hipLaunchKernelGGL((expand_sym_kernel<T>), dim3(std::min(2048u, tiles)), dim3(256), 0, st, d, c, cf);
   hipLaunchKernelGGL((sigma_column_kernel<T, K>), dim3(parts * n), dim3(col_threads<T>()), (unsigned)SH::lds, st, n,
-                     ptab, ptabT, (const T*)cf, cf_step, (const T*)vfg, Sm);
+                     ptab, ptabT, (const T*)cf, cf_step, (const T*)vfg, Sm, mode == 0 || column_ordered(d));
   if (mode == 0)
     hipLaunchKernelGGL(column_sum_kernel, dim3(tiles), dim3(256), 0, st, n, Sm, sig);
   else

@@ -9,8 +9,9 @@
 //   gather:    sigma_I = sum over links of alpha(I) of sign E[Q][(J, beta)]
 //                      + sum over links of beta(I) of sign E[Q][(alpha, J)].
 // For symmetric c, E is symmetric in its two string indices and the beta
-// gather is the transpose of the alpha gather.  Half-filled increments of 10
-// to 16 orbitals take the fused column form below instead.
+// gather is the transpose of the alpha gather.  Increments of 9 to 14 orbitals,
+// and half-filled ones of 16 for symmetric c, take the fused column form below
+// instead.
 #pragma once
 
 #include <type_traits>
@@ -187,13 +188,21 @@ __global__ void __launch_bounds__(kWideThreads) gather_sym_kernel(IncDev d, cons
 // table rows come from L2.  Where LDS allows, the column copy is stored with
 // its negation and S with a negated twin, so one table index J + neg (n + 1)
 // addresses both the signed C value and the signed accumulator slot (S is
-// the first half minus the second).  FP64 sums of the FP32 products make S
-// practically independent of the atomic order.
+// the first half minus the second).  The order of those additions is that in
+// which the waves come to them, unless the tiles scatter in turn
+// (column_ordered); FP64 sums of FP32 products hardly depend on it, sums of
+// FP64 products do to rounding.
 // Both precisions run three waves per SIMD (more waves hide the loads and
 // VALU work beside the MFMAs; four leave too few registers; FP64 with three
 // instead of two: 14o14e 5.50 -> 5.29 ms).
 template <typename T>
 constexpr int col_threads() { return 768; }
+
+// Whether the tiles of a column scatter in turn, which makes a product of
+// symmetric vectors the same to the bit each time.  Half-filled increments of
+// 10, 12 and 14 orbitals never were (in turn 14o14e takes 6.9 ms instead of
+// 5.2); the other shapes, and any product of vectors of no symmetry, are.
+__host__ __device__ inline bool column_ordered(const IncDev& d) { return 2 * d.na != d.k; }
 
 template <typename T, int K>
 struct ColShape {
@@ -303,10 +312,10 @@ __global__ void __launch_bounds__(256) col_frag_kernel(const double* __restrict_
 // Column b of the product (see above); `lds` is the workgroup's dynamic
 // LDS.  load_frag: copy the A-fragment image vfg into LDS first (it stays
 // there for later columns of the same increment).  ordered: the tiles scatter
-// in turn, so that the sums do not depend on how the waves are scheduled (for
-// vectors of any symmetry, whose product has always been reproducible to the
-// bit; a wave only waits for tiles of the waves beside it, which are resident
-// with it; for a symmetric vector it would cost 14o14e 5.2 -> 6.9 ms).  Ends with a barrier, so the next column may reuse the LDS at once.
+// in turn, so that the sums do not depend on how the waves are scheduled
+// (column_ordered; a wave only waits for tiles of the waves beside it, which
+// are resident with it).  Ends with a barrier, so the next column may reuse
+// the LDS at once.
 template <typename T, int K>
 __device__ __forceinline__ void column_body(int N, const int32_t* __restrict__ ptab, const int16_t* __restrict__ ptabT,
                                             const T* __restrict__ cf, const T* __restrict__ vfg,
@@ -431,12 +440,12 @@ __global__ void __launch_bounds__(col_threads<T>()) sigma_column_kernel(int n, c
                                                                    const int16_t* __restrict__ ptabT,
                                                                    const T* __restrict__ cf, int64_t cf_step,
                                                                    const T* __restrict__ vfg,
-                                                                   double* __restrict__ Sm) {
+                                                                   double* __restrict__ Sm, bool ordered) {
   // block n + b: column b of a second matrix, cf_step entries after the first
   extern __shared__ __align__(16) char lds[];
   const int part = (int)blockIdx.x >= n ? 1 : 0;
   column_body<T, K>(n, ptab, ptabT, cf + part * cf_step, vfg, Sm + (int64_t)part * n * n, (int)blockIdx.x - part * n,
-                    lds, true, (int)gridDim.x > n);
+                    lds, true, ordered);
 }
 
 // 16 orbitals (12,870 strings, 136 pairs) do not fit that LDS layout.  The

@@ -268,7 +268,7 @@ __global__ void __launch_bounds__((wide_col_threads<T, K>()), (wide_col_waves<T,
     const ColScratch cs = col_scratch(w->d);
     column_body<T, K>(n, w->tabs + w->d.pair_off, (const int16_t*)(w->tabs + w->d.pairT_off), (const T*)(w->sc + cs.cf),
                       (const T*)(w->sc + (sizeof(T) == 4 ? cs.vf32 : cs.vf64)), w->sc + cs.sm, b, lds,
-                      item != prev, false);
+                      item != prev, column_ordered(w->d));
     prev = item;
   }
 }
