@@ -336,10 +336,11 @@ __device__ inline int lowest_pair(const double* G, int n, int p, double tp, cons
 // the rotations of its two planes formed by itself.
 // Pivots below 1e-15 ||A||_F are not rotated (FP64 rounding keeps
 // regenerating off-diagonal noise near 1e-16 ||A||); sweeps stop after one
-// whose squared pivots sum below 1e-24 ||A||_F^2.  (Not at 1e-16: where
-// eigenvalues lie as close to each other as the pivots are large, the angles
-// of a sweep are not small and the off-diagonal part after it is of the size
-// of the pivots before it; up to 1e-8 ||A|| was left there.)  Executed by one
+// whose pivots times angles (the sizes of both sums of squares) are below 1e-18
+// ||A||_F: a sweep leaves no more than that of the off-diagonal part.  (The
+// pivots alone do not tell: where eigenvalues lie as close to each other as the
+// pivots are large, the angles are not small and what is left is of the
+// pivots' own size.)  Executed by one
 // full wavefront, which orders its own LDS accesses, so no workgroup
 // barrier is needed.  Returns the sorted eigenvalues in evals, their
 // columns of Q in perm, and the lowest pair in theta / y.
@@ -371,7 +372,7 @@ __device__ inline void jacobi_warm(double* A, double* Q, int n, double* theta, d
   auto other = [&](int k) { return k == 0 ? 0 : m - k; };
   auto next = [&](int v) { return v + 1 == m ? 0 : v + 1; };
   for (int sweep = 0; sweep < 12 && N > 1; ++sweep) {
-    double piv2 = 0.0;
+    double piv2 = 0.0, ang2 = 0.0;
     int x1 = first(kr < H ? kr : 0), y1 = other(kr < H ? kr : 0);
     int x2 = first(kc < H ? kc : 0), y2 = other(kc < H ? kc : 0);
     for (int s = 0; s < m; ++s) {
@@ -404,7 +405,10 @@ __device__ inline void jacobi_warm(double* A, double* Q, int n, double* theta, d
       double c1, s1, c2, s2;
       rotation(pp1, qq1, pq1, c1, s1);
       rotation(pp2, qq2, pq2, c2, s2);
-      if (kr == 0 && kc < H) piv2 += pq2 * pq2;
+      if (kr == 0 && kc < H) {
+        piv2 += pq2 * pq2;
+        ang2 += s2 * s2;
+      }
       if (kr > 0) x1 = next(x1);
       y1 = next(y1);
       if (kc > 0) x2 = next(x2);
@@ -430,8 +434,7 @@ __device__ inline void jacobi_warm(double* A, double* Q, int n, double* theta, d
       }
       __builtin_amdgcn_wave_barrier();
     }
-    piv2 = wave_sum(piv2);
-    if (!(piv2 > 1e-24 * f2)) break;
+    if (!(wave_sum(piv2) * wave_sum(ang2) > 1e-36 * f2)) break;
   }
   __builtin_amdgcn_wave_barrier();
   // eigenvalues in increasing order (ties by index): perm[i] is the column
