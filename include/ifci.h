@@ -269,6 +269,8 @@ ifci_status ifci_davidson(ifci_plan_t plan, int64_t first, int64_t count, double
  * Stream order and return as in ifci_davidson; converged vectors stay in
  * each plan's workspace.  The first plan keeps the solve's control block and
  * work list (device memory it allocates on first use and grows as needed).
+ * Where every increment fits on chip the call can be captured into a graph,
+ * once a call of the same plans has allocated that memory.
  * IFCI_ERR_UNSUPPORTED for a plan with a screening mask (ifci_screen). */
 ifci_status ifci_davidson_group(const ifci_plan_t* plans, int32_t n_plans, double* const* e_out,
                                 int32_t* const* status_out, int32_t* const* iters_out,

@@ -102,6 +102,9 @@ void free_device(ifci_plan_s* P) {
   P->group_ctl_bytes = 0;
   free_one(P->group_jobs);
   P->group_jobs_bytes = 0;
+  P->group_list.clear();
+  for (char*& b : P->group_captured) free_one(b);
+  P->group_captured.clear();
   release_in_flight(P, true);
   if (P->capture_stream) (void)hipStreamDestroy(P->capture_stream);
   P->capture_stream = nullptr;
@@ -470,24 +473,53 @@ ifci_status launch_on_chip_group(ifci_plan_s* owner, const std::vector<WideMembe
   std::stable_sort(work.begin(), work.end(), [&](const int2& a, const int2& b) {
     return of_job[a.x]->P->inc[a.y].n_det > of_job[b.x]->P->inc[b.y].n_det;
   });
-  release_in_flight(owner, false);
   const int64_t at_work = ((int64_t)jobs.size() * sizeof(SolveArgs) + 255) / 256 * 256;
   const int64_t need = at_work + (int64_t)work.size() * sizeof(int2);
-  ifci_status s = grow(&owner->group_jobs, &owner->group_jobs_bytes, need, st, "ifci_davidson_group work list");
-  if (s != IFCI_OK) return s;
-  ifci_plan_s::InFlight fl;  // keeps the host copies until their upload has run
-  const char* h_jobs = push_bytes(fl.host, jobs);
-  const char* h_work = push_bytes(fl.host, work);
-  HIP_TRY(hipMemcpyAsync(owner->group_jobs, h_jobs, jobs.size() * sizeof(SolveArgs), hipMemcpyHostToDevice, st),
-          "ifci_davidson_group upload");
-  HIP_TRY(hipMemcpyAsync(owner->group_jobs + at_work, h_work, work.size() * sizeof(int2), hipMemcpyHostToDevice, st),
-          "ifci_davidson_group upload");
-  HIP_TRY(hipEventCreateWithFlags(&fl.done, hipEventDisableTiming), "event");
-  const hipError_t re = hipEventRecord(fl.done, st);
-  owner->in_flight.push_back(std::move(fl));
-  HIP_TRY(re, "event");
-  HIP_TRY(launch_batched_group((const SolveArgs*)owner->group_jobs, (const int2*)(owner->group_jobs + at_work),
-                               (int)work.size(), owner->opt.max_space, lds, st),
+  std::vector<char> list(need, 0);
+  std::memcpy(list.data(), jobs.data(), jobs.size() * sizeof(SolveArgs));
+  std::memcpy(list.data() + at_work, work.data(), work.size() * sizeof(int2));
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  const bool captured = hipStreamIsCapturing(st, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone;
+  if (need > owner->group_jobs_bytes) {
+    if (captured) {
+      set_error("ifci_davidson_group: the first call of a group allocates; make it before capturing one");
+      return IFCI_ERR_STATE;
+    }
+    const int64_t bytes = std::max(need, 2 * owner->group_jobs_bytes);
+    owner->group_list.clear();
+    ifci_status s = grow(&owner->group_jobs, &owner->group_jobs_bytes, bytes, st, "ifci_davidson_group work list");
+    if (s != IFCI_OK) return s;
+    // a smaller buffer of captured calls stays, graphs hold it
+    owner->group_captured.reserve(owner->group_captured.size() + 1);
+    char* buf = nullptr;
+    const hipError_t e = hipMalloc((void**)&buf, bytes);
+    if (e != hipSuccess) {
+      free_one(owner->group_jobs);
+      owner->group_jobs_bytes = 0;
+      return dev_err(e, "ifci_davidson_group work list");
+    }
+    owner->group_captured.push_back(buf);
+  }
+  char* const buf = captured ? owner->group_captured.back() : owner->group_jobs;
+  if (captured) {
+    // by launches alone: a graph must not read this call's host memory, nor
+    // what a later call leaves in a buffer that both use
+    HIP_TRY(launch_store(buf, list.data(), need, st), "ifci_davidson_group store");
+  } else if (list != owner->group_list) {
+    release_in_flight(owner, false);
+    owner->group_list.clear();
+    ifci_plan_s::InFlight fl;  // keeps the host copy until its upload has run
+    const char* h = push_bytes(fl.host, list);
+    HIP_TRY(hipEventCreateWithFlags(&fl.done, hipEventDisableTiming), "event");
+    const hipError_t ue = hipMemcpyAsync(buf, h, need, hipMemcpyHostToDevice, st);
+    const hipError_t re = hipEventRecord(fl.done, st);
+    owner->in_flight.push_back(std::move(fl));
+    HIP_TRY(ue, "ifci_davidson_group upload");
+    HIP_TRY(re, "event");
+    owner->group_list = std::move(list);
+  }
+  HIP_TRY(launch_batched_group((const SolveArgs*)buf, (const int2*)(buf + at_work), (int)work.size(),
+                               owner->opt.max_space, lds, st),
           "ifci_davidson_group batched");
   return IFCI_OK;
 }

@@ -22,6 +22,8 @@ int64_t batched_lds_want(int k, int n_str, int n_link);
 hipError_t launch_batched(const SolveArgs& A, int lds_bytes, hipStream_t st);
 // The same for the increments of several plans: work (device) holds pairs
 // (index into jobs, increment of that job), count of them.
+// (bytes of src, a multiple of 4, to dst in device memory by kernel arguments)
+hipError_t launch_store(void* dst, const void* src, int64_t bytes, hipStream_t st);
 hipError_t launch_batched_group(const SolveArgs* jobs, const int2* work, int count, int max_space, int lds_bytes,
                                 hipStream_t st);
 hipError_t launch_sigma_one(const IncDev* incs, int inc, const double* ints, const int32_t* tables,

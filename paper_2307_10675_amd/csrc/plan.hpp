@@ -58,8 +58,13 @@ struct ifci_plan_s {
   std::vector<InFlight> in_flight;
   char* group_ctl = nullptr;  // control block of solves across several plans (grown on demand)
   int64_t group_ctl_bytes = 0;
-  char* group_jobs = nullptr;  // arguments and work list of on-chip solves across several plans
+  // arguments and work list of on-chip solves across several plans: the
+  // device's and what it holds, and those that captured calls write (the last
+  // one; the others are as small, and held by graphs)
+  char* group_jobs = nullptr;
   int64_t group_jobs_bytes = 0;
+  std::vector<char> group_list;
+  std::vector<char*> group_captured;
   // device
   ifci::IncDev* d_inc = nullptr;
   int32_t* d_orbs = nullptr;
