@@ -42,7 +42,8 @@ struct DavState {
   int plarge;  // largest component of y (for the next subspace solve)
   int fresh;   // V[m] is in place (start of a stage), not to be formed from t
   int count;   // blocks of the current pass that are done (last_block)
-  int pad[2];
+  int exhausted;  // the last correction lay in the span of the basis: V[m] is zero
+  int pad;
   int perm[16];
 };
 
@@ -53,6 +54,7 @@ struct SmallG {
 };
 
 // action codes written by the residual test (small_A)
+// (kActMaxIter: out of iterations or of directions)
 enum { kActContinue = 0, kActDone = 1, kActSwitch = 2, kActMaxIter = 3, kActEvicted = 4 };
 
 constexpr int kPartBlocks = 1024;
@@ -310,6 +312,7 @@ __device__ inline void small_switch(DavState* S) {
     S->m = 0;
     S->plarge = 0;
     S->fresh = 1;
+    S->exhausted = 0;
   }
 }
 
@@ -331,10 +334,11 @@ __device__ __forceinline__ double advance_value(const double* Vb, int64_t st, co
 // New column of the Rayleigh matrix from the partials of op_dots, then its
 // lowest eigenpair (lowest_pair; a full Jacobi decomposition at a restart or
 // where that does not apply); counts the iteration and decides whether the
-// next orthogonalisation is preceded by a thick restart.
+// next orthogonalisation is preceded by a thick restart.  With a zero V[m] the
+// pair is that of the basis before it.
 __device__ inline void small_G(DavState* S, const double* part, int nblk, int mmax, SmallG* sh, double* red) {
   const int m = S->m, n = m + 1, lane = threadIdx.x;
-  const bool restart = n == mmax;
+  const bool exhausted = S->exhausted != 0, restart = n == mmax && !exhausted;
   sh->G[threadIdx.x] = S->G[threadIdx.x];
   if (lane < kMaxSpace) sh->y[lane] = S->y[lane];
   reduce_parts(part, nblk, n, sh->g, red);
@@ -347,7 +351,17 @@ __device__ inline void small_G(DavState* S, const double* part, int nblk, int mm
   }
   __syncthreads();
   if (threadIdx.x < 64) {
-    int pn = restart ? -1 : lowest_pair(sh->G, n, S->plarge, S->theta, sh->y, &sh->theta, sh->y);
+    int pn;
+    if (exhausted) {
+      pn = S->plarge;
+      if (lane == 0) {
+        sh->theta = S->theta;
+        sh->y[m] = 0.0;
+      }
+      __builtin_amdgcn_wave_barrier();
+    } else {
+      pn = restart ? -1 : lowest_pair(sh->G, n, S->plarge, S->theta, sh->y, &sh->theta, sh->y);
+    }
     if (pn < 0) {
       jacobi_lowest(sh->G, sh->Q, n, &sh->theta, sh->y, sh->ev, sh->perm);
       for (int i = lane; i < 256; i += 64) S->Q[i] = sh->Q[i];
@@ -372,7 +386,9 @@ __device__ inline void small_G(DavState* S, const double* part, int nblk, int mm
 }
 
 // Residual test on the partials of op_passA: decides the action (continue,
-// done, switch to the FP64 stage, out of iterations, evicted).  Where the
+// done, switch to the FP64 stage, out of iterations, evicted).  Without a
+// direction left the FP32 stage passes on to the FP64 one, and that one ends.
+// Where the
 // iteration continues through a thick restart, the kept Ritz vectors become
 // the basis (pass B writes them): their Ritz values are the diagonal of G, and
 // cf is re-expressed in them.
@@ -387,14 +403,14 @@ __device__ inline void small_A(DavState* S, const double* part, int nblk, double
   if (evict) {
     action = kActEvicted;
     status = IFCI_INC_EVICTED;
-  } else if (resid <= tol) {
+  } else if (resid <= tol || (S->exhausted && S->phase == 32)) {
     if (S->phase == 32) {
       action = (S->iters >= max_iter) ? kActMaxIter : kActSwitch;
     } else {
       action = kActDone;
       status = IFCI_INC_DONE;
     }
-  } else if (S->iters >= max_iter) {
+  } else if (S->iters >= max_iter || S->exhausted) {
     action = kActMaxIter;
   }
   const bool restart = action == kActContinue && S->restart;
@@ -424,7 +440,10 @@ __device__ inline void small_A(DavState* S, const double* part, int nblk, double
 
 // Norm of the correction after the first pass, and whether a second one is
 // due: it is when less than half of the squared norm is left, and the squared
-// norm after it is |t|^2 - |V^T t|^2 (V orthonormal).
+// norm after it is |t|^2 - |V^T t|^2 (V orthonormal).  The second pass takes
+// away rounding of the first: where it would take most of what is left, the
+// correction lay in the span of the basis, no digit of the difference is sure,
+// and there is no direction to go on with.
 __device__ inline void small_B(DavState* S, const double* part, int nblk, double* v, double* red) {
   const int mb = S->mb;
   reduce_parts(part, nblk, mb + 2, v, red);
@@ -433,12 +452,14 @@ __device__ inline void small_B(DavState* S, const double* part, int nblk, double
     const bool reorth = tt < 0.5 * S->tt0;
     if (reorth)
       for (int j = 0; j <= mb; ++j) tt -= v[1 + j] * v[1 + j];
+    const bool exhausted = !(tt > (reorth ? 0.1 * v[0] : 0.0));
     for (int j = 0; j < 16; ++j) S->c2[j] = (j <= mb) ? v[1 + j] : 0.0;
-    S->reorth = reorth;
+    S->reorth = reorth && !exhausted;
     S->tt = tt;
-    S->inv = tt > 0.0 ? 1.0 / sqrt(tt) : 0.0;
+    S->inv = exhausted ? 0.0 : 1.0 / sqrt(tt);
     S->m = mb + 1;
     S->fresh = 0;
+    S->exhausted = exhausted;
   }
 }
 

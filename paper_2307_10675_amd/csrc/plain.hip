@@ -230,6 +230,7 @@ __global__ void init_state_kernel(DavState* S, const double* part, int nblk, dou
     S->plarge = 0;
     S->fresh = 1;
     S->count = 0;
+    S->exhausted = 0;
     S->theta = 0.0;
     S->resid = 1e300;
   }

@@ -119,6 +119,7 @@ __global__ void __launch_bounds__(64) wb_init_kernel(WideItem* const* it, int n,
       S->plarge = 0;
       S->fresh = 1;
       S->count = 0;
+      S->exhausted = 0;
       S->theta = 0.0;
       S->resid = 1e300;
       S->alive = 1;
