@@ -193,10 +193,9 @@ ifci_status ifci_set_integrals(ifci_plan_t plan, const double* h, const double* 
  * IFCI_FP64 or IFCI_MIXED (FP32 arithmetic, results widened to FP64).
  * Uses the workspace; c and sigma must not alias.  At 9 to 14 orbitals the
  * fused column kernel runs on c and on its transpose (E never leaves LDS);
- * elsewhere E (npair x n_det) is materialised, and where the plan's workspace
- * is sized only for the column path (half-filled 16-orbital increments, 180
- * GB of E otherwise) the call returns IFCI_ERR_UNSUPPORTED: use
- * ifci_sigma_sector there. */
+ * elsewhere E (npair x n_det) is materialised, except for half-filled
+ * 16-orbital increments (180 GB of E), where the call returns
+ * IFCI_ERR_UNSUPPORTED: use ifci_sigma_sector there. */
 ifci_status ifci_sigma(ifci_plan_t plan, int64_t inc, const double* c, double* sigma,
                        int32_t precision, ifci_stream_t stream);
 

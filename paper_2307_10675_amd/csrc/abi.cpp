@@ -782,9 +782,9 @@ ifci_status ifci_sigma(ifci_plan_t p, int64_t inc, const double* c, double* sigm
   ifci_status s = need_ints(p);
   if (s != IFCI_OK) return s;
   const IncDev& d = p->inc[inc];
-  if (d.npair * d.n_det > p->E_doubles) {
-    set_error("ifci_sigma: the general product of this increment needs npair x n_det scratch "
-              "(use ifci_sigma_sector for symmetric vectors)");
+  if (!sigma_general_supported(d)) {
+    set_error("ifci_sigma: half-filled 16-orbital increments have the product of symmetric vectors only "
+              "(use ifci_sigma_sector)");
     return IFCI_ERR_UNSUPPORTED;
   }
   DeviceGuard g(p->device);

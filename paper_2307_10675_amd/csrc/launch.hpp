@@ -34,10 +34,11 @@ hipError_t launch_sigma_one(const IncDev* incs, int inc, const double* ints, con
 // vectors, any c.  mode 1: c and sigma packed scaled symmetric vectors.
 // Increments of 9 to 14 orbitals (mode 1: and half-filled 16) take the fused
 // column kernel (sigma_column_supported), others the materialised E.  `E` is
-// scratch: npair x n_det values, or sigma_column_ws_doubles(d, 2 in mode 0).
+// scratch of sigma_ws_doubles(d).
 bool sigma_column_supported(const IncDev& d);
 bool sigma_sector_shape(const IncDev& d);  // shapes of ifci_sigma_sector above 8 orbitals
-int64_t sigma_column_ws_doubles(const IncDev& d, int parts);  // workspace of the column path
+bool sigma_general_supported(const IncDev& d);  // products of vectors of any symmetry (mode 0)
+int64_t sigma_ws_doubles(const IncDev& d);  // scratch of a product in any mode d has
 // The static scratch array (plain.hip): its device address on the current
 // device (looked up once per device), kStaticScratchDoubles doubles.
 constexpr int64_t kStaticScratchDoubles = (int64_t)4 << 20;  // 32 MiB

@@ -36,10 +36,18 @@ bool sigma_sector_shape(const IncDev& d) {
 // Workspace doubles of the column path (full C of either precision, S, the
 // fragment image, with 256-byte alignment of each); `parts` matrices and S.
 static int64_t up32(int64_t x) { return (x + 31) / 32 * 32; }
-int64_t sigma_column_ws_doubles(const IncDev& d, int parts) {
+static int64_t sigma_column_ws_doubles(const IncDev& d, int parts) {
   const int64_t n = d.n_str;
   const int64_t np = (int64_t)d.k * (d.k + 1) / 2, mt = (np + 15) / 16, ks = (np + 3) / 4;
   return parts * (up32((n + 1) * n + 16) + up32(n * n)) + up32(mt * (ks + 1) * 64) + 64;
+}
+
+// 16 orbitals have the column form for symmetric vectors only, and no room for
+// E at half filling.
+bool sigma_general_supported(const IncDev& d) { return !sigma_column_supported(d) || d.k <= 14; }
+int64_t sigma_ws_doubles(const IncDev& d) {
+  if (sigma_column_supported(d)) return sigma_column_ws_doubles(d, sigma_general_supported(d) ? 2 : 1);
+  return (int64_t)d.npair * d.n_det;
 }
 
 // mode 0: c and sig full vectors, any c; mode 1: packed scaled symmetric ones.
@@ -162,8 +170,7 @@ hipError_t launch_sigma_wide(const IncDev& d, const IncDev*, int, const double* 
   const double* V = ints + d.int_off + int_block(d.k).V;
   const int32_t* ptab = tables + d.pair_off;
   const int32_t* links = tables + d.link_off;
-  // 16 orbitals have the column form for symmetric vectors only
-  if (sigma_column_supported(d) && (mode == 1 || d.k <= 14))
+  if (sigma_column_supported(d) && (mode == 1 || sigma_general_supported(d)))
     return launch_sigma_column(d, V, ptab, (const int16_t*)(tables + d.pairT_off), c, sig, E, precision, mode, shift,
                                st);
   const int64_t tiles = (d.n_det + 63) / 64;

@@ -318,17 +318,12 @@ ifci_status plan_build(ifci_plan_s* P, const ifci_problem* pr, const ifci_option
   off = align_up(off + P->ints_doubles * 8, A);
   P->off_dav = off;
   off = align_up(off + P->dav_doubles * 8, A);
-  // device-wide scratch: the materialised E (npair x n_det) where the
-  // general product may run; at 16 orbitals only the column path's (full C,
-  // S and fragments: 2.7 GB instead of 180 GB of E)
+  // device-wide scratch of one product: full C, S and fragments where the
+  // column kernels run (14o14e: 0.4 GB instead of 9.9 GB of E, 16o16e: 2.7 GB
+  // instead of 180), the materialised E elsewhere
   {
     int64_t need = 0;
-    for (const ifci::IncDev& d : P->inc) {
-      int64_t e = d.npair * d.n_det;
-      if (ifci::sigma_column_supported(d))
-        e = d.k > 14 ? ifci::sigma_column_ws_doubles(d, 1) : std::max(e, ifci::sigma_column_ws_doubles(d, 2));
-      need = std::max(need, e);
-    }
+    for (const ifci::IncDev& d : P->inc) need = std::max(need, ifci::sigma_ws_doubles(d));
     P->E_doubles = align_up(need, 32);
   }
   // device-wide solves run several increments at once when their scratch is
