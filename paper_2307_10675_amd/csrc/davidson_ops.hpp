@@ -26,7 +26,7 @@
 
 namespace ifci {
 
-constexpr int kNVmax = kMaxSpace + 3;
+constexpr int kNV = kMaxSpace + 2;  // values of a partial row
 
 // Solver state of one increment (device memory, one block of 4096 doubles).
 struct DavState {
@@ -36,7 +36,7 @@ struct DavState {
   double cf[16];   // V^T t (first orthogonalisation pass)
   double c2[16];   // V^T t (second pass)
   double ev[16];   // Ritz values, increasing
-  double theta, E0, resid, tt0, tt, dx, inv, ecore;
+  double theta, E0, resid, tt0, tt, inv, ecore;
   int m, phase, iters, status, restart, action, mb, reorth;
   int guess, keep, alive;
   int plarge;  // largest component of y (for the next subspace solve)
@@ -49,7 +49,7 @@ struct DavState {
 
 // LDS of small_G
 struct SmallG {
-  double g[kNVmax], G[256], Q[256], y[16], ev[16], theta;
+  double g[kNV], G[256], Q[256], y[16], ev[16], theta;
   int perm[16];
 };
 
@@ -58,7 +58,6 @@ struct SmallG {
 enum { kActContinue = 0, kActDone = 1, kActSwitch = 2, kActMaxIter = 3, kActEvicted = 4 };
 
 constexpr int kPartBlocks = 1024;
-constexpr int kNV = kNVmax;
 
 // Partial sums are written and read past the caches of an XCD, so that the
 // last block of the same launch sees those of all others.
@@ -177,7 +176,7 @@ __device__ inline void op_dots(const double* __restrict__ Vb, int64_t st, int m,
 
 // Ritz vector x = V y, residual r = S y - theta x, preconditioned
 // t = r / (theta - (H_II - E0)) (denominator clamped at 1e-8); stores x and
-// t; partials: r.r, t.t, x.t, then V_j . t (j <= m) from 3 on.  `ysh` is 16
+// t; partials: r.r, t.t, then V_j . t (j <= m) from 2 on.  `ysh` is 16
 // doubles of LDS.
 __device__ inline void op_passA(const DavState* __restrict__ S, const double* __restrict__ Vb,
                                 const double* __restrict__ Sb, int64_t st, const double* __restrict__ HD,
@@ -209,13 +208,12 @@ __device__ inline void op_passA(const DavState* __restrict__ S, const double* __
       const double t = r / den;
       acc[0] += r * r;
       acc[1] += t * t;
-      acc[2] += x * t;
 #pragma unroll
-      for (int j = 0; j < N; ++j) acc[3 + j] += v[j] * t;
+      for (int j = 0; j < N; ++j) acc[2 + j] += v[j] * t;
       T[i] = t;
       X[i] = x;
     }
-    block_partial_row(acc, m + 4, part_row, red);
+    block_partial_row(acc, m + 3, part_row, red);
   });
 }
 
@@ -395,7 +393,7 @@ __device__ inline void small_G(DavState* S, const double* part, int nblk, int mm
 __device__ inline void small_A(DavState* S, const double* part, int nblk, double tol32, double tol64, int max_iter,
                                int evict, double* v, double* red) {
   const int m = S->m;
-  reduce_parts(part, nblk, m + 4, v, red);
+  reduce_parts(part, nblk, m + 3, v, red);
   if (threadIdx.x >= 64) return;
   const double resid = sqrt(v[0]);
   const double tol = S->phase == 32 ? tol32 : tol64;
@@ -416,11 +414,11 @@ __device__ inline void small_A(DavState* S, const double* part, int nblk, double
   const bool restart = action == kActContinue && S->restart;
   const int keep = S->keep, j = threadIdx.x;
   if (j < 16) {
-    double c = j <= m ? v[3 + j] : 0.0;
+    double c = j <= m ? v[2 + j] : 0.0;
     if (restart) {
       c = 0.0;
       if (j < keep)
-        for (int l = 0; l <= m; ++l) c += S->Q[l * 16 + S->perm[j]] * v[3 + l];
+        for (int l = 0; l <= m; ++l) c += S->Q[l * 16 + S->perm[j]] * v[2 + l];
       S->y[j] = j == 0 ? 1.0 : 0.0;
     }
     S->cf[j] = c;
@@ -430,7 +428,6 @@ __device__ inline void small_A(DavState* S, const double* part, int nblk, double
   if (j == 0) {
     S->resid = resid;
     S->tt0 = v[1];
-    S->dx = v[2];
     S->mb = restart ? keep - 1 : m;
     if (restart) S->plarge = 0;
     if (status) S->status = status;
