@@ -336,7 +336,7 @@ __device__ inline int lowest_pair(const double* G, int n, int p, double tp, cons
 // the rotations of its two planes formed by itself.
 // Pivots below 1e-15 ||A||_F are not rotated (FP64 rounding keeps
 // regenerating off-diagonal noise near 1e-16 ||A||); sweeps stop after one
-// whose pivots times angles (the sizes of both sums of squares) are below 1e-18
+// whose pivots times angles (the sizes of both sums of squares) are below 1e-17
 // ||A||_F: a sweep leaves no more than that of the off-diagonal part.  (The
 // pivots alone do not tell: where eigenvalues lie as close to each other as the
 // pivots are large, the angles are not small and what is left is of the
@@ -387,14 +387,14 @@ __device__ inline void jacobi_warm(double* A, double* Q, int n, double* theta, d
       const double u0 = Q[i0 * 16 + p2], v0 = Q[i0 * 16 + q2], u1 = Q[i1 * 16 + p2], v1 = Q[i1 * 16 + q2];
       auto rotation = [&](double app, double aqq, double apq, double& c, double& sn) {
         // tangent of the angle in single precision, then one Newton step on
-        // apq (t^2 - 1) + (aqq - app) t = 0, whose slope keeps its sign there:
-        // 1e-14 of the pivot is left; c and s are normalised to FP64 rounding,
-        // which keeps Q orthogonal
-        const double d = aqq - app;
-        const float tau = (float)(d * 0.5 * __builtin_amdgcn_rcp(apq));
-        const float tf = __builtin_amdgcn_rcpf(fabsf(tau) + __builtin_amdgcn_sqrtf(fmaf(tau, tau, 1.0f)));
-        double t = (double)(tau >= 0.0f ? tf : -tf);
-        t -= fma(apq, fma(t, t, -1.0), d * t) * __builtin_amdgcn_rcp(fma(2.0 * apq, t, d));
+        // apq (t^2 - 1) + (aqq - app) t = 0, whose slope is 2 apq (t + tau) =
+        // +-2 apq sqrt(tau^2 + 1): 1e-14 of the pivot is left; c and s are
+        // normalised to FP64 rounding, which keeps Q orthogonal
+        const double d = aqq - app, ra = __builtin_amdgcn_rcp(apq);
+        const float tau = (float)(d * 0.5 * ra);
+        const float u = fmaf(tau, tau, 1.0f), ru = __builtin_amdgcn_rsqf(u);
+        double t = (double)copysignf(__builtin_amdgcn_rcpf(fmaf(u, ru, fabsf(tau))), tau);
+        t -= fma(apq, fma(t, t, -1.0), d * t) * (0.5 * ra * (double)copysignf(ru, tau));
         t = fabs(apq) > tol ? t : 0.0;
         const double h = fma(t, t, 1.0);
         c = __builtin_amdgcn_rsq(h);
@@ -434,7 +434,7 @@ __device__ inline void jacobi_warm(double* A, double* Q, int n, double* theta, d
       }
       __builtin_amdgcn_wave_barrier();
     }
-    if (!(wave_sum(piv2) * wave_sum(ang2) > 1e-36 * f2)) break;
+    if (!(wave_sum(piv2) * wave_sum(ang2) > 1e-34 * f2)) break;
   }
   __builtin_amdgcn_wave_barrier();
   // eigenvalues in increasing order (ties by index): perm[i] is the column
