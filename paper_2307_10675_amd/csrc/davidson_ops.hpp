@@ -70,7 +70,13 @@ __device__ __forceinline__ double part_load(const double* p) {
 
 // True in every thread of the block that comes last of the nb blocks of an
 // increment's pass (its partial rows, written by part_store, all visible);
-// resets the counter.  Every block of the pass calls it once.
+// resets the counter.  Every block of the pass calls it once.  The atomics are
+// relaxed, with no release and acquire between them (which would write back
+// and invalidate an L2 per block): what orders them is that an agent-scope
+// store of gfx950 is written through to memory and has reached it once vmcnt
+// is zero, and that an agent-scope load is not served from a cache that it
+// could be stale in.  So only data stored by part_store and loaded by part_load
+// passes from one block to another here.
 __device__ __forceinline__ bool last_block(int* count, int nb) {
   __shared__ int last;
   // each wave's stores have reached memory before its thread count passes on

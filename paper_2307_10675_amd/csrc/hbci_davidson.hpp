@@ -10,9 +10,9 @@
 // A step is five launches, none of which the host waits for: the small state
 // (subspace matrix, coefficients, the end of the loop) lives on the device and
 // is advanced by the block of a pass that ends last, from the partials of all
-// blocks.  (Driven from the host a step was 13 launches and 3 read-backs: 29 ms
-// of passes and most of 83 ms of waiting in a 376 ms solve of a 16-orbital
-// increment with 285020 keys; now 22 ms and 11 ms in 159 ms.)
+// blocks.  (Driven from the host a step was 13 launches and 3 read-backs: of
+// a solve of a 16-orbital increment with 285020 keys 29 ms were passes and most
+// of 83 ms waiting; now 22 and 11.)
 #pragma once
 
 #include "device_common.hpp"
@@ -72,9 +72,11 @@ struct DavSpace {
 // its row in the share.
 constexpr int kWinBits = 13, kWin = 1 << kWinBits, kShareRows = 8192, kShares = 256;
 // Spaces in blocked form: at most this many keys (64 windows; a row's piece of a
-// window then still has 13 entries at 850 a row) ...
+// window then still has 13 entries at 850 a row) and rows (what 256 shares of
+// 8192 rows surely take, hbci_share_kernel).  The limits are those of the
+// layout; what it would give past them was not measured.
 constexpr int64_t kBlockMax = (int64_t)64 * kWin;
-constexpr int64_t kBlockMaxRows = (int64_t)(kShareRows / 8 - 1) * kShares;  // ... and rows (hbci_share_kernel)
+constexpr int64_t kBlockMaxRows = (int64_t)(kShareRows / 8 - 1) * kShares;
 constexpr int kBlockLds = (kWin + kShareRows + 16 * kMaxM) * 8;
 
 constexpr double kRoot2 = 1.4142135623730951, kRRoot2 = 0.70710678118654752;
@@ -92,8 +94,9 @@ __device__ __forceinline__ double gather(const DavSpace& a, int64_t q) {
   return p == a.fpos[q] ? t : t * kRoot2;
 }
 
-// True in every thread of the block that comes last of a pass, whose
-// partials (stored with agent scope) are then all visible.
+// True in every thread of the block that comes last of a pass, whose partials
+// (stored and loaded with agent scope, in an order that rests on vmcnt as
+// last_block of davidson_ops.hpp explains) are then all visible.
 __device__ __forceinline__ bool dav_last(DavCtl* c, int* flag) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
@@ -241,8 +244,8 @@ __global__ void __launch_bounds__(kVecThreads) hbci_dav_orth_kernel(DavSpace a, 
 }
 
 // S_m = H V_m from the spread x, and its overlaps with the basis, for spaces
-// past the limits of the blocked form (below), which is the faster one at every
-// size that it takes (on average over a solve: 16.1 us here and 11.1 there at 10
+// past the limits of the blocked form (below), which is the faster one where
+// both were timed (on average over a solve: 16.1 us here and 11.1 there at 10
 // orbitals, 41.8 and 23.3 at 12, both at eps1 = 1 mEh; 48 and 26 at 14 and 2
 // mEh; 338 and 154 at 16, 285020 keys).  One wave per row, 16 neighbouring rows in a workgroup.  Bound by
 // first-level cache misses of the gathers.

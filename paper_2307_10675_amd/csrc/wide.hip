@@ -33,7 +33,7 @@ namespace {
 
 constexpr int kVecThreads = 256;
 constexpr int kVecGrid = 1024;    // persistent grid of the vector steps
-constexpr int kSmallGrid = 512;   // persistent grid of the one-wave steps
+constexpr int kInitGrid = 512;    // persistent grid of the start states (one wave each)
 constexpr int kCompactThreads = 1024;
 
 // Blocks of a vector pass over one increment: four entries a thread, so that
@@ -496,7 +496,7 @@ hipError_t wide_setup(const WideRun& R, hipStream_t s) {
                      dim3(kVecThreads), 0, s, R.items, n);
   hipLaunchKernelGGL(wb_hdiag_kernel, dim3(grid_for((int64_t)n * vec_blocks(d.n_sym), kVecGrid)), dim3(kVecThreads), 0,
                      s, R.items, n);
-  hipLaunchKernelGGL(wb_init_kernel, dim3(grid_for(n, kSmallGrid)), dim3(64), 0, s, R.items, n, R.precision);
+  hipLaunchKernelGGL(wb_init_kernel, dim3(grid_for(n, kInitGrid)), dim3(64), 0, s, R.items, n, R.precision);
   if (sigma_column_supported(d)) {
     hipError_t e = R.precision == IFCI_MIXED ? frags<float>(R, s) : hipSuccess;
     if (e == hipSuccess) e = frags<double>(R, s);
