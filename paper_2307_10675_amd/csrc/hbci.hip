@@ -538,40 +538,6 @@ __global__ void hbci_prep_kernel(const double* __restrict__ h, const double* __r
     const int b = Q - a * (a + 1) / 2;
     ints[k * k + t] = E4(act[i], act[j], act[a], act[b]);
   }
-  __syncthreads();
-  // bounds on H (make_screen)
-  const double* h1 = ints;
-  const double* g = ints + k * k;
-  double* bound = ints + bounds_at(k);
-  const int np = k * (k + 1) / 2;
-  __shared__ unsigned long long top[2];  // non-negative doubles order as their bits
-  if (threadIdx.x < 2) top[threadIdx.x] = 0ull;
-  __syncthreads();
-  for (int t = threadIdx.x; t < np; t += blockDim.x) {
-    int i = 0;
-    while ((i + 1) * (i + 2) / 2 <= t) ++i;
-    const int j = t - i * (i + 1) / 2;
-    double m = 0.0, one = fabs(h1[i * k + j]);
-    for (int w = 0; w < k; ++w) {
-      for (int q = 0; q < w; ++q) m = fmax(m, fabs(G(g, i, j, w, q)));
-      one += 2.0 * fabs(G(g, i, j, w, w)) + fabs(G(g, i, w, w, j));
-    }
-    bound[t] = m;
-    atomicMax(&top[0], (unsigned long long)__double_as_longlong(one * (1.0 + 1e-12)));
-  }
-  const int nd = k * (k - 1) / 2;
-  double same = 0.0;
-  for (int t = threadIdx.x; t < nd * nd; t += blockDim.x) {
-    int p = 1, r = 1;
-    const int u = t / nd, v = t % nd;
-    while ((p + 1) * p / 2 <= u) ++p;
-    while ((r + 1) * r / 2 <= v) ++r;
-    const int q = u - p * (p - 1) / 2, w = v - r * (r - 1) / 2;
-    same = fmax(same, fabs(G(g, r, p, w, q) - G(g, r, q, w, p)));
-  }
-  atomicMax(&top[1], (unsigned long long)__double_as_longlong(same));
-  __syncthreads();
-  if (threadIdx.x < 2) bound[np + threadIdx.x] = __longlong_as_double((long long)top[threadIdx.x]);
   if (threadIdx.x == 0) {
     ctl->n_det = 0;
     ctl->n_ext = 0;
@@ -580,6 +546,59 @@ __global__ void hbci_prep_kernel(const double* __restrict__ h, const double* __r
     ctl->nnz = 0;
     ctl->n_rep = 0;
   }
+}
+
+// The bounds on H of make_screen, one workgroup of 1024 threads: a thread per
+// orbital pair and third orbital, its share of the pair's bounds in LDS.  (A
+// thread per pair, at the end of the kernel above, took 20 us at 10 orbitals and
+// 70 at 14.)
+__global__ void __launch_bounds__(1024) hbci_bounds_kernel(double* __restrict__ ints, int k) {
+  constexpr int kMaxPair = kMaxAct * (kMaxAct + 1) / 2, kMaxUp = kMaxAct * (kMaxAct - 1) / 2;
+  __shared__ double large[kMaxPair * kMaxAct], one[kMaxPair * kMaxAct];
+  __shared__ uint8_t pi[kMaxPair], pj[kMaxPair], up[kMaxUp], uq[kMaxUp];
+  __shared__ unsigned long long top[2];  // non-negative doubles order as their bits
+  const double* h1 = ints;
+  const double* g = ints + k * k;
+  double* bound = ints + bounds_at(k);
+  const int np = k * (k + 1) / 2, nd = k * (k - 1) / 2, tid = threadIdx.x;
+  if (tid < 2) top[tid] = 0ull;
+  if (tid < np) {
+    int i = 0;
+    while ((i + 1) * (i + 2) / 2 <= tid) ++i;
+    pi[tid] = (uint8_t)i;
+    pj[tid] = (uint8_t)(tid - i * (i + 1) / 2);
+  } else if (tid >= 512 && tid - 512 < nd) {
+    int p = 1;
+    while ((p + 1) * p / 2 <= tid - 512) ++p;
+    up[tid - 512] = (uint8_t)p;
+    uq[tid - 512] = (uint8_t)(tid - 512 - p * (p - 1) / 2);
+  }
+  __syncthreads();
+  for (int t = tid; t < np * k; t += 1024) {
+    const int u = t / k, w = t - u * k, i = pi[u], j = pj[u];
+    double m = 0.0;
+    for (int q = 0; q < w; ++q) m = fmax(m, fabs(G(g, i, j, w, q)));
+    large[t] = m;
+    one[t] = 2.0 * fabs(G(g, i, j, w, w)) + fabs(G(g, i, w, w, j));
+  }
+  double same = 0.0;
+  for (int t = tid; t < nd * nd; t += 1024) {
+    const int u = t / nd, v = t - u * nd, p = up[u], q = uq[u], r = up[v], w = uq[v];
+    same = fmax(same, fabs(G(g, r, p, w, q) - G(g, r, q, w, p)));
+  }
+  atomicMax(&top[1], (unsigned long long)__double_as_longlong(same));
+  __syncthreads();
+  if (tid < np) {
+    double m = 0.0, s = fabs(h1[pi[tid] * k + pj[tid]]);
+    for (int w = 0; w < k; ++w) {
+      m = fmax(m, large[tid * k + w]);
+      s += one[tid * k + w];
+    }
+    bound[tid] = m;
+    atomicMax(&top[0], (unsigned long long)__double_as_longlong(s * (1.0 + 1e-12)));
+  }
+  __syncthreads();
+  if (tid < 2) bound[np + tid] = __longlong_as_double((long long)top[tid]);
 }
 
 __global__ void fill_u64_kernel(uint64_t* p, int64_t n, uint64_t v) {
@@ -1475,7 +1494,8 @@ struct Run {
     return hipSuccess;
   }
 
-  hipError_t prepare() {
+  // screen: with the bounds on H that selection and PT2 screen by
+  hipError_t prepare(bool screen) {
     pin = staging();
     if (!pin) return hipErrorOutOfMemory;
     hipError_t e = hipSuccess;
@@ -1490,6 +1510,7 @@ struct Run {
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(hbci_prep_kernel, dim3(1), dim3(256), 0, st, I.h, I.eri, I.n_orb, I.act, I.k, I.core,
                        I.n_core, I.e_core, at<double>(L.ints), at<HbciCtl>(L.ctl));
+    if (screen) hipLaunchKernelGGL(hbci_bounds_kernel, dim3(1), dim3(1024), 0, st, at<double>(L.ints), I.k);
     return hipGetLastError();
   }
 
@@ -1791,7 +1812,7 @@ int64_t hbci_work_bytes(int k, const ifci_hbci_options& o) { return layout(k, o)
 ifci_status hbci_solve(const HbciInc& I, const ifci_hbci_options& o, void* work, double* result, uint64_t* dets_out,
                        double* c_out, hipStream_t st) {
   Run R{I, o, layout(I.k, o), (char*)work, st};
-  HB_TRY(R.prepare(), "hbci prepare");
+  HB_TRY(R.prepare(true), "hbci prepare");
   HB_TRY(R.load_reference(), "hbci load");
   const double shift = R.ctl.e_core + I.e_const;
   int64_t n = (int64_t)R.ctl.n_det, n_rep = 0;
@@ -1859,7 +1880,7 @@ ifci_status hbci_solve(const HbciInc& I, const ifci_hbci_options& o, void* work,
 ifci_status hbci_sigma(const HbciInc& I, const ifci_hbci_options& o, void* work, const uint64_t* dets, int64_t n,
                        const double* c, double* sigma, hipStream_t st) {
   Run R{I, o, layout(I.k, o), (char*)work, st};
-  HB_TRY(R.prepare(), "hbci prepare");
+  HB_TRY(R.prepare(false), "hbci prepare");
   HB_TRY(R.load(dets, n), "hbci load");
   if (R.ctl.flags) return capacity_failure(R.ctl.flags);
   HB_TRY(R.diag(0, n), "hbci diagonal");
@@ -1877,7 +1898,7 @@ ifci_status hbci_sigma(const HbciInc& I, const ifci_hbci_options& o, void* work,
 ifci_status hbci_select(const HbciInc& I, const ifci_hbci_options& o, void* work, const uint64_t* dets, int64_t n,
                         const double* c, double eps1, uint64_t* added, int64_t* n_added, hipStream_t st) {
   Run R{I, o, layout(I.k, o), (char*)work, st};
-  HB_TRY(R.prepare(), "hbci prepare");
+  HB_TRY(R.prepare(true), "hbci prepare");
   HB_TRY(R.load(dets, n), "hbci load");
   if (R.ctl.flags) return capacity_failure(R.ctl.flags);
   HB_TRY(R.select(R.list(), R.at<uint64_t>(R.L.dets), nullptr, n, c, eps1), "hbci select");
@@ -1893,7 +1914,7 @@ ifci_status hbci_select(const HbciInc& I, const ifci_hbci_options& o, void* work
 ifci_status hbci_pt2(const HbciInc& I, const ifci_hbci_options& o, void* work, const uint64_t* dets, int64_t n,
                      const double* c, double e_var, double eps2, double* e_pt2, int64_t* n_ext, hipStream_t st) {
   Run R{I, o, layout(I.k, o), (char*)work, st};
-  HB_TRY(R.prepare(), "hbci prepare");
+  HB_TRY(R.prepare(true), "hbci prepare");
   HB_TRY(R.load(dets, n), "hbci load");
   if (R.ctl.flags) return capacity_failure(R.ctl.flags);
   const double shift = R.ctl.e_core + I.e_const;
