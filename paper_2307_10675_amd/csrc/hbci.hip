@@ -458,7 +458,9 @@ __device__ __forceinline__ void replaced_ranks(const Det& d, const Ranks& R, int
 // the single ones, the same-spin doubles, and the alpha-beta doubles of those
 // single replacements of either spin whose orbital pair has an integral large
 // enough.  (All bounds hold in floating point too: rounding is monotone, and
-// the sums of a single replacement are given a margin.)
+// the sums of a single replacement are given a margin.  A NaN among the
+// integrals makes the bound of the single ones NaN, which excludes none; the
+// others are largest values, which leave out a NaN, as the test itself does.)
 struct Screen {
   int singles, same, na, nb, total;
   const uint8_t *a, *b;  // kept pairs, empty orbital << 4 | occupied
@@ -467,7 +469,7 @@ struct Screen {
 __device__ __forceinline__ Screen make_screen(const Det& d, const Lds& s, double c, double eps, uint8_t* L, int lane) {
   Screen S;
   const double ac = fabs(c);
-  S.singles = s.b_single * ac > eps ? d.sa + d.sb : 0;
+  S.singles = s.b_single * ac <= eps ? 0 : d.sa + d.sb;
   S.same = s.b_same * ac > eps ? d.daa + d.dbb : 0;
   uint8_t* P = L + 32;
   const uint64_t below = (1ull << lane) - 1ull;

@@ -5,7 +5,7 @@ the list form of the product; and a solve that runs out of steps."""
 import numpy as np
 import pytest
 
-from paper_2307_10675_amd import ifci
+from paper_2307_10675_amd import ifci, synthetic
 from tests.helpers import gpu_available
 
 pytestmark = pytest.mark.gpu
@@ -73,3 +73,29 @@ def test_out_of_steps(bodies, max_dav):
     e, rn = _residual(plan, r)
     assert abs(rn - r["residual"]) < 1e-9
     plan.close()
+
+
+def test_selection_beside_an_integral_that_is_not_a_number():
+    """Elements that are NaN pass no threshold; all others are selected as
+    before (from the reference alone: every single replacement but that of the
+    NaN pair, and every double)."""
+    import torch
+    p = synthetic.merged(synthetic.chain(3, seed=5400, order=1))
+    nocc = p.nocc[0]
+    occ, emp = p.bodies[0][nocc - 1], p.bodies[0][nocc]
+    o = ifci.hbci_options(max_det=1 << 12)
+    got = []
+    for bad in (False, True):
+        h = p.h.copy()
+        if bad:
+            h[occ, emp] = h[emp, occ] = float("nan")
+        plan = ifci.Plan(p, tuning=None).attach(h, p.eri)
+        ref = plan.hbci(0, ifci.hbci_options(eps1=1e9, max_iter=1), with_space=True) if not bad else ref
+        one = torch.ones(1, dtype=torch.float64, device="cuda")
+        got.append(set(plan.hbci_select(0, ref["dets"], one, 1e-4, o).cpu().tolist()))
+        plan.close()
+    print(f"[hbci] {len(got[0])} keys, {len(got[1])} beside a NaN", flush=True)
+    key = int(ref["dets"][0])
+    order = sorted(p.bodies[0])
+    bit = 1 << order.index(occ) | 1 << order.index(emp)
+    assert got[1] == got[0] - {key ^ bit, key ^ (bit << 32)} and len(got[1]) == len(got[0]) - 2
